@@ -12,7 +12,8 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspconv.so")
 SOURCES = ["abi.hip", "rulebook.hip", "forward.hip", "forward_w0.hip", "forward_w1.hip",
-           "forward_w2.hip", "ops.hip", "sort.hip", "blockcache.hip", "noalloc.hip"]
+           "forward_w2.hip", "forward_slab_ff.hip", "forward_slab_fb.hip", "forward_slab_bf.hip",
+           "forward_slab_bb.hip", "ops.hip", "sort.hip", "blockcache.hip", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

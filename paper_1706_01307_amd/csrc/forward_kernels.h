@@ -23,8 +23,11 @@
 //   k_fwd_lowc  at most 4 input planes (e.g. the 1 plane of a pen-stroke
 //               input): one lane per (output row, 16 output columns), fp32
 //               FMA chains, weights through the scalar cache.
-//   k_fwd_vec   any other channel count: one lane per (output row, output
-//               column), fp32 FMA chain.
+//   k_fwd_slab  (forward_slab.h) any other channel count on the matrix cores,
+//               rows walked in slabs of channels.
+//   k_fwd_vec   few input planes on small layers, or operands past the
+//               buffer range: one lane per (output row, output column), fp32
+//               FMA chain.
 #pragma once
 
 #include <cstdlib>
@@ -874,21 +877,42 @@ void launch_lowc(const Call& c, int C_in, uint32_t x_bytes) {
       C_in, c.C_out, x_bytes, c.epi);
 }
 
+template <typename TIn, typename TOut>
+constexpr auto slab_entry() {
+  if constexpr (sizeof(TIn) == 4) return sizeof(TOut) == 4 ? forward_slab_ff : forward_slab_fb;
+  else return sizeof(TOut) == 4 ? forward_slab_bf : forward_slab_bb;
+}
+
+// Channel counts k_fwd_mfma is not compiled for.  Returns false for a
+// segmented view that no kernel here takes.
 template <typename TIn, typename TOut, int WT>
-void launch_generic(const Call& c, int C_in) {
-  // one grid row of blocks per kLowCols columns (at most 65535), the inputs
-  // and one offset's map row addressable by a buffer resource (< 2^31 bytes).
-  // Below kLowMinRows positions the one-lane-per-column kernel finishes
-  // first (measured: 460 rows of 16 columns 6.1 us against 7.7 us; 29759
-  // rows of 32 columns 16.4 us against 12.7 us).
+bool launch_generic(const Call& c, int C_in) {
+  // buffer ranges (inputs, weights, one offset's map row) are kept below 2^31
+  // bytes; lowc also needs one grid row of blocks per kLowCols columns (at
+  // most 65535).  Below kLowMinRows positions of few planes the
+  // one-lane-per-column kernel finishes first (measured: 460 rows of 16
+  // columns 6.1 us against 7.7 us; 29759 rows of 32 columns 16.4 us against
+  // 12.7 us).
   constexpr int64_t kLowMinRows = 2048;
   const uint64_t xb = static_cast<uint64_t>(c.v.n_src) * C_in * sizeof(TIn);
-  if (C_in <= kLowCin && c.v.n_cap >= kLowMinRows && c.C_out % kLowCols == 0 &&
-      c.C_out / kLowCols <= 65535 &&
-      xb < kBufOOB && static_cast<uint64_t>(c.v.gstride) * 4 < kBufOOB)
+  const uint64_t wb = static_cast<uint64_t>(c.v.K) * C_in * c.C_out * sizeof(TIn);
+  const bool fits = xb < kBufOOB && static_cast<uint64_t>(c.v.gstride) * 4 < kBufOOB;
+  const bool few = C_in <= kLowCin;
+  if (!c.v.seg && few && fits && c.v.n_cap >= kLowMinRows && c.C_out % kLowCols == 0 &&
+      c.C_out / kLowCols <= 65535) {
     launch_lowc<TIn, TOut, WT>(c, C_in, static_cast<uint32_t>(xb));
-  else
-    launch_vec<TIn, TOut, WT>(c, C_in);
+    return true;
+  }
+  const bool wfits = (c.v.seg ? 1024 * wb : wb) < kBufOOB;
+  if (!force_vector_path() && fits && wfits && (c.v.seg || !few || c.v.n_cap >= kLowMinRows)) {
+    Call cc = c;
+    cc.x_bytes = static_cast<uint32_t>(xb);
+    slab_entry<TIn, TOut>()(cc, WT, C_in, static_cast<uint32_t>(c.v.seg ? 0x7fffffffu : wb));
+    return true;
+  }
+  if (c.v.seg) return false;
+  launch_vec<TIn, TOut, WT>(c, C_in);
+  return true;
 }
 
 template <int WT>
@@ -899,16 +923,10 @@ bool run(const Call& c, int in_dt, int out_dt, int C_in) {
                                 : try_mfma<uint16_t, WT>(c, in_dt, C_in);
   }
   if (done) return true;
-  if (c.v.seg) return false;               // segmented views run on the matrix cores only
-  if (in_dt == SPCONV_F32 && out_dt == SPCONV_F32)
-    launch_generic<float, float, WT>(c, C_in);
-  else if (in_dt == SPCONV_F32)
-    launch_generic<float, uint16_t, WT>(c, C_in);
-  else if (out_dt == SPCONV_F32)
-    launch_generic<uint16_t, float, WT>(c, C_in);
-  else
-    launch_generic<uint16_t, uint16_t, WT>(c, C_in);
-  return true;
+  if (in_dt == SPCONV_F32 && out_dt == SPCONV_F32) return launch_generic<float, float, WT>(c, C_in);
+  if (in_dt == SPCONV_F32) return launch_generic<float, uint16_t, WT>(c, C_in);
+  if (out_dt == SPCONV_F32) return launch_generic<uint16_t, float, WT>(c, C_in);
+  return launch_generic<uint16_t, uint16_t, WT>(c, C_in);
 }
 
 }  // namespace

@@ -60,5 +60,11 @@ struct FwdCall {
 bool forward_run_w0(const FwdCall& c, int in_dt, int out_dt, int C_in);
 bool forward_run_w1(const FwdCall& c, int in_dt, int out_dt, int C_in);
 bool forward_run_w2(const FwdCall& c, int in_dt, int out_dt, int C_in);
+// Any channel counts, by the types of inputs and outputs (f: fp32, b: bf16);
+// c.x_bytes set, w_bytes the bytes of w (both below 2^31).
+void forward_slab_ff(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
+void forward_slab_fb(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
+void forward_slab_bf(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
+void forward_slab_bb(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
 
 }  // namespace spc

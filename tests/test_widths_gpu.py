@@ -1,0 +1,81 @@
+"""Channel counts around the edges of the matrix-core kernels' slabs, column
+tiles and 16-byte pieces, against the oracle: forward, input gradient, weight
+and bias gradients of VSC, SC and DC layers, with and without the block
+epilogue, on layers of several row tiles with a remainder.  The bounds are the
+ones of the other parity tests: per element rtol times the sum of absolute
+terms, rtol 1e-5 for fp32, 2e-2 for bf16, 1e-4 for weight gradients."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import paper_1706_01307_amd as spc  # noqa: E402
+from paper_1706_01307_amd import inputs  # noqa: E402
+from tests import dense_ref  # noqa: E402
+from tests.test_ops_gpu import OP, RTOL_GRAD, _dev, _feats, _odt  # noqa: E402
+from tests.test_parity_gpu import (RTOL_BF16, RTOL_F32, _say, _t, _to_np,  # noqa: E402
+                                   check_features, compare_layer)
+
+pytestmark = pytest.mark.gpu
+
+# one plane past and short of a slab (64 bf16, 32 fp32), of a k-chunk, of a 16-byte piece and of
+# a column tile (32, 64, 96, 128 columns); rows that are no whole pieces on either or both sides
+WIDTHS = [(8, 8), (24, 40), (40, 24), (72, 136), (192, 96), (136, 264), (16, 20), (31, 33),
+          (65, 16), (33, 130), (5, 3), (2, 30), (48, 1), (129, 8)]
+
+
+def _layer(op, dtype):
+    if op == "vsc":
+        coords = inputs.pen_strokes(2, 64, seed=41, target=300)[:513]
+        return coords, [2, 64, 64], [1, 3, 3], [1, 1, 1]
+    f = [1, 2, 2, 2] if dtype == "bf16" else [1, 3, 3, 3]   # single-offset runs / general map
+    return (inputs.surfaces(1, 24, 4.0, 10.0, seed=42, target=700)[:700], [1, 24, 24, 24], f,
+            [1, 2, 2, 2])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("op", ["vsc", "sc", "dc"])
+@pytest.mark.parametrize("ci,co", WIDTHS)
+def test_layer_and_gradients(op, ci, co, dtype):
+    coords, size, f, s = _layer(op, dtype)
+    kind = spc.VSC if op == "vsc" else spc.SC
+    rb = spc.build_rulebook(kind, _t(coords), size, f, s, transpose=op != "vsc")
+    ref = oracle.Rulebook(kind, coords, size, f, s)
+    rin, rout = (ref.n_out, ref.n_in) if op == "dc" else (ref.n_in, ref.n_out)
+    _say(f"[widths] {op} {rin} -> {rout} C={ci}->{co} {dtype}")
+    x, dy = _feats(rin, ci, dtype, 1), _feats(rout, co, dtype, 2)
+    wf = inputs.normal_f32((ref.K, ci, co), std=1.0 / np.sqrt(ref.K * ci), seed=3)
+    w = inputs.to_bf16_bits(wf) if dtype == "bf16" else wf
+    b = inputs.normal_f32((co,), std=0.1, seed=4)
+    rtol = RTOL_F32 if dtype == "f32" else RTOL_BF16
+    fwd = {"vsc": spc.vsc_forward, "sc": spc.sc_forward, "dc": spc.dc_forward}[op]
+    y = fwd(rb, _dev(x, dtype), _dev(w, dtype), _t(b))
+    yo, ab = (ref.dc_forward if op == "dc" else ref.forward)(x, w, b, in_dt=_odt(dtype))
+    check_features(_to_np(y), yo, ab, rtol, "y")
+    dx = spc.backward_data(rb, OP[op][0], _dev(dy, dtype), _dev(w, dtype))
+    dxo, ad = ref.backward_data(OP[op][1], dy, w, _odt(dtype))
+    check_features(_to_np(dx), dxo, ad, rtol, "dx")
+    dw, db = spc.backward_weight(rb, OP[op][0], _dev(x, dtype), _dev(dy, dtype), ci, co)
+    dwo, dbo, aw, adb = ref.backward_weight(OP[op][1], x, dy, ci, co, _odt(dtype))
+    check_features(dw.cpu().numpy(), dwo, aw, RTOL_GRAD, "dw")
+    check_features(db.cpu().numpy(), dbo, adb, RTOL_GRAD, "db")
+    dw2, _ = spc.backward_weight(rb, OP[op][0], _dev(x, dtype), _dev(dy, dtype), ci, co)
+    assert torch.equal(dw, dw2)
+    if op == "vsc":
+        scale = inputs.normal_f32((co,), seed=5)
+        res = _feats(rout, co, dtype, 6)
+        yf = spc.forward_fused(rb, _dev(x, dtype), _dev(w, dtype), scale=_t(scale), shift=_t(b),
+                               residual=_dev(res, dtype), relu=True)
+        y64, a64 = ref.forward(x, w, None, in_dt=_odt(dtype))
+        zo, bound = oracle.fused_epilogue(y64, a64, scale, b, res, True, _odt(dtype))
+        check_features(_to_np(yf), zo, bound, rtol, "fused")
+
+
+@pytest.mark.parametrize("ci,co,dtype", [(40, 24, "f32"), (24, 40, "bf16"), (72, 72, "bf16"),
+                                         (20, 96, "f32")])
+def test_many_rows(ci, co, dtype):
+    """Enough rows for the largest row tiles."""
+    c = dense_ref.random_sites(np.random.default_rng(43), [1, 64, 64, 64], 0.62)
+    compare_layer(spc.VSC, c, [1, 64, 64, 64], [1, 1, 1, 3], [1] * 4, ci, co, dtype=dtype,
+                  what="many rows")
