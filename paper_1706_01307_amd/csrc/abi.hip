@@ -559,6 +559,7 @@ int spconv_backward_weight_workspace(spconv_rulebook rb, int op, int C_in, int C
                                      size_t* bytes) {
   if (!rb || !bytes || C_in < 1 || C_out < 1) return SPCONV_EINVAL;
   if (op == SPCONV_OP_DC ? rb->kind != SPCONV_SC : op != rb->kind) return SPCONV_EINVAL;
+  if (sync_rulebook(rb) == SPCONV_EHIP) return SPCONV_EHIP;   // the chunks follow the row count
   *bytes = backward_weight_workspace(rb, C_in, C_out, op);
   return SPCONV_OK;
 }
@@ -568,12 +569,13 @@ int spconv_backward_weight(spconv_rulebook rb, int op, int dt, const void* x, co
                            size_t workspace_bytes, void* stream) {
   if (!rb || C_in < 1 || C_out < 1 || !dtype_ok(dt) || !dw) return SPCONV_EINVAL;
   if (op == SPCONV_OP_DC ? rb->kind != SPCONV_SC : op != rb->kind) return SPCONV_EINVAL;
-  if (!workspace || workspace_bytes < backward_weight_workspace(rb, C_in, C_out, op))
-    return SPCONV_EINVAL;
+  if (!workspace) return SPCONV_EINVAL;
   if (misaligned(x) || misaligned(dy) || misaligned(workspace) ||
       (reinterpret_cast<uintptr_t>(dw) & 3) || (reinterpret_cast<uintptr_t>(db) & 3))
     return SPCONV_EINVAL;
-  const int st = sync_rulebook(rb);    // the bias gradient needs n_out on the host
+  // the chunks and the bias gradient need n_out on the host
+  const int st = sync_rulebook(rb);
+  if (workspace_bytes < backward_weight_workspace(rb, C_in, C_out, op)) return SPCONV_EINVAL;
   if (st != SPCONV_OK) return st;
   // rows of x and dy: VSC both n_in; SC x n_in, dy n_out; DC the reverse
   const int64_t xr = op == SPCONV_OP_DC ? rb->n_out : rb->n_in;

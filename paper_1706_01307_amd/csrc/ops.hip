@@ -29,11 +29,10 @@
 //
 // Weight gradient dW^i = sum over the pairs of R_i of (input row)^T x (output
 // gradient row): the output positions of the rule book's schedule are cut
-// into chunks of kChunk positions, and chunk c of R_i is its pairs whose
-// output lies in chunk c (at most kChunk of them); one workgroup forms
-// the fp32 partial product of a chunk for a 64x64 tile of dW^i (bf16: on the
-// matrix cores, pairs gathered row-major into LDS and read back transposed;
-// fp32 and odd widths: vector ALU, 4x4 outputs per lane), and a second kernel
+// into chunks of up to 4096 positions, and chunk c of R_i is its pairs whose
+// output lies in chunk c; one workgroup forms the fp32 partial product of a
+// chunk for a tile of dW^i on the matrix cores (pairs gathered row-major into
+// LDS and contracted there), and a second kernel
 // adds the chunks of every entry in ascending chunk order.  The bias
 // gradient sums the output-gradient rows in fixed row chunks the same way.
 // No atomics anywhere: results are bitwise reproducible.
@@ -297,8 +296,9 @@ __global__ __launch_bounds__(256) void k_scatter_transpose(
 // ---------------------------------------------------------------------------
 // Weight and bias gradients
 // ---------------------------------------------------------------------------
-constexpr int64_t kChunk = 4096;   // output positions (so at most as many pairs) per partial
+// One partial covers bpc blocks of kBlock output positions (dw_plan).
 constexpr int kSub = 64;           // pairs staged in LDS at a time
+constexpr int64_t kRowChunk = 512; // rows per bias-gradient partial
 
 // The (offset, chunk) of this workgroup and its pair range inside R_i, from
 // the rule book's per-block bases (blk_base[i][b] = first pair of R_i whose
@@ -310,176 +310,182 @@ struct DwChunk {
   int64_t start, end;      // pair range [start, end) relative to R_i
 };
 __device__ __forceinline__ bool dw_chunk(const int32_t* blk_base, const int64_t* pair_off,
-                                         int64_t nblk, int K, int nchunk, DwChunk* d) {
+                                         int64_t nblk, int K, int nchunk, int bpc, DwChunk* d) {
   const int L = blockIdx.x, xcd = L % 8, q = L / 8;
   d->c = xcd + 8 * (q / K);
   d->i = q % K;
   if (d->c >= nchunk) return false;
-  constexpr int64_t kBpc = kChunk / kBlock;     // rule-book blocks per chunk
-  const int64_t b0 = d->c * kBpc, b1 = b0 + kBpc;
+  const int64_t b0 = static_cast<int64_t>(d->c) * bpc, b1 = b0 + bpc;
   const int64_t k_i = pair_off[d->i + 1] - pair_off[d->i];
   d->start = blk_base[d->i * nblk + b0];
-  d->end = b1 < nblk ? blk_base[d->i * nblk + b1] : k_i;
+  d->end = b1 < nblk && d->c + 1 < nchunk ? blk_base[d->i * nblk + b1] : k_i;
   return true;
 }
-constexpr int64_t kRowChunk = 512;    // rows per bias-gradient partial
 
-// grid: (8 K ceil(nchunk / 8) (offset, chunk) pairs, see dw_chunk; tile);
-// tile = (c-block of 64) x (n-block of 64).
-template <typename T, bool DC>
-__global__ __launch_bounds__(256) void k_dw_partial(
-    const int32_t* __restrict__ pairs, const int64_t* __restrict__ pair_off,
-    const int32_t* __restrict__ blk_base, int64_t nblk, const T* __restrict__ x,
-    const T* __restrict__ dy, int C_in, int C_out, int K, int nchunk, float* __restrict__ part) {
-  __shared__ float s_x[kSub][64 + 1];
-  __shared__ float s_g[kSub][64 + 1];
-  __shared__ int32_t s_a[kSub], s_b[kSub];
-  DwChunk dc_;
-  if (!dw_chunk(blk_base, pair_off, nblk, K, nchunk, &dc_)) return;
-  const int i = dc_.i, chunk = dc_.c;
-  const int ntn = (C_out + 63) / 64;
-  const int c0 = (blockIdx.y / ntn) * 64, n0 = (blockIdx.y % ntn) * 64;
-  const int64_t base = pair_off[i];
-  const int64_t start = dc_.start, end = dc_.end;
-  const int tc = threadIdx.x / 16, tn = threadIdx.x % 16;
-  float acc[4][4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[u][v] = 0.0f;
-  for (int64_t sub = start; sub < end; sub += kSub) {
-    const int np = static_cast<int>(end - sub < kSub ? end - sub : kSub);
-    if (threadIdx.x < np) {
-      const int32_t a = pairs[2 * (base + sub + threadIdx.x)];
-      const int32_t b = pairs[2 * (base + sub + threadIdx.x) + 1];
-      // (input row, gradient row): (a, b) for VSC / SC; DC reads its pairs backwards
-      s_a[threadIdx.x] = DC ? b : a;
-      s_b[threadIdx.x] = DC ? a : b;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < kSub * 64; e += 256) {
-      const int pp = e / 64, cc = e % 64;
-      float xv = 0.0f, gv = 0.0f;
-      if (pp < np) {
-        if (c0 + cc < C_in) xv = IO<T>::ld(x, static_cast<int64_t>(s_a[pp]) * C_in + c0 + cc);
-        if (n0 + cc < C_out) gv = IO<T>::ld(dy, static_cast<int64_t>(s_b[pp]) * C_out + n0 + cc);
-      }
-      s_x[pp][cc] = xv;
-      s_g[pp][cc] = gv;
-    }
-    __syncthreads();
-    for (int pp = 0; pp < np; ++pp) {
-      float xr[4], gr[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) xr[u] = s_x[pp][tc * 4 + u];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) gr[v] = s_g[pp][tn * 4 + v];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fmaf(xr[u], gr[v], acc[u][v]);
-    }
-    __syncthreads();
-  }
-  float* out = part + (static_cast<int64_t>(i) * nchunk + chunk) * C_in * C_out;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int c = c0 + tc * 4 + u;
-    if (c >= C_in) continue;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int n = n0 + tn * 4 + v;
-      if (n < C_out) out[static_cast<int64_t>(c) * C_out + n] = acc[u][v];
-    }
-  }
-}
-
-// Matrix-core partial products (bf16 inputs, fp32 accumulation): grid
-// (chunk, offset, 64x64 tile of dW^i).  Per step 64 pairs: their input rows
-// and gradient rows (this tile's 64 columns of each) are gathered into LDS
-// row-major, 8 lanes per 128-byte row; wave w multiplies all pairs of the
-// step, 32 at a time in order, into its own 32x32 quadrant of the tile (so
-// each result is one in-order sum, written straight out, and a wave holds 16
-// accumulator registers; with 64-pair steps four workgroups share a compute
-// unit, which hides the gathers' latency better than larger steps with fewer
-// workgroups).
-// The contraction runs over pairs, so an operand fragment holds one channel
-// of 8 consecutive pairs: it comes from the row-major tile through gfx950's
-// transposing LDS read (16 lanes read 4 pairs x 16 channels, each lane
-// receives one channel of the 4 pairs).  Columns past C_in / C_out are zero.
+// Matrix-core partial products of dW^i (fp32 accumulation): grid (the
+// (offset, chunk) pairs of dw_chunk; TC x TN tile of dW^i).  Per step 64
+// pairs: their input rows and gradient rows (this tile's columns of each) are
+// gathered into LDS row-major; the contraction runs over pairs, on 32x32
+// products (32x32x16 bf16, 32x32x2 fp32).  The tile's 32x32 quadrants are
+// dealt to the four waves; where there are fewer than four, the waves of one
+// quadrant share each step's pairs and their sums are added in wave order at
+// the end.  So every result is a fixed-order sum, and a wave holds 16
+// accumulator registers (four workgroups share a compute unit, which hides
+// the gathers' latency better than larger steps with fewer workgroups).
+//   bf16: an operand fragment holds one channel of 8 consecutive pairs; it
+//   comes from the row-major tile through gfx950's transposing LDS read (16
+//   lanes read 4 pairs x 16 channels, each receives one channel of the 4
+//   pairs).  fp32: one channel of one pair per lane, a plain 4-byte read.
+// Columns past C_in / C_out are zero.  AL: rows are whole 16-byte pieces;
+// otherwise single elements are loaded.
+//
+// Measured: fp32, 348,208 surface rows 32 x 32 3^3, 1,143 us with the vector
+// ALU kernel this replaced (64x64 tiles whatever the widths); 165 us
+// here.
+// (MFMA floor 53 us, gathers 1 GB).  bf16, 902,504 surface rows 64 x 64 3^3:
+// 256 us with 16x16x32 products and one set of tiles, 252 us with 32x32x16 and
+// two.
 // dbpart != NULL (VSC): the workgroups of the centre offset, whose pairs are
 // every output row once, also sum the gradient rows (the bias gradient) with
-// two more products per 32 pairs, a fragment of ones times the staged rows,
-// in waves 0 and 1 of the first channel tile; dbpart[chunk][n] receives the
+// one more product per fragment, a fragment of ones times the staged rows, in
+// the waves of the first channel quadrant; dbpart[chunk][n] receives the
 // chunk's column sums.
 typedef short dw_s4 __attribute__((ext_vector_type(4)));
 typedef __bf16 dw_bf8 __attribute__((ext_vector_type(8)));
-typedef float dw_f4 __attribute__((ext_vector_type(4)));
+typedef float dw_f16 __attribute__((ext_vector_type(16)));
 typedef unsigned dw_u4 __attribute__((ext_vector_type(4)));
 
-// Tiles of 64-channel rows (128 bytes) in LDS store the 16-byte chunk k of
-// row r at chunk k ^ (r & 7): the rows read together by one transposing read
-// then fall on different banks (unswizzled 128-byte rows all start on the
-// same bank).
-__device__ __forceinline__ int dw_swz(int row, int col) {
-  return row * 64 + ((((col >> 3) ^ (row & 7)) << 3) | (col & 7));
+// Element types: KS pairs per product; frag() reads channels c0 .. c0 + 31 of
+// pairs p0 .. p0 + KS - 1 from a tile of W-channel rows; swz() places 16-byte
+// piece k of row r so that the rows of one read fall on different banks
+// (256-byte bank period; narrow tiles are contiguous there already).
+template <typename T> struct Dw;
+template <> struct Dw<uint16_t> {
+  static constexpr int KS = 16;
+  typedef dw_bf8 Frag;
+  template <int W> __device__ static int at(int row, int col) {
+    const int k = W == 64 ? (col >> 3) ^ (((row >> 1) & 1) << 2) : col >> 3;
+    return row * W + ((k << 3) | (col & 7));
+  }
+  template <int W> __device__ static Frag frag(const uint16_t* tile, int p0, int c0, int lane) {
+    // lanes 16q + j: pairs p0 + 8 (q / 2) + j / 4 (+4 for the upper half),
+    // channels c0 + 16 (q % 2) + 4 (j % 4) .. + 3
+    const int j = lane & 15, q = lane >> 4;
+    const int row = p0 + 8 * (q >> 1) + (j >> 2), col = c0 + 16 * (q & 1) + 4 * (j & 3);
+    typedef __attribute__((address_space(3))) dw_s4 lds_s4;
+    // generic -> LDS address-space conversion (the tile is a __shared__ array)
+    lds_s4* lo = (lds_s4*)(const_cast<uint16_t*>(tile) + at<W>(row, col));
+    lds_s4* hi = (lds_s4*)(const_cast<uint16_t*>(tile) + at<W>(row + 4, col));
+    const dw_s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lo);
+    const dw_s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16(hi);
+    typedef short s8 __attribute__((ext_vector_type(8)));
+    const s8 v = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    return __builtin_bit_cast(dw_bf8, v);
+  }
+  __device__ static Frag ones() {
+    Frag f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) f[k] = static_cast<__bf16>(1.0f);
+    return f;
+  }
+  __device__ static dw_f16 mma(Frag a, Frag b, dw_f16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  }
+};
+template <> struct Dw<float> {
+  static constexpr int KS = 2;
+  typedef float Frag;
+  template <int W> __device__ static int at(int row, int col) {
+    const int k = W == 64 ? (col >> 2) ^ ((row & 1) << 3) : col >> 2;
+    return row * W + ((k << 2) | (col & 3));
+  }
+  template <int W> __device__ static Frag frag(const float* tile, int p0, int c0, int lane) {
+    return tile[at<W>(p0 + (lane >> 5), c0 + (lane & 31))];
+  }
+  __device__ static Frag ones() { return 1.0f; }
+  __device__ static dw_f16 mma(Frag a, Frag b, dw_f16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+  }
+};
+
+// The 16 bytes of columns c .. of row `row`, zero where ok is false or past
+// `width` columns.  AL: one load (row 0, column 0 when not ok); the caller
+// zeroes.  Otherwise element loads, each from a column that exists.
+template <typename T, bool AL>
+__device__ __forceinline__ dw_u4 dw_piece(const T* __restrict__ p, int64_t row, int64_t width,
+                                          int c, bool ok) {
+  if constexpr (AL) {
+    return *reinterpret_cast<const dw_u4*>(p + (ok ? row * width + c : 0));
+  } else {
+    const int64_t base = ok ? row * width : 0;
+    dw_u4 v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if constexpr (sizeof(T) == 4) {
+        const int e = c + q;
+        const uint32_t u = __float_as_uint(p[base + (e < width ? e : 0)]);
+        v[q] = e < width ? u : 0u;
+      } else {
+        const int e = c + 2 * q;
+        const uint32_t lo = p[base + (e < width ? e : 0)];
+        const uint32_t hi = p[base + (e + 1 < width ? e + 1 : 0)];
+        v[q] = (e < width ? lo : 0u) | (e + 1 < width ? hi << 16 : 0u);
+      }
+    }
+    return v;
+  }
 }
 
-__device__ __forceinline__ dw_bf8 tr_frag(const uint16_t* tile, int p0, int c0, int lane) {
-  // lanes 16q + j: pairs p0 + 8q + j/4 (+4 for the upper half), channels c0 + 4(j%4)..+3
-  const int j = lane & 15, q = lane >> 4;
-  const int row = p0 + 8 * q + (j >> 2), col = c0 + 4 * (j & 3);
-  typedef __attribute__((address_space(3))) dw_s4 lds_s4;
-  // generic -> LDS address-space conversion (the tile is a __shared__ array)
-  lds_s4* lo = (lds_s4*)(const_cast<uint16_t*>(tile) + dw_swz(row, col));
-  lds_s4* hi = (lds_s4*)(const_cast<uint16_t*>(tile) + dw_swz(row + 4, col));
-  const dw_s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lo);
-  const dw_s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16(hi);
-  typedef short s8 __attribute__((ext_vector_type(8)));
-  const s8 v = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  return __builtin_bit_cast(dw_bf8, v);
-}
-
-template <bool DC>
-__global__ __launch_bounds__(256, 4) void k_dw_mfma(
+template <typename T, bool DC, int TC, int TN, bool AL>
+__global__ __launch_bounds__(256, !AL ? 2 : (sizeof(T) == 4 && TC != TN ? 3 : 4)) void k_dw_mfma(
     const int32_t* __restrict__ pairs, const int64_t* __restrict__ pair_off,
-    const int32_t* __restrict__ blk_base, int64_t nblk, const uint16_t* __restrict__ x,
-    const uint16_t* __restrict__ dy, int C_in, int C_out, int K, int nchunk,
+    const int32_t* __restrict__ blk_base, int64_t nblk, const T* __restrict__ x,
+    const T* __restrict__ dy, int C_in, int C_out, int K, int nchunk, int bpc,
     float* __restrict__ part, int centre, float* __restrict__ dbpart) {
-  constexpr int STEP = 64;
-  constexpr int PASS = STEP / 32;                      // 32 rows per pass of 256 lanes
-  // staging tiles and a ring of the pairs of four steps: 18 KB
-  __shared__ __attribute__((aligned(16))) uint16_t s_buf[2 * STEP * 64];
+  using E = Dw<T>;
+  constexpr int STEP = kSub;
+  constexpr int EPP = 16 / static_cast<int>(sizeof(T));   // elements per 16-byte piece
+  constexpr int LX = TC / EPP, LG = TN / EPP;             // lanes per staged row
+  constexpr int PX = STEP * LX / 256, PG = STEP * LG / 256;   // passes of 256 lanes
+  static_assert(PX >= 1 && PG >= 1, "a step fills the workgroup");
+  constexpr int NQ = (TC / 32) * (TN / 32);               // quadrants
+  constexpr int NS = 4 / NQ;                              // waves per quadrant
+  constexpr int GRP = STEP / E::KS;                       // products per step
+  // staging tiles (and, at the end, the waves' sums) and a ring of the pairs
+  // of four steps; two sets of tiles while four workgroups still fit a compute
+  // unit (the rows of step t + 1 then need no barrier of their own)
+  constexpr int kTiles = STEP * (TC + TN);
+  constexpr int kSums = (NS - 1) * NQ * 1024 * 4, kTileBytes = kTiles * static_cast<int>(sizeof(T));
+  constexpr int NB = kTileBytes <= 16384 ? 2 : 1;
+  __shared__ __attribute__((aligned(16)))
+  unsigned char s_buf[kSums > NB * kTileBytes ? kSums : NB * kTileBytes];
   __shared__ int2 s_pr[4][STEP];
-  uint16_t* s_x = s_buf;
-  uint16_t* s_g = s_buf + STEP * 64;
+  T* const s_t = reinterpret_cast<T*>(s_buf);         // buffer t % NB: x rows, then dy rows
   DwChunk dc_;
-  if (!dw_chunk(blk_base, pair_off, nblk, K, nchunk, &dc_)) return;
+  if (!dw_chunk(blk_base, pair_off, nblk, K, nchunk, bpc, &dc_)) return;
   const int i = dc_.i, chunk = dc_.c;
-  const int ntn = (C_out + 63) / 64;
-  const int c0 = (blockIdx.y / ntn) * 64, n0 = (blockIdx.y % ntn) * 64;
+  const int ntn = (C_out + TN - 1) / TN;
+  const int c0 = (blockIdx.y / ntn) * TC, n0 = (blockIdx.y % ntn) * TN;
   const int64_t base = pair_off[i];
   const int64_t start = dc_.start, end = dc_.end;
   const int nsteps = static_cast<int>((end - start + STEP - 1) / STEP);
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int cx = C_in - c0 < 64 ? C_in - c0 : 64;     // valid columns of this tile
-  const int cg = C_out - n0 < 64 ? C_out - n0 : 64;
   float* out = part + (static_cast<int64_t>(i) * nchunk + chunk) * C_in * C_out;
   const bool dbt = dbpart && i == centre && c0 == 0;    // this tile sums the bias gradient
   if (nsteps == 0) {                                   // no pair of R_i in this chunk
-    for (int t = threadIdx.x; t < 64 * 64; t += 256) {
-      const int c = c0 + t / 64, n = n0 + t % 64;
+    for (int t = threadIdx.x; t < TC * TN; t += 256) {
+      const int c = c0 + t / TN, n = n0 + t % TN;
       if (c < C_in && n < C_out) out[static_cast<int64_t>(c) * C_out + n] = 0.0f;
     }
-    if (dbt && threadIdx.x < 64 && n0 + threadIdx.x < C_out)
+    if (dbt && threadIdx.x < TN && n0 + threadIdx.x < C_out)
       dbpart[static_cast<int64_t>(chunk) * C_out + n0 + threadIdx.x] = 0.0f;
     return;
   }
 
   // Over steps of STEP pairs: at step t the pairs of step t + 3 are loaded
-  // (threads 0..STEP-1, one each) and, after the MFMAs, put in the LDS ring;
+  // (threads 0..STEP-1, one each) and, after the products, put in the LDS ring;
   // the data rows of step t + 2 are gathered (their pairs from the ring) into
-  // one of two register sets, the MFMAs of step t run on the LDS tiles, and
+  // one of two register sets, the products of step t run on the LDS tiles, and
   // the rows of step t + 1 (the other set) are written to LDS.  Every load is
   // unconditional (pairs past the chunk read its first pair; rows past the
   // chunk and columns past C read row 0 / column 0 and are zeroed when
@@ -487,9 +493,10 @@ __global__ __launch_bounds__(256, 4) void k_dw_mfma(
   // before the rows) lets the in-order load counter keep the rows in flight
   // while the pair is waited on.
   const int npairs = static_cast<int>(end - start);
-  const int ch = (threadIdx.x % 8) * 8;                // this lane's 8 columns
-  const bool colx = ch < cx, colg = ch < cg;
-  typedef dw_u4 Rows[PASS];
+  const int chx = (threadIdx.x % LX) * EPP, chg = (threadIdx.x % LG) * EPP;
+  const bool colx = c0 + chx < C_in, colg = n0 + chg < C_out;
+  typedef dw_u4 RowsX[PX];
+  typedef dw_u4 RowsG[PG];
   auto pair_load = [&](int t) __attribute__((always_inline)) -> int2 {
     const int e = t * STEP + (threadIdx.x < STEP ? threadIdx.x : 0);
     return *reinterpret_cast<const int2*>(pairs + 2 * (base + start + (e < npairs ? e : 0)));
@@ -497,47 +504,54 @@ __global__ __launch_bounds__(256, 4) void k_dw_mfma(
   auto pair_put = [&](int t, int2 v) __attribute__((always_inline)) {
     if (threadIdx.x < STEP) s_pr[t & 3][threadIdx.x] = v;
   };
-  auto gather = [&](int t, Rows& vx, Rows& vg, uint32_t& ok) __attribute__((always_inline)) {
+  auto gather = [&](int t, RowsX& vx, RowsG& vg, uint32_t& ok) __attribute__((always_inline)) {
     ok = 0;
 #pragma unroll
-    for (int pass = 0; pass < PASS; ++pass) {
-      const int e = t * STEP + pass * 32 + threadIdx.x / 8;
-      const int2 pr = s_pr[t & 3][pass * 32 + threadIdx.x / 8];
+    for (int p = 0; p < PX; ++p) {
+      const int r = p * (256 / LX) + threadIdx.x / LX;
+      const int2 pr = s_pr[t & 3][r];
       // (input row, gradient row); DC reads its pairs backwards
-      const int32_t ra = DC ? pr.y : pr.x, rg = DC ? pr.x : pr.y;
-      const bool okx = e < npairs && colx, okg = e < npairs && colg;
-      ok |= (okx ? 1u : 0u) << (2 * pass) | (okg ? 2u : 0u) << (2 * pass);
-      vx[pass] = *reinterpret_cast<const dw_u4*>(
-          x + (okx ? static_cast<int64_t>(ra) * C_in + c0 + ch : 0));
-      vg[pass] = *reinterpret_cast<const dw_u4*>(
-          dy + (okg ? static_cast<int64_t>(rg) * C_out + n0 + ch : 0));
+      const bool o = t * STEP + r < npairs && colx;
+      ok |= (o ? 1u : 0u) << p;
+      vx[p] = dw_piece<T, AL>(x, DC ? pr.y : pr.x, C_in, c0 + chx, o);
+    }
+#pragma unroll
+    for (int p = 0; p < PG; ++p) {
+      const int r = p * (256 / LG) + threadIdx.x / LG;
+      const int2 pr = s_pr[t & 3][r];
+      const bool o = t * STEP + r < npairs && colg;
+      ok |= (o ? 1u : 0u) << (8 + p);
+      vg[p] = dw_piece<T, AL>(dy, DC ? pr.x : pr.y, C_out, n0 + chg, o);
     }
   };
-  auto stage = [&](const Rows& vx, const Rows& vg, uint32_t ok) __attribute__((always_inline)) {
+  auto stage = [&](int t, const RowsX& vx, const RowsG& vg, uint32_t ok)
+      __attribute__((always_inline)) {
+    T* s_x = s_t + (t % NB) * kTiles;
+    T* s_g = s_x + STEP * TC;
     const dw_u4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int pass = 0; pass < PASS; ++pass) {
-      const int pp = pass * 32 + threadIdx.x / 8;
-      *reinterpret_cast<dw_u4*>(&s_x[dw_swz(pp, ch)]) = (ok >> (2 * pass)) & 1u ? vx[pass] : z;
-      *reinterpret_cast<dw_u4*>(&s_g[dw_swz(pp, ch)]) = (ok >> (2 * pass)) & 2u ? vg[pass] : z;
-    }
+    for (int p = 0; p < PX; ++p)
+      *reinterpret_cast<dw_u4*>(
+          &s_x[E::template at<TC>(p * (256 / LX) + threadIdx.x / LX, chx)]) =
+          (ok >> p) & 1u ? vx[p] : z;
+#pragma unroll
+    for (int p = 0; p < PG; ++p)
+      *reinterpret_cast<dw_u4*>(
+          &s_g[E::template at<TN>(p * (256 / LG) + threadIdx.x / LG, chg)]) =
+          (ok >> (8 + p)) & 1u ? vg[p] : z;
   };
 
-  // wave w owns the 32 x 32 quadrant (channel blocks 2 (w / 2) + uu, gradient
-  // blocks 2 (w % 2) + vv) of the 64 x 64 tile, over all pairs of the chunk
-  const int ub = 2 * (wave / 2), vb = 2 * (wave % 2);
-  dw_f4 acc[2][2];
+  // wave -> quadrant (qc, qn) and share ks of every step's products
+  const int quad = wave % NQ, ks = wave / NQ;
+  const int qc = quad / (TN / 32) * 32, qn = quad % (TN / 32) * 32;
+  dw_f16 acc, accb;
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int v = 0; v < 2; ++v) acc[u][v] = dw_f4{0.f, 0.f, 0.f, 0.f};
-  const bool dbw = dbt && wave < 2;                    // waves 0, 1 cover all 4 column blocks
-  dw_f4 accb[2] = {dw_f4{0.f, 0.f, 0.f, 0.f}, dw_f4{0.f, 0.f, 0.f, 0.f}};
-  dw_bf8 ones;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) ones[k] = static_cast<__bf16>(1.0f);
+  for (int e = 0; e < 16; ++e) acc[e] = accb[e] = 0.0f;
+  const bool dbw = dbt && qc == 0;
+  const typename E::Frag ones = E::ones();
 
-  Rows xa, ga, xb, gb;
+  RowsX xa, xb;
+  RowsG ga, gb;
   uint32_t oka = 0, okb = 0;
   pair_put(0, pair_load(0));
   pair_put(1, pair_load(1));
@@ -545,35 +559,27 @@ __global__ __launch_bounds__(256, 4) void k_dw_mfma(
   __syncthreads();
   gather(0, xa, ga, oka);
   gather(1, xb, gb, okb);
-  stage(xa, ga, oka);
+  stage(0, xa, ga, oka);
   __syncthreads();
   // step t: the set holding step t + 1 is `nx`, the free set `fr`
   // (the gather of step t + 2 is issued even past the last step, as rows that
   // are all zeroed, so that the number of loads in flight never depends on t)
-  auto step = [&](int t, Rows& nxx, Rows& nxg, uint32_t& nok, Rows& frx, Rows& frg,
+  auto step = [&](int t, RowsX& nxx, RowsG& nxg, uint32_t& nok, RowsX& frx, RowsG& frg,
                   uint32_t& fok) __attribute__((always_inline)) {
     const int2 pn = pair_load(t + 3);
     gather(t + 2, frx, frg, fok);
+    const T* s_x = s_t + (t % NB) * kTiles;
+    const T* s_g = s_x + STEP * TC;
 #pragma unroll
-    for (int kc = 0; kc < STEP / 32; ++kc) {   // the step's pairs, 32 at a time, in order
-      dw_bf8 fa[2], fb[2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) fa[u] = tr_frag(s_x, kc * 32, (ub + u) * 16, lane);
-#pragma unroll
-      for (int v = 0; v < 2; ++v) fb[v] = tr_frag(s_g, kc * 32, (vb + v) * 16, lane);
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 2; ++v)
-          acc[u][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[u], fb[v], acc[u][v], 0, 0, 0);
-      if (dbw) {
-#pragma unroll
-        for (int v = 0; v < 2; ++v)
-          accb[v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, fb[v], accb[v], 0, 0, 0);
-      }
+    for (int g = 0; g < GRP / NS; ++g) {        // this wave's share of the pairs, in order
+      const int p0 = (ks * (GRP / NS) + g) * E::KS;
+      const typename E::Frag fa = E::template frag<TC>(s_x, p0, qc, lane);
+      const typename E::Frag fb = E::template frag<TN>(s_g, p0, qn, lane);
+      acc = E::mma(fa, fb, acc);
+      if (dbw) accb = E::mma(ones, fb, accb);
     }
-    __syncthreads();                           // tiles (and ring slot t + 3 = t - 1) free
-    if (t + 1 < nsteps) stage(nxx, nxg, nok);
+    if (NB == 1) __syncthreads();              // the tiles are read
+    if (t + 1 < nsteps) stage(t + 1, nxx, nxg, nok);
     pair_put(t + 3, pn);
     __syncthreads();
   };
@@ -583,24 +589,39 @@ __global__ __launch_bounds__(256, 4) void k_dw_mfma(
     step(t + 1, xa, ga, oka, xb, gb, okb);
   }
   if (t < nsteps) step(t, xb, gb, okb, xa, ga, oka);
-  // lane (r, g) holds rows 4g + e, column r of each 16x16 block
-  const int r = lane % 16, g = lane / 16;
+  // the sums of a quadrant's waves, added in wave order (the tiles are free:
+  // the last step ended with a barrier)
+  if constexpr (NS > 1) {
+    float* s_sum = reinterpret_cast<float*>(s_buf);
+    auto add = [&](dw_f16& a) {
+      if (ks > 0) {
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int v = 0; v < 2; ++v)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int c = c0 + (ub + u) * 16 + 4 * g + e, n = n0 + (vb + v) * 16 + r;
-        if (c < C_in && n < C_out) out[static_cast<int64_t>(c) * C_out + n] = acc[u][v][e];
+        for (int e = 0; e < 16; ++e) s_sum[(((ks - 1) * NQ + quad) * 16 + e) * 64 + lane] = a[e];
       }
-  if (dbw && g == 0) {                                 // every row of accb holds the sums
+      __syncthreads();
+      if (ks == 0) {
 #pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      const int n = n0 + (vb + v) * 16 + r;
-      if (n < C_out) dbpart[static_cast<int64_t>(chunk) * C_out + n] = accb[v][0];
-    }
+        for (int k = 0; k < NS - 1; ++k)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) a[e] += s_sum[((k * NQ + quad) * 16 + e) * 64 + lane];
+      }
+      __syncthreads();
+    };
+    add(acc);
+    if (dbt) add(accb);                        // workgroup-uniform
   }
+  if (ks > 0) return;
+  // lane (r, h) holds rows 8 (e / 4) + 4 h + e % 4, column r of its quadrant
+  const int r = lane % 32, h = lane / 32;
+  const int n = n0 + qn + r;
+  if (n >= C_out) return;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int c = c0 + qc + 8 * (e / 4) + 4 * h + e % 4;
+    if (c < C_in) out[static_cast<int64_t>(c) * C_out + n] = acc[e];
+  }
+  if (dbw && h == 0)                           // every row of accb holds the sums
+    dbpart[static_cast<int64_t>(chunk) * C_out + n] = accb[0];
 }
 
 // Bias gradient, stage 2 (workgroups of k_dw_reduce past the weight's): 4
@@ -752,9 +773,60 @@ __global__ __launch_bounds__(256) void k_db_partial(const T* __restrict__ dy, in
 }
 
 
-int64_t dw_nchunk(spconv_rulebook rb) {
-  constexpr int64_t kBpc = kChunk / kBlock;
-  return (rb->nblk + kBpc - 1) / kBpc;
+// How the output positions are cut into partials: bpc blocks of kBlock
+// positions each.  16 blocks (4096 positions: a row the K offsets share comes
+// back while it is in L2), fewer while that leaves the device short of
+// workgroups (4096: four rounds of four per compute unit; 2048 left the fp32
+// layer above 20 us slower, 16,384 gained nothing) and the partials
+// stay small (29,760 pen-stroke rows 32 x 32 fp32 3x3 have 72 workgroups of
+// 4096 positions, 1,053 of 256).  The row count is the host's best knowledge,
+// so a book's plan may change when it is synchronised; the workspace query
+// and the gradient both synchronise first.
+struct DwPlan {
+  int nchunk, bpc, tc, tn;
+};
+DwPlan dw_plan(spconv_rulebook rb, int C_in, int C_out) {
+  DwPlan p;
+  p.tc = C_in <= 32 ? 32 : 64;
+  p.tn = C_out <= 32 ? 32 : 64;
+  const int64_t rows = rb->synced && rb->n_out < rb->n_cap ? rb->n_out : rb->n_cap;
+  const int64_t nblk = (rows + kBlock - 1) / kBlock;
+  const int64_t tiles = static_cast<int64_t>((C_in + p.tc - 1) / p.tc) *
+                        ((C_out + p.tn - 1) / p.tn);
+  const int64_t per = 4ll * C_in * C_out * rb->K;        // bytes of one chunk's partials
+  p.bpc = 16;
+  while (p.bpc > 1 && rb->K * tiles * ((nblk + p.bpc - 1) / p.bpc) < 4096 &&
+         per * ((nblk + p.bpc / 2 - 1) / (p.bpc / 2)) <= (32ll << 20))
+    p.bpc /= 2;
+  p.nchunk = static_cast<int>((nblk + p.bpc - 1) / p.bpc);
+  return p;
+}
+
+template <typename T, int TC, int TN>
+void launch_dw(spconv_rulebook rb, const DwPlan& p, bool dc, const void* x, const void* dy,
+               int C_in, int C_out, float* part, int centre, float* dbpart, hipStream_t st) {
+  constexpr int EPP = 16 / static_cast<int>(sizeof(T));
+  const int K = static_cast<int>(rb->K);
+  const int tiles = ((C_in + TC - 1) / TC) * ((C_out + TN - 1) / TN);
+  // (offset, chunk) pairs: 8 XCDs x K offsets x ceil(nchunk / 8) chunks each
+  const dim3 grid(static_cast<unsigned>(8 * K * ((p.nchunk + 7) / 8)),
+                  static_cast<unsigned>(tiles));
+  // C % EPP == 0 keeps every gathered 16-byte load inside its row
+  const bool al = C_in % EPP == 0 && C_out % EPP == 0;
+  auto kern = al ? (dc ? k_dw_mfma<T, true, TC, TN, true> : k_dw_mfma<T, false, TC, TN, true>)
+                 : (dc ? k_dw_mfma<T, true, TC, TN, false> : k_dw_mfma<T, false, TC, TN, false>);
+  kern<<<grid, 256, 0, st>>>(rb->pairs, rb->pair_off, rb->blk_cnt, rb->nblk,
+                             static_cast<const T*>(x), static_cast<const T*>(dy), C_in, C_out, K,
+                             p.nchunk, p.bpc, part, centre, dbpart);
+}
+
+template <typename T>
+void launch_dw_tile(spconv_rulebook rb, const DwPlan& p, bool dc, const void* x, const void* dy,
+                    int C_in, int C_out, float* part, int centre, float* dbpart,
+                    hipStream_t st) {
+  auto f = p.tc == 32 ? (p.tn == 32 ? launch_dw<T, 32, 32> : launch_dw<T, 32, 64>)
+                      : (p.tn == 32 ? launch_dw<T, 64, 32> : launch_dw<T, 64, 64>);
+  f(rb, p, dc, x, dy, C_in, C_out, part, centre, dbpart, st);
 }
 
 }  // namespace
@@ -939,50 +1011,29 @@ FwdView transpose_view(spconv_rulebook rb) {
 size_t backward_weight_workspace(spconv_rulebook rb, int C_in, int C_out, int op) {
   const int64_t rows = op == SPCONV_OP_DC ? rb->n_in : rb->n_cap;
   const int64_t nrc = (rows + kRowChunk - 1) / kRowChunk;
-  return static_cast<size_t>(rb->K * dw_nchunk(rb)) * C_in * C_out * 4 +
-         static_cast<size_t>(nrc > 0 ? nrc : 1) * C_out * 4 + 256;  // nrc >= the chunk count
+  const int64_t nchunk = dw_plan(rb, C_in, C_out).nchunk;
+  return static_cast<size_t>(rb->K * nchunk) * C_in * C_out * 4 +
+         static_cast<size_t>(nrc > nchunk ? nrc : nchunk + 1) * C_out * 4 + 256;
 }
 
 int backward_weight(spconv_rulebook rb, int op, int dt, const void* x, const void* dy, float* dw,
                     float* db, int C_in, int C_out, void* ws, hipStream_t st) {
-  const int nchunk = static_cast<int>(dw_nchunk(rb));
+  const DwPlan plan = dw_plan(rb, C_in, C_out);
+  const int nchunk = plan.nchunk;
   const int K = static_cast<int>(rb->K);
   float* part = static_cast<float*>(ws);
   const int64_t per = static_cast<int64_t>(C_in) * C_out;
-  // VSC on the matrix cores: the bias gradient comes from the weight
-  // gradient's centre-offset workgroups (its pairs are every output row once,
-  // each with itself), per chunk, into the bias partials' area (at least
-  // nchunk rows of C_out floats)
+  // VSC: the bias gradient comes from the weight gradient's centre-offset
+  // workgroups (its pairs are every output row once, each with itself), per
+  // chunk, into the bias partials' area (at least nchunk rows of C_out floats)
   int centre = 0;
   for (int j = 0; j < rb->D; ++j) centre = centre * rb->f[j] + (rb->f[j] - 1) / 2;
-  const bool db_fused = db && op == SPCONV_OP_VSC && nchunk > 0 && dt == SPCONV_BF16 &&
-                        C_in % 8 == 0 && C_out % 8 == 0;
+  const bool db_fused = db && op == SPCONV_OP_VSC && nchunk > 0;
   float* partb_fused = part + static_cast<int64_t>(rb->K) * nchunk * per;
-  if (nchunk > 0) {
-    const int tiles = ((C_in + 63) / 64) * ((C_out + 63) / 64);
-    // (offset, chunk) pairs: 8 XCDs x K offsets x ceil(nchunk / 8) chunks each
-    dim3 grid(static_cast<unsigned>(8 * K * ((nchunk + 7) / 8)), static_cast<unsigned>(tiles));
-    const bool dc = op == SPCONV_OP_DC;
-    // matrix cores for bf16 rows of whole 16-byte chunks (C % 8 == 0 keeps
-    // every gathered 16-byte load inside its row)
-    if (dt == SPCONV_BF16 && C_in % 8 == 0 && C_out % 8 == 0) {
-      auto kern = dc ? k_dw_mfma<true> : k_dw_mfma<false>;
-      kern<<<grid, 256, 0, st>>>(rb->pairs, rb->pair_off, rb->blk_cnt, rb->nblk,
-                                 static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(dy),
-                                 C_in, C_out, K, nchunk, part, db_fused ? centre : -1,
-                                 db_fused ? partb_fused : nullptr);
-    } else if (dt == SPCONV_F32) {
-      auto kern = dc ? k_dw_partial<float, true> : k_dw_partial<float, false>;
-      kern<<<grid, 256, 0, st>>>(rb->pairs, rb->pair_off, rb->blk_cnt, rb->nblk,
-                                 static_cast<const float*>(x), static_cast<const float*>(dy), C_in,
-                                 C_out, K, nchunk, part);
-    } else {
-      auto kern = dc ? k_dw_partial<uint16_t, true> : k_dw_partial<uint16_t, false>;
-      kern<<<grid, 256, 0, st>>>(rb->pairs, rb->pair_off, rb->blk_cnt, rb->nblk,
-                                 static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(dy),
-                                 C_in, C_out, K, nchunk, part);
-    }
-  }
+  if (nchunk > 0)
+    (dt == SPCONV_F32 ? launch_dw_tile<float> : launch_dw_tile<uint16_t>)(
+        rb, plan, op == SPCONV_OP_DC, x, dy, C_in, C_out, part, db_fused ? centre : -1,
+        db_fused ? partb_fused : nullptr, st);
   // bias-gradient partials: from k_dw_mfma (fused) or one pass over dy
   const float* partb = nullptr;
   int nrc = 0;
