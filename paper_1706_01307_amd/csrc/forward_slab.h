@@ -167,24 +167,22 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
     }
   };
 
-  typedef int32_t GRegs[RB];
+  typedef int32_t GRegs;
+  const int64_t map_row = row0 + map_lane<RB>(lane);
+  const uint32_t map_off = map_row < n_rows ? static_cast<uint32_t>(map_row) * 4u : kBufOOB;
   auto g_load = [&](At a, GRegs& g) {
     const int ic = a.i < K ? a.i : 0;
     const __amdgpu_buffer_rsrc_t gr = buf_rsrc(gmap + static_cast<int64_t>(ic) * gstride,
                                                gmap_bytes);
-#pragma unroll
-    for (int b = 0; b < RB; ++b) {
-      const int64_t row = row0 + b * 16 + lr;
-      const uint32_t off = (a.i < K && row < n_rows) ? static_cast<uint32_t>(row) * 4u : kBufOOB;
-      g[b] = static_cast<int32_t>(__builtin_amdgcn_raw_buffer_load_b32(gr, off, 0, 0)) - 1;
-    }
+    g = static_cast<int32_t>(__builtin_amdgcn_raw_buffer_load_b32(
+            gr, a.i < K ? map_off : kBufOOB, 0, 0)) - 1;
   };
   typedef u32x4 ARegs[RB][NCH];
-  auto a_load = [&](At at, const GRegs& g, ARegs& a) -> uint32_t {
-    uint32_t pres = 0;
+  auto a_load = [&](At at, const GRegs& gv, ARegs& a) -> uint32_t {
+    int32_t g[RB];
+    spread_map<RB>(gv, g);
 #pragma unroll
     for (int b = 0; b < RB; ++b) {
-      if (__ballot(g[b] >= 0) != 0) pres |= 1u << b;
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch) {
         const int c = at.c + ch * KC + lg * EPP;
@@ -193,7 +191,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
         a[b][ch] = buf_piece<TIn, AX>(xr, off, cnt);
       }
     }
-    return pres;
+    return map_blocks<RB>(gv);
   };
 
   f32x4 acc[RB][NCB];
