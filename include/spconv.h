@@ -80,8 +80,9 @@ enum {
   /* Return as soon as the work is enqueued.  Device-detected errors
    * (EDUP, ERANGE, ECAP) are then reported by spconv_rulebook_status. */
   SPCONV_BUILD_ASYNC = 1,
-  /* SC only: also build the transposed rule book (every pair reversed),
-   * which spconv_dc_forward and the SC input gradient walk. */
+  /* SC only: make the reversed direction available (spconv_dc_forward and
+   * the SC input gradient): builds the transposed rule book (every pair
+   * reversed), or nothing where f = s and the strides divide the extents. */
   SPCONV_BUILD_TRANSPOSE = 2
 };
 
@@ -233,8 +234,8 @@ int spconv_pool_forward(spconv_rulebook rb, int mode, int dt, const void* x, voi
  *   w       device [K][C_in][C_out]; bias fp32 [C_out] or NULL
  *   y       device [n_in][C_out] (rows in the SC input order), overwritten
  * Accumulation, rounding and determinism as spconv_vsc_forward.  For
- * f = s the first such call on a book reads its pair offsets once (a wait);
- * later calls are asynchronous.
+ * f = s on extents the stride does not divide, the first such call on a book
+ * reads its pair offsets once (a wait); other calls are asynchronous.
  * Errors: EINVAL (kind, no transposed book, dtype, C < 1, NULL). */
 int spconv_dc_forward(spconv_rulebook rb, int in_dt, const void* x, const void* w,
                       const float* bias, int out_dt, void* y, int C_in, int C_out,
@@ -249,8 +250,8 @@ int spconv_dc_forward(spconv_rulebook rb, int in_dt, const void* x, const void* 
  *   op SPCONV_OP_DC  (SC book):   dy [n_in][C_out]  -> dx [n_out][C_in]
  * dt is the dtype of dy and w, out_dt that of dx.  fp32 accumulation in a
  * fixed order, rounded once; deterministic; allocates nothing; asynchronous
- * (for op SC with f = s the first such call on a book reads its pair offsets
- * once, as spconv_dc_forward).
+ * (for op SC with f = s the first such call on a book may read its pair
+ * offsets once, as spconv_dc_forward).
  * Errors: EINVAL (op / book mismatch, missing transposed book, dtype, NULL). */
 int spconv_backward_data(spconv_rulebook rb, int op, int dt, const void* dy, const void* w,
                          int out_dt, void* dx, int C_in, int C_out, void* stream);

@@ -272,7 +272,11 @@ static int build_impl(int kind, int D, const int32_t* coords, int64_t N,
   bytes += align_up((Kz + 1) * 8, 256);
   bytes += align_up(Kz * n_cap * 8, 256);
   bytes += align_up(n_cap * 4, 256);
-  const size_t tbytes = transpose ? transpose_bytes(N, K) : 0;
+  rb->t_direct = transpose;
+  for (int j = 1; j < D; ++j)
+    rb->t_direct = rb->t_direct && f[j] == s[j] && spatial_size[j] % s[j] == 0;
+  const bool t_maps = transpose && !rb->t_direct;
+  const size_t tbytes = t_maps ? transpose_bytes(N, K) : 0;
   bytes += tbytes;
   if (dev_alloc(rb, bytes, rb->stream, &rb->mem) != SPCONV_OK) {
     delete rb;
@@ -298,10 +302,10 @@ static int build_impl(int kind, int D, const int32_t* coords, int64_t N,
   rb->pair_off = reinterpret_cast<int64_t*>(take((Kz + 1) * 8));
   rb->pairs = reinterpret_cast<int32_t*>(take(Kz * n_cap * 8));
   rb->perm = reinterpret_cast<int32_t*>(take(n_cap * 4));
-  char* tmem = transpose ? take(tbytes) : nullptr;
+  char* tmem = t_maps ? take(tbytes) : nullptr;
 
   int st = kind == SPCONV_VSC ? build_vsc(rb, coords) : build_sc(rb, coords);
-  if (st == SPCONV_OK && transpose) st = build_transpose(rb, coords, tmem);
+  if (st == SPCONV_OK && t_maps) st = build_transpose(rb, coords, tmem);
   if (st != SPCONV_OK) {
     release(rb);
     return st;
@@ -494,13 +498,15 @@ int spconv_pool_forward(spconv_rulebook rb, int mode, int dt, const void* x, voi
 int spconv_dc_forward(spconv_rulebook rb, int in_dt, const void* x, const void* w,
                       const float* bias, int out_dt, void* y, int C_in, int C_out,
                       void* stream) {
-  if (!rb || rb->kind != SPCONV_SC || !rb->t_gmap) return SPCONV_EINVAL;
+  if (!rb || rb->kind != SPCONV_SC || !(rb->t_gmap || rb->t_direct)) return SPCONV_EINVAL;
   if (!dtype_ok(in_dt) || !dtype_ok(out_dt) || C_in < 1 || C_out < 1) return SPCONV_EINVAL;
   if (rb->n_in > 0 && (!y || !w || (out_rows(rb) > 0 && !x))) return SPCONV_EINVAL;
   if (misaligned(x) || misaligned(w) || misaligned(y) ||
       (reinterpret_cast<uintptr_t>(bias) & 3))
     return SPCONV_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (rb->t_direct)
+    return used_on(rb, stream, forward_up(rb, 0, in_dt, x, w, bias, out_dt, y, C_in, C_out, st));
   if (rb->t_single && rb->n_in > 0) {
     const int r = transpose_single(rb, 0, in_dt, x, w, bias, out_dt, y, C_in, C_out, st);
     if (r != kNotSingle) return used_on(rb, stream, r);
@@ -519,8 +525,8 @@ static int data_grad_view(spconv_rulebook rb, int op, FwdView* v, int* wmode) {
       *wmode = 1;
       return SPCONV_OK;
     case SPCONV_OP_SC:
-      if (rb->kind != SPCONV_SC || !rb->t_gmap) return SPCONV_EINVAL;
-      *v = transpose_view(rb);       // SC pairs reversed
+      if (rb->kind != SPCONV_SC || !(rb->t_gmap || rb->t_direct)) return SPCONV_EINVAL;
+      if (!rb->t_direct) *v = transpose_view(rb);       // SC pairs reversed
       *wmode = 2;
       return SPCONV_OK;
     case SPCONV_OP_DC:
@@ -547,6 +553,9 @@ int spconv_backward_data(spconv_rulebook rb, int op, int dt, const void* dy, con
   if (misaligned(dy) || misaligned(w) || misaligned(dx)) return SPCONV_EINVAL;
   // the kernels' input channels are the layer's output channels
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (op == SPCONV_OP_SC && rb->t_direct)
+    return used_on(rb, stream, forward_up(rb, wmode, dt, dy, w, nullptr, out_dt, dx, C_out, C_in,
+                                          st));
   if (op == SPCONV_OP_SC && rb->t_single && rb->n_in > 0) {
     const int r = transpose_single(rb, wmode, dt, dy, w, nullptr, out_dt, dx, C_out, C_in, st);
     if (r != kNotSingle) return used_on(rb, stream, r);

@@ -37,6 +37,18 @@ int forward_view(const FwdView& v, int wmode, int in_dt, const void* x, const vo
   return hipGetLastError() == hipSuccess ? SPCONV_OK : SPCONV_EHIP;
 }
 
+int forward_up(spconv_rulebook rb, int wmode, int in_dt, const void* x, const void* w,
+               const float* bias, int out_dt, void* y, int C_in, int C_out, hipStream_t stream) {
+  FwdCall c{view_of(rb), x, 0u, w, bias, y, C_out, stream, Epilogue{}};
+  if (c.v.n_cap == 0) return SPCONV_OK;
+  c.v.n_src = x ? rb->n_cap : 0;          // the source rows are the book's output rows
+  if (in_dt == SPCONV_F32)
+    (out_dt == SPCONV_F32 ? forward_up_ff : forward_up_fb)(c, wmode, C_in);
+  else
+    (out_dt == SPCONV_F32 ? forward_up_bf : forward_up_bb)(c, wmode, C_in);
+  return hipGetLastError() == hipSuccess ? SPCONV_OK : SPCONV_EHIP;
+}
+
 int forward(spconv_rulebook rb, int in_dt, const void* x, const void* w, const float* bias,
             int out_dt, void* y, int C_in, int C_out, hipStream_t stream) {
   return forward_view(view_of(rb), 0, in_dt, x, w, bias, out_dt, y, C_in, C_out, stream);

@@ -942,7 +942,7 @@ bool launch_generic(const Call& c, int C_in) {
     return true;
   }
   const bool wfits = (c.v.seg ? 1024 * wb : wb) < kBufOOB;
-  if (!force_vector_path() && fits && wfits && (c.v.seg || !few || c.v.n_cap >= kLowMinRows)) {
+  if ((c.v.seg || !few || c.v.n_cap >= kLowMinRows) && fits && wfits && !force_vector_path()) {
     Call cc = c;
     cc.x_bytes = static_cast<uint32_t>(xb);
     slab_entry<TIn, TOut>()(cc, WT, C_in, static_cast<uint32_t>(c.v.seg ? 0x7fffffffu : wb));

@@ -57,6 +57,82 @@ __device__ __forceinline__ u32x4 buf_piece(__amdgpu_buffer_rsrc_t r, uint32_t of
   }
 }
 
+// Staging of one slab of W^i (SLAB k-rows, COLS columns from col0) into its
+// LDS image, transposed as WImage describes.  WT 0: a task is KPT k-rows x one
+// 16-byte piece of columns (bf16 packs pairs of k-rows); WT 1 / 2 (w holds
+// W^T): one 16-byte piece of k of one column.
+// LDS row of column n of the tile: with x as the first operand (result rows =
+// positions) lane r of a 16-lane group ends up with columns r NCB ..;
+// ROWS: with W^T as the first operand (result rows = columns) the lanes of
+// group g end up with columns 4 NCB g .. of one position each.
+template <typename TIn, int NCH, int NCB, int WT, bool AX, bool AW, bool ROWS = false>
+struct WStage {
+  static constexpr int ESZ = static_cast<int>(sizeof(TIn));
+  static constexpr int EPP = 16 / ESZ;
+  static constexpr int SLAB = NCH * MT<TIn>::KC;
+  static constexpr int COLS = NCB * 16;
+  static constexpr int ROWB = SLAB * ESZ;
+  static constexpr int KPT = ESZ == 2 ? 2 : 1;
+  static constexpr int NGRP = COLS / EPP;
+  static constexpr int CPR = ROWB / 16;
+  static constexpr int NTASK = WT == 0 ? (SLAB / KPT) * NGRP : COLS * CPR;
+  static constexpr int TPT = (NTASK + 255) / 256;
+  static constexpr int NWR = WT == 0 ? TPT * KPT : TPT;
+  typedef u32x4 Regs[NWR];
+
+  // slab of channels c0 .. of w[iv]; zeros where `in` is false
+  __device__ static void load(__amdgpu_buffer_rsrc_t wr, bool in, int iv, int c0, int C_in,
+                              int C_out, int col0, Regs& r) {
+#pragma unroll
+    for (int q = 0; q < TPT; ++q) {
+      const int t = threadIdx.x + q * 256;
+      const bool live = in && (NTASK % 256 == 0 || t < NTASK);
+      if constexpr (WT == 0) {
+        const int k = c0 + t / NGRP * KPT, n = col0 + t % NGRP * EPP;
+#pragma unroll
+        for (int e = 0; e < KPT; ++e) {
+          const int cnt = live && k + e < C_in ? C_out - n : 0;
+          const uint32_t off = ((static_cast<uint32_t>(iv) * C_in + k + e) * C_out + n) * ESZ;
+          r[q * KPT + e] = buf_piece<TIn, AW>(wr, off, cnt);
+        }
+      } else {
+        const int n = col0 + t / CPR, k = c0 + t % CPR * EPP;
+        const int cnt = live && n < C_out ? C_in - k : 0;
+        const uint32_t off = ((static_cast<uint32_t>(iv) * C_out + n) * C_in + k) * ESZ;
+        r[q] = buf_piece<TIn, AX>(wr, off, cnt);
+      }
+    }
+  }
+  __device__ static int row_of(int n) {
+    if constexpr (ROWS) return n % (4 * NCB) / 4 * 16 + n / (4 * NCB) * 4 + n % 4;
+    return (n % NCB) * 16 + n / NCB;
+  }
+  __device__ static void store(unsigned char* dst, const Regs& r) {
+#pragma unroll
+    for (int q = 0; q < TPT; ++q) {
+      const int t = threadIdx.x + q * 256;
+      if (NTASK % 256 != 0 && t >= NTASK) continue;
+      if constexpr (WT == 0) {
+        const int kt = t / NGRP, nt = t % NGRP;
+#pragma unroll
+        for (int j = 0; j < EPP; ++j) {
+          uint32_t v;
+          if constexpr (ESZ == 2) {
+            const uint32_t a = r[q * KPT][j / 2], b = r[q * KPT + 1][j / 2];
+            v = (j & 1) ? ((a >> 16) | (b & 0xffff0000u)) : ((a & 0xffffu) | (b << 16));
+          } else {
+            v = r[q][j];
+          }
+          *reinterpret_cast<uint32_t*>(&dst[WImage<ROWB>::at(row_of(nt * EPP + j), kt * 4)]) = v;
+        }
+      } else {
+        const int n = t / CPR, kc = t % CPR;
+        *reinterpret_cast<u32x4*>(&dst[WImage<ROWB>::at(row_of(n), kc * 16)]) = r[q];
+      }
+    }
+  }
+};
+
 template <typename TIn, typename TOut, int NCH, int NCB, int RB, int WT, bool AX, bool AW>
 __global__ __launch_bounds__(256, 2) void k_fwd_slab(
     const int32_t* __restrict__ gmap, const int32_t* __restrict__ perm, int64_t gstride,
@@ -71,12 +147,6 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
   constexpr int EPP = 16 / ESZ;                   // elements per 16-byte piece
   constexpr int ROWB = SLAB * ESZ;                // bytes of one row's slab
   constexpr int LDWB = WImage<ROWB>::kRowBytes;
-  constexpr int KPT = ESZ == 2 ? 2 : 1;           // k-rows per staging task (WT 0)
-  constexpr int NGRP = COLS / EPP;
-  constexpr int CPR = ROWB / 16;
-  constexpr int NTASK = WT == 0 ? (SLAB / KPT) * NGRP : COLS * CPR;
-  constexpr int TPT = (NTASK + 255) / 256;
-  constexpr int NWR = WT == 0 ? TPT * KPT : TPT;
   constexpr int WAVE_ROWS = RB * 16;
   constexpr int TILE_ROWS = 4 * WAVE_ROWS;
   static_assert(kSegRows % TILE_ROWS == 0, "tiles inside one segment chunk");
@@ -116,56 +186,13 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
     }
   };
 
-  typedef u32x4 WRegs[NWR];
+  using WS = WStage<TIn, NCH, NCB, WT, AX, AW>;
+  typedef typename WS::Regs WRegs;
   auto w_load = [&](At a, WRegs& r) {
     const int iv = wseg >= 0 ? wseg : (WT == 1 ? K - 1 - a.i : a.i);
-    const bool in = a.i < K;
-#pragma unroll
-    for (int q = 0; q < TPT; ++q) {
-      const int t = threadIdx.x + q * 256;
-      const bool live = in && (NTASK % 256 == 0 || t < NTASK);
-      if constexpr (WT == 0) {
-        const int k = a.c + t / NGRP * KPT, n = col0 + t % NGRP * EPP;
-#pragma unroll
-        for (int e = 0; e < KPT; ++e) {
-          const int cnt = live && k + e < C_in ? C_out - n : 0;
-          const uint32_t off = ((static_cast<uint32_t>(iv) * C_in + k + e) * C_out + n) * ESZ;
-          r[q * KPT + e] = buf_piece<TIn, AW>(wr_, off, cnt);
-        }
-      } else {
-        const int n = col0 + t / CPR, k = a.c + t % CPR * EPP;
-        const int cnt = live && n < C_out ? C_in - k : 0;
-        const uint32_t off = ((static_cast<uint32_t>(iv) * C_out + n) * C_in + k) * ESZ;
-        r[q] = buf_piece<TIn, AX>(wr_, off, cnt);
-      }
-    }
+    WS::load(wr_, a.i < K, iv, a.c, C_in, C_out, col0, r);
   };
-  auto w_row = [](int n) { return (n % NCB) * 16 + n / NCB; };
-  auto w_store = [&](int buf, const WRegs& r) {
-    unsigned char* dst = s_w[buf];
-#pragma unroll
-    for (int q = 0; q < TPT; ++q) {
-      const int t = threadIdx.x + q * 256;
-      if (NTASK % 256 != 0 && t >= NTASK) continue;
-      if constexpr (WT == 0) {
-        const int kt = t / NGRP, nt = t % NGRP;
-#pragma unroll
-        for (int j = 0; j < EPP; ++j) {
-          uint32_t v;
-          if constexpr (ESZ == 2) {
-            const uint32_t a = r[q * KPT][j / 2], b = r[q * KPT + 1][j / 2];
-            v = (j & 1) ? ((a >> 16) | (b & 0xffff0000u)) : ((a & 0xffffu) | (b << 16));
-          } else {
-            v = r[q][j];
-          }
-          *reinterpret_cast<uint32_t*>(&dst[WImage<ROWB>::at(w_row(nt * EPP + j), kt * 4)]) = v;
-        }
-      } else {
-        const int n = t / CPR, kc = t % CPR;
-        *reinterpret_cast<u32x4*>(&dst[WImage<ROWB>::at(w_row(n), kc * 16)]) = r[q];
-      }
-    }
-  };
+  auto w_store = [&](int buf, const WRegs& r) { WS::store(s_w[buf], r); };
 
   typedef int32_t GRegs;
   const int64_t map_row = row0 + map_lane<RB>(lane);
@@ -316,6 +343,223 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
   }
 }
 
+// 16 bytes of adjacent output elements, rounded once.
+__device__ __forceinline__ void store16(float* p, const float* v) { OutStore<float, 4>::store(p, v); }
+__device__ __forceinline__ void store16(uint16_t* p, const float* v) {
+  uint4 u;
+  u.x = f32_to_bf16(v[0]) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16);
+  u.y = f32_to_bf16(v[2]) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
+  u.z = f32_to_bf16(v[4]) | (static_cast<uint32_t>(f32_to_bf16(v[5])) << 16);
+  u.w = f32_to_bf16(v[6]) | (static_cast<uint32_t>(f32_to_bf16(v[7])) << 16);
+  *reinterpret_cast<uint4*>(p) = u;
+}
+
+// ---------------------------------------------------------------------------
+// The reversed direction of SC with f = s
+// ---------------------------------------------------------------------------
+// k_fwd_up: DC and the SC input gradient on a book whose filter equals its
+// stride.  Every SC input row then hangs on exactly one (offset, SC output
+// row), so the reversed layer is a dense product of the SC output rows with
+// all K matrices whose results are dealt to the SC input rows: a tile of
+// output positions reads its rows once (registers, C_in <= 4 k-chunks: KEEP;
+// wider rows come again per slab), walks the offsets, and stores row p of
+// x W^i to input row G[i][p] - 1 of the forward's own gather map.  No
+// transposed map is built or read.  Every destination row is written exactly
+// once provided every input row has its pair (the book checks the extents).
+//
+// Bound: HBM, the destination rows and their map.  Measured, 505,281 surface
+// rows 64 -> 1,703,204 rows 32 bf16 2^3: DC 72 us, the input gradient 66 us
+// (77-81 us with the rows gathered once per pair from per-offset lists, whose
+// building also took 130 us of every book; 101 us here with x as the first
+// operand, every result row then stored in 4-byte pieces).
+template <typename TIn, typename TOut, int NCH, int NCB, int RB, int WT, bool KEEP, bool AX,
+          bool AW>
+__global__ __launch_bounds__(256, 2) void k_fwd_up(
+    const int32_t* __restrict__ gmap, const int32_t* __restrict__ perm, int64_t gstride,
+    const DeviceHeader* __restrict__ hdr, int K, const TIn* __restrict__ x, uint32_t x_bytes,
+    const TIn* __restrict__ w, uint32_t w_bytes, const float* __restrict__ bias,
+    TOut* __restrict__ y, int C_in, int C_out, int64_t ntiles) {
+  using WS = WStage<TIn, NCH, NCB, WT, AX, AW, true>;
+  constexpr int KC = MT<TIn>::KC;
+  constexpr int SLAB = WS::SLAB;
+  constexpr int EPP = WS::EPP, ESZ = WS::ESZ, ROWB = WS::ROWB;
+  constexpr int WAVE_ROWS = RB * 16;
+  constexpr int TILE_ROWS = 4 * WAVE_ROWS;
+  __shared__ __attribute__((aligned(16))) unsigned char s_w[2][WS::COLS * WImage<ROWB>::kRowBytes];
+
+  // XCD-contiguous tile ranges over the device-side row count, as k_fwd_mfma
+  const int64_t n_rows = hdr->n_out;
+  const int64_t nt_real = (n_rows + TILE_ROWS - 1) / TILE_ROWS;
+  const int64_t nt = nt_real < ntiles ? nt_real : ntiles;
+  const int64_t per = (nt + 7) / 8;
+  const int64_t q8 = blockIdx.x / 8;
+  if (q8 >= per) return;
+  const int64_t tile = static_cast<int64_t>(blockIdx.x % 8) * per + q8;
+  if (tile >= nt) return;
+
+  const int col0 = blockIdx.y * WS::COLS;
+  const int lane = threadIdx.x % kWave;
+  const int lr = lane % 16, lg = lane / 16;
+  const int64_t row0 = tile * TILE_ROWS + threadIdx.x / kWave * WAVE_ROWS;
+  const uint32_t row_bytes = static_cast<uint32_t>(C_in) * ESZ;
+  const __amdgpu_buffer_rsrc_t xr = buf_rsrc(x, x_bytes);
+  const __amdgpu_buffer_rsrc_t wr = buf_rsrc(w, w_bytes);
+  const uint32_t gmap_bytes = static_cast<uint32_t>(gstride * 4);
+
+  int32_t src[RB];                                 // x row of position 16 b + lr, -1 past the end
+#pragma unroll
+  for (int b = 0; b < RB; ++b) {
+    const int64_t p = row0 + b * 16 + lr;
+    src[b] = p < n_rows ? perm[p] : -1;
+  }
+  typedef u32x4 ARegs[RB][NCH];
+  auto a_load = [&](int c0, ARegs& a) {
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch) {
+        const int c = c0 + ch * KC + lg * EPP;
+        const uint32_t off =
+            static_cast<uint32_t>(src[b]) * row_bytes + static_cast<uint32_t>(c) * ESZ;
+        a[b][ch] = buf_piece<TIn, AX>(xr, off, src[b] >= 0 ? C_in - c : 0);
+      }
+  };
+  // destinations (row, -1 = none) of the wave's positions at offset i, as
+  // k_fwd_mfma's map entries
+  const int64_t map_row = row0 + map_lane<RB>(lane);
+  const uint32_t map_off = map_row < n_rows ? static_cast<uint32_t>(map_row) * 4u : kBufOOB;
+  auto d_load = [&](int i) -> int32_t {
+    const __amdgpu_buffer_rsrc_t gr =
+        buf_rsrc(gmap + static_cast<int64_t>(i < K ? i : 0) * gstride, gmap_bytes);
+    return static_cast<int32_t>(
+               __builtin_amdgcn_raw_buffer_load_b32(gr, i < K ? map_off : kBufOOB, 0, 0)) - 1;
+  };
+
+  // W^T is the first operand of the products, so a lane holds 4 NCB adjacent
+  // columns (from n0) of position 16 b + lr and stores them in 16-byte pieces
+  constexpr int LC = 4 * NCB;
+  constexpr int PC = 16 / static_cast<int>(sizeof(TOut));
+  const bool whole = C_out % PC == 0;
+  const int n0 = col0 + lg * LC;
+  float bv[LC];
+#pragma unroll
+  for (int e = 0; e < LC; ++e) bv[e] = bias && n0 + e < C_out ? bias[n0 + e] : 0.0f;
+  f32x4 acc[RB][NCB];
+  auto clear = [&]() {
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) acc[b][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  auto mma = [&](int c0, int buf, const ARegs& a, uint32_t pres) {
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      if (ch > 0 && c0 + ch * KC >= C_in) break;
+      u32x4 bw[NCB];
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb)
+        bw[cb] = *reinterpret_cast<const u32x4*>(
+            &s_w[buf][WImage<ROWB>::at(cb * 16 + lr, ch * 64 + lg * 16)]);
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        if (!(pres & (1u << b))) continue;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) acc[b][cb] = MT<TIn>::mma(bw[cb], a[b][ch], acc[b][cb]);
+      }
+    }
+  };
+  auto put = [&](int32_t dv, uint32_t pres) {
+    int32_t d[RB];
+    spread_map<RB>(dv, d);
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      if (!(pres & (1u << b)) || d[b] < 0) continue;
+      TOut* out = y + static_cast<int64_t>(d[b]) * C_out + n0;
+      float z[LC];
+#pragma unroll
+      for (int e = 0; e < LC; ++e) z[e] = acc[b][e / 4][e % 4] + bv[e];
+      if (whole) {
+#pragma unroll
+        for (int q = 0; q < LC / PC; ++q)
+          if (n0 + q * PC < C_out) store16(out + q * PC, z + q * PC);
+      } else {
+#pragma unroll
+        for (int e = 0; e < LC; ++e)
+          if (n0 + e < C_out) ElemIO<TOut>::store(out, e, z[e]);
+      }
+    }
+  };
+
+  // step e = (offset i, slab from channel c); W of step e + 1 (and, without
+  // KEEP, its rows) and the destinations of offset i + 1 are on their way
+  // while step e multiplies
+  typename WS::Regs wn;
+  ARegs a0, a1;
+  a_load(0, a0);
+  int32_t d0 = d_load(0), d1 = -1;
+  WS::load(wr, true, 0, 0, C_in, C_out, col0, wn);
+  WS::store(s_w[0], wn);
+  __syncthreads();
+  clear();
+  int i = 0, c = 0, buf = 0;
+  uint32_t pres = map_blocks<RB>(d0);
+  for (;;) {
+    int ni = i, nc = c + SLAB;
+    if (KEEP || nc >= C_in) {
+      nc = 0;
+      ++ni;
+    }
+    d1 = d_load(ni);
+    WS::load(wr, ni < K, ni, nc, C_in, C_out, col0, wn);
+    if constexpr (!KEEP) a_load(nc, a1);
+    mma(c, buf, a0, pres);
+    WS::store(s_w[buf ^ 1], wn);
+    if (ni != i) {
+      put(d0, pres);
+      if (ni >= K) break;
+      clear();
+      d0 = d1;
+      pres = map_blocks<RB>(d0);
+    }
+    if constexpr (!KEEP) {
+#pragma unroll
+      for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) a0[b][ch] = a1[b][ch];
+    }
+    __syncthreads();
+    i = ni;
+    c = nc;
+    buf ^= 1;
+  }
+}
+
+// The same on the vector ALU, one lane per (position, offset, column): for
+// operands past the buffer range.
+template <typename TIn, typename TOut, int WT>
+__global__ __launch_bounds__(256) void k_fwd_up_vec(
+    const int32_t* __restrict__ gmap, const int32_t* __restrict__ perm, int64_t gstride,
+    const DeviceHeader* __restrict__ hdr, int K, const TIn* __restrict__ x,
+    const TIn* __restrict__ w, const float* __restrict__ bias, TOut* __restrict__ y, int C_in,
+    int C_out) {
+  const int64_t n_rows = hdr->n_out, total = n_rows * K * C_out;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  for (int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; t < total;
+       t += stride) {
+    const int n = static_cast<int>(t % C_out);
+    const int64_t r = t / C_out, p = r % n_rows;
+    const int i = static_cast<int>(r / n_rows);
+    const int64_t dst = static_cast<int64_t>(gmap[i * gstride + p]) - 1;
+    if (dst < 0) continue;
+    const int64_t xb = static_cast<int64_t>(perm[p]) * C_in;
+    float acc = 0.0f;
+    for (int c = 0; c < C_in; ++c)
+      acc = fmaf(ElemIO<TIn>::load(x, xb + c),
+                 ElemIO<TIn>::load(w, w_index<WT>(i, K, c, n, C_in, C_out)), acc);
+    ElemIO<TOut>::store(y, dst * C_out + n, bias ? acc + bias[n] : acc);
+  }
+}
+
 template <typename TIn, typename TOut, int WT, int NCH, int NCB, int RB, bool AX, bool AW>
 void launch_slab_tile(const Call& c, int C_in, uint32_t w_bytes) {
   constexpr int kTileRows = 4 * RB * 16;
@@ -384,6 +628,72 @@ void run_slab(const Call& c, int wmode, int C_in, uint32_t w_bytes) {
     case 1: launch_slab<TIn, TOut, 1>(c, C_in, w_bytes); break;
     default: launch_slab<TIn, TOut, 2>(c, C_in, w_bytes); break;
   }
+}
+
+template <typename TIn, typename TOut, int WT, int NCH, int NCB, int RB, bool KEEP, bool AX,
+          bool AW>
+void launch_up_tile(const Call& c, int C_in, uint32_t w_bytes) {
+  constexpr int kTileRows = 4 * RB * 16;
+  const int64_t ntiles = (c.v.n_cap + kTileRows - 1) / kTileRows;
+  const dim3 grid(static_cast<unsigned>(8 * ((ntiles + 7) / 8)),
+                  static_cast<unsigned>((c.C_out + NCB * 16 - 1) / (NCB * 16)));
+  k_fwd_up<TIn, TOut, NCH, NCB, RB, WT, KEEP, AX, AW><<<grid, 256, 0, c.stream>>>(
+      c.v.gmap, c.v.perm, c.v.gstride, c.v.hdr, static_cast<int>(c.v.K),
+      static_cast<const TIn*>(c.x), c.x_bytes, static_cast<const TIn*>(c.w), w_bytes, c.bias,
+      static_cast<TOut*>(c.y), C_in, c.C_out, ntiles);
+}
+
+template <typename TIn, typename TOut, int WT, int NCB>
+void launch_up_cols(const Call& c, int C_in, uint32_t w_bytes) {
+  const int chunks = (C_in + MT<TIn>::KC - 1) / MT<TIn>::KC;
+  // 64-row tiles for small layers, as the forward
+  const bool small = c.v.n_cap / 256 < kSmallLayerTiles;
+  if (chunks == 1)
+    (small ? launch_up_tile<TIn, TOut, WT, 1, NCB, 1, true, true, true>
+           : launch_up_tile<TIn, TOut, WT, 1, NCB, 4, true, true, true>)(c, C_in, w_bytes);
+  else if (chunks == 2)
+    (small ? launch_up_tile<TIn, TOut, WT, 2, NCB, 1, true, true, true>
+           : launch_up_tile<TIn, TOut, WT, 2, NCB, 4, true, true, true>)(c, C_in, w_bytes);
+  else if (chunks <= 4)
+    (small ? launch_up_tile<TIn, TOut, WT, 4, NCB, 1, true, true, true>
+           : launch_up_tile<TIn, TOut, WT, 4, NCB, 2, true, true, true>)(c, C_in, w_bytes);
+  else
+    (small ? launch_up_tile<TIn, TOut, WT, 2, NCB, 1, false, true, true>
+           : launch_up_tile<TIn, TOut, WT, 2, NCB, 2, false, true, true>)(c, C_in, w_bytes);
+}
+
+template <typename TIn, typename TOut, int WT>
+void launch_up(const Call& c, int C_in) {
+  constexpr int EPP = 16 / static_cast<int>(sizeof(TIn));
+  const uint64_t xb = static_cast<uint64_t>(c.v.n_src) * C_in * sizeof(TIn);
+  const uint64_t wb = static_cast<uint64_t>(c.v.K) * C_in * c.C_out * sizeof(TIn);
+  if (force_vector_path() || xb >= kBufOOB || wb >= kBufOOB ||
+      static_cast<uint64_t>(c.v.gstride) * 4 >= kBufOOB) {
+    int64_t blocks = (c.v.n_cap * c.v.K * c.C_out + 255) / 256;
+    if (blocks > 65536) blocks = 65536;
+    k_fwd_up_vec<TIn, TOut, WT><<<static_cast<unsigned>(blocks), 256, 0, c.stream>>>(
+        c.v.gmap, c.v.perm, c.v.gstride, c.v.hdr, static_cast<int>(c.v.K),
+        static_cast<const TIn*>(c.x), static_cast<const TIn*>(c.w), c.bias,
+        static_cast<TOut*>(c.y), C_in, c.C_out);
+    return;
+  }
+  Call cc = c;
+  cc.x_bytes = static_cast<uint32_t>(xb);
+  const uint32_t w_bytes = static_cast<uint32_t>(wb);
+  const bool ax = C_in % EPP == 0, aw = WT != 0 || c.C_out % EPP == 0;
+  if (ax && aw)
+    (c.C_out <= 32 ? launch_up_cols<TIn, TOut, WT, 2>
+                   : launch_up_cols<TIn, TOut, WT, 4>)(cc, C_in, w_bytes);
+  else if (WT == 0 && ax)
+    launch_up_tile<TIn, TOut, WT, 1, 4, 1, false, true, WT != 0>(cc, C_in, w_bytes);
+  else
+    launch_up_tile<TIn, TOut, WT, 1, 4, 1, false, false, WT != 0>(cc, C_in, w_bytes);
+}
+
+template <typename TIn, typename TOut>
+void run_up(const Call& c, int wmode, int C_in) {
+  if (wmode == 0) launch_up<TIn, TOut, 0>(c, C_in);
+  else launch_up<TIn, TOut, 2>(c, C_in);
 }
 
 }  // namespace

@@ -66,5 +66,11 @@ void forward_slab_ff(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
 void forward_slab_fb(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
 void forward_slab_bf(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
 void forward_slab_bb(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
+// The reversed direction (wmode 0: DC, 2: the SC input gradient) on the
+// forward's view of an SC book with f = s whose input rows all have a pair.
+void forward_up_ff(const FwdCall& c, int wmode, int C_in);
+void forward_up_fb(const FwdCall& c, int wmode, int C_in);
+void forward_up_bf(const FwdCall& c, int wmode, int C_in);
+void forward_up_bb(const FwdCall& c, int wmode, int C_in);
 
 }  // namespace spc

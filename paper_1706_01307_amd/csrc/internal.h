@@ -187,6 +187,10 @@ struct spconv_rulebook_s {
   // transposed rule book (SC built with SPCONV_BUILD_TRANSPOSE), or NULL:
   // the SC input rows ordered by offset class, and for every (offset, position
   // in that order) 1 + the SC output row paired with that input row
+  // t_direct: f = s and the strides divide the extents, so every input row has
+  // exactly one pair and the reversed direction runs on the forward's own map;
+  // none of the arrays below are built then.
+  bool t_direct = false;
   spc::DeviceHeader* t_hdr;    // n_out = n_in
   int32_t* t_perm;             // [n_in]
   int32_t* t_gmap;             // [K][t_gstride]
@@ -255,6 +259,9 @@ FwdView view_of(spconv_rulebook rb);
 int forward_view(const FwdView& v, int wmode, int in_dt, const void* x, const void* w,
                  const float* bias, int out_dt, void* y, int C_in, int C_out,
                  hipStream_t stream, const Epilogue& epi = Epilogue{});
+// The reversed direction of a book with t_direct (wmode 0 or 2).
+int forward_up(spconv_rulebook rb, int wmode, int in_dt, const void* x, const void* w,
+               const float* bias, int out_dt, void* y, int C_in, int C_out, hipStream_t stream);
 int forward(spconv_rulebook rb, int in_dt, const void* x, const void* w,
             const float* bias, int out_dt, void* y, int C_in, int C_out,
             hipStream_t stream);

@@ -8,7 +8,9 @@
 // AP sums in fp32 and divides by prod_j f_j once.
 //
 // Transposed rule book (Section 3: DC(.,.,f,s) inverts SC(.,.,f,s), same
-// connections reversed; the SC input gradient runs the same reversed pairs):
+// connections reversed; the SC input gradient runs the same reversed pairs),
+// for books whose filter overlaps or whose extents the stride does not divide
+// (the others run on the forward's own map, k_fwd_up):
 //   k_class_keys + radix sort  SC input rows ordered by their offset class
 //                              x mod s (stable, so by row inside a class):
 //                              with f = s every row of a class takes the same

@@ -53,8 +53,9 @@
 //   k_bitsum / k_bitscan / k_sc_emit
 //                rank the marked sites by a popcount prefix sum, which
 //                numbers the output rows in lexicographic order (small
-//                bitmaps: k_sc_emit alone); on the grid path the emission
-//                also fills the output grid
+//                bitmaps: k_sc_emit alone; large ones on the grid path: marked
+//                as bytes, k_bytes_bits in place of k_bitsum); on the grid path
+//                the emission also fills the output grid
 //   then the schedule of the output sites (the output grid, or Morton codes
 //   and the sort), and probe / scan / compact on input site s*y + o.
 #include <cstdlib>
@@ -191,11 +192,12 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t v, uint64_t n) {
     p[i] = v;
 }
 
-// Zero n 32-bit words at a 16-byte aligned p: 16-byte stores, then the tail.
-// With hdr set, also initialises the build's header (status 0, n_out).
+// Zero n 32-bit words at a 16-byte aligned p: 16-byte stores, then the tail;
+// and n2 more at p2 likewise.  With hdr set, also initialises the build's
+// header (status 0, n_out).
 __global__ void k_zero_u32(uint32_t* __restrict__ p, uint64_t n, DeviceHeader* hdr,
-                           int64_t n_out) {
-  const uint64_t n4 = n / 4;
+                           int64_t n_out, uint32_t* __restrict__ p2, uint64_t n2) {
+  const uint64_t n4 = n / 4, m4 = n2 / 4;
   const uint64_t stride = static_cast<uint64_t>(gridDim.x) * blockDim.x;
   const uint64_t t = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x;
   if (hdr && t == 0) {
@@ -206,6 +208,9 @@ __global__ void k_zero_u32(uint32_t* __restrict__ p, uint64_t n, DeviceHeader* h
   uint4* q = reinterpret_cast<uint4*>(p);
   for (uint64_t i = t; i < n4; i += stride) q[i] = make_uint4(0u, 0u, 0u, 0u);
   if (t < n - 4 * n4) p[4 * n4 + t] = 0u;
+  uint4* q2 = reinterpret_cast<uint4*>(p2);
+  for (uint64_t i = t; i < m4; i += stride) q2[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (t < n2 - 4 * m4) p2[4 * m4 + t] = 0u;
 }
 
 __global__ void k_init_header(DeviceHeader* h, int64_t n_out) {
@@ -1163,9 +1168,13 @@ __global__ __launch_bounds__(kBlock) void k_compact(
 // first inside a level, keeping only the bits a coordinate can have
 // (B = sum_j bits_j).  Walking cells in increasing order is the Z-order of
 // the sites.  M[j] marks the bits of Z that hold coordinate j.
+// cubic: every spatial coordinate has the same number of bits, so the bits of
+// coordinate j are every (D - 1)-th bit and a coordinate is spread by shifts
+// and masks instead of bit by bit.
 struct GridGeom {
   int D;
   int B;
+  bool cubic;
   uint32_t M[kMaxD];
   int32_t size[kMaxD];
 };
@@ -1181,9 +1190,17 @@ __host__ __device__ inline uint32_t deposit(uint32_t v, uint32_t m) {
   return r;
 }
 
+// Coordinate j's value at its bits of the cell (bits it cannot have dropped).
+// B <= 29 bits in all: at most 14 per coordinate in 2-D, 9 in 3-D, which is
+// what spread_bits takes.
+__device__ __forceinline__ uint32_t place(const GridGeom& g, uint32_t v, int j) {
+  if (g.cubic) return (spread_bits(v, g.D - 1) << (g.D - 1 - j)) & g.M[j];
+  return deposit(v, g.M[j]);
+}
+
 __device__ __forceinline__ uint32_t grid_cell(const GridGeom& g, const int32_t* x) {
   uint32_t cell = static_cast<uint32_t>(x[0]) << g.B;
-  for (int j = 1; j < g.D; ++j) cell |= deposit(static_cast<uint32_t>(x[j]), g.M[j]);
+  for (int j = 1; j < g.D; ++j) cell |= place(g, static_cast<uint32_t>(x[j]), j);
   return cell;
 }
 
@@ -1233,16 +1250,43 @@ __global__ __launch_bounds__(kBlock) void k_sc_mark(
 
 // SC on dense grids, first step in one pass over the input rows: row r is
 // placed at its cell of the input grid by compare-and-swap from 0 (a cell
-// found taken is a duplicate site), and the output sites it feeds are marked
-// as k_sc_mark does.  With `count` set only the first *count rows exist
-// (count_copy, when set, receives that count).
+// found taken is a duplicate site), and the output sites it feeds are marked.
+// With `count` set only the first *count rows exist (count_copy, when set,
+// receives that count).
+// Coordinate x_j = q_j s_j + r_j feeds the output coordinates q_j - k through
+// the offsets r_j + k s_j < f_j, so a row divides once per dimension.
+//   kMarkRounds (f = s): one site per row, marked in the round of its offset
+//   (see k_sc_mark; the offsets' packed remainders, 10 bits each as o_j < f_j
+//   <= kMaxK, are compared from LDS).
+//   kMarkFan: the k of all dimensions are walked directly, 8 sites at a time,
+//   their bitmap words in flight together: 18 us instead of 40 us on 27,072
+//   shuffled rows 3^3 stride 2, whose waves found some row matching in each
+//   of the 27 offsets' rounds and waited out every round's load.
+//   kMarkBytes: as kMarkFan, a byte per output cell instead of a bit: plain
+//   stores, no atomics on words that many rows share; k_bytes_bits makes the
+//   bitmap.  1,703,204 surface rows 2^3 stride 2: 82 us in rounds, 79 us in
+//   one step with the bits set by atomics, 48 us with bytes (the scatter
+//   alone takes 45 us).
+enum { kMarkRounds = 0, kMarkFan = 1, kMarkBytes = 2 };
+template <int MARK>
 __global__ __launch_bounds__(kBlock) void k_sc_scatter_mark(
     const int32_t* __restrict__ coords, int64_t N, const int64_t* __restrict__ count,
     GridGeom g, uint32_t* __restrict__ grid, uint32_t* __restrict__ status,
     int64_t* __restrict__ count_copy, OffsetTable ot, Extents E, uint32_t* __restrict__ bitmap) {
-  __shared__ int16_t s_off[kMaxK][kMaxD];
-  fill_offsets(ot, s_off);
-  __syncthreads();
+  static_assert(kMaxK <= 1024 && kMaxD == 4, "three remainders below 2^10 in a word");
+  __shared__ uint32_t s_rem[MARK == kMarkRounds ? kMaxK : 1];
+  if constexpr (MARK == kMarkRounds) {
+    for (int i = threadIdx.x; i < ot.K; i += kBlock) {
+      int rem = i;
+      uint32_t packed = 0;
+      for (int j = ot.D - 1; j >= 1; --j) {
+        packed |= static_cast<uint32_t>(rem % ot.f[j]) << (10 * (j - 1));
+        rem /= ot.f[j];
+      }
+      s_rem[i] = packed;
+    }
+    __syncthreads();
+  }
   const int64_t r = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x;
   if (count_copy && r == 0) *count_copy = *count;
   if (r >= N || (count && r >= *count)) return;
@@ -1258,18 +1302,63 @@ __global__ __launch_bounds__(kBlock) void k_sc_scatter_mark(
   }
   const uint32_t prev = atomicCAS(&grid[grid_cell(g, x)], 0u, static_cast<uint32_t>(r + 1));
   // (the compare-and-swap's answer is awaited only after the marking)
-  for (int i = 0; i < ot.K; ++i) {
-    uint32_t L = 0;
+  int32_t q[kMaxD], rem[kMaxD];
+  for (int j = 1; j < g.D; ++j) {
+    q[j] = static_cast<int32_t>(static_cast<uint32_t>(x[j]) / static_cast<uint32_t>(ot.s[j]));
+    rem[j] = x[j] - q[j] * ot.s[j];
+  }
+  if constexpr (MARK == kMarkRounds) {
+    uint32_t L = static_cast<uint32_t>(x[0]), rems = 0;
     bool in = true;
-    for (int j = 0; j < ot.D; ++j) {
-      const int32_t t = x[j] - s_off[i][j];
-      const int32_t q = t / ot.s[j];
-      in = in && t >= 0 && q * ot.s[j] == t && q < E.e[j];
-      L = L * static_cast<uint32_t>(E.e[j]) + static_cast<uint32_t>(q);
+    for (int j = 1; j < g.D; ++j) {
+      in = in && q[j] < E.e[j];
+      L = L * static_cast<uint32_t>(E.e[j]) + static_cast<uint32_t>(q[j]);
+      rems |= static_cast<uint32_t>(rem[j]) << (10 * (j - 1));
     }
-    if (in) {
-      const uint32_t bit = 1u << (L & 31);
-      if (!(bitmap[L >> 5] & bit)) atomicOr(&bitmap[L >> 5], bit);
+    const uint32_t bit = 1u << (L & 31);
+    for (int i = 0; i < ot.K; ++i)
+      if (in && s_rem[i] == rems && !(bitmap[L >> 5] & bit)) atomicOr(&bitmap[L >> 5], bit);
+  } else {
+    int32_t m[kMaxD] = {1, 1, 1, 1};               // k per dimension, at most
+    int fan = 1;
+    for (int j = 1; j < g.D; ++j) {
+      m[j] = (ot.f[j] + ot.s[j] - 1) / ot.s[j];
+      fan *= m[j];
+    }
+    constexpr int B = MARK == kMarkBytes ? 1 : 8;
+    for (int t0 = 0; t0 < fan; t0 += B) {
+      uint32_t L[B], word[B];
+      bool in[B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        int t = t0 + u;
+        int32_t y[kMaxD];
+        in[u] = t < fan;
+#pragma unroll
+        for (int j = kMaxD - 1; j >= 1; --j) {
+          if (j >= g.D) continue;
+          const int k = t % m[j];                  // uniform
+          t /= m[j];
+          y[j] = q[j] - k;
+          in[u] = in[u] && rem[j] + k * ot.s[j] < ot.f[j] && y[j] >= 0 && y[j] < E.e[j];
+        }
+        uint32_t l = static_cast<uint32_t>(x[0]);
+#pragma unroll
+        for (int j = 1; j < kMaxD; ++j)
+          if (j < g.D) l = l * static_cast<uint32_t>(E.e[j]) + static_cast<uint32_t>(y[j]);
+        if constexpr (MARK == kMarkBytes) {
+          if (in[u]) reinterpret_cast<uint8_t*>(bitmap)[l] = 1;
+        } else {
+          L[u] = in[u] ? l : 0u;
+          word[u] = bitmap[L[u] >> 5];             // (word 0 where there is no site)
+        }
+      }
+      if constexpr (MARK == kMarkBytes) continue;
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const uint32_t bit = 1u << (L[u] & 31);
+        if (in[u] && !(word[u] & bit)) atomicOr(&bitmap[L[u] >> 5], bit);
+      }
     }
   }
   if (prev != 0u) atomicOr(status, kStDup);
@@ -1281,6 +1370,28 @@ __global__ __launch_bounds__(kBlock) void k_bitsum(const uint32_t* __restrict__ 
   const uint64_t w = blockIdx.x * static_cast<uint64_t>(kBlock) + threadIdx.x;
   uint32_t tot;
   block_excl_scan<uint32_t>(w < nwords ? __popc(bitmap[w]) : 0u, &tot);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+}
+
+// The bitmap of a byte map (one word, 32 bytes, per thread) and its popcounts
+// per 256 words.
+__global__ __launch_bounds__(kBlock) void k_bytes_bits(const uint8_t* __restrict__ bytes,
+                                                       uint64_t nwords,
+                                                       uint32_t* __restrict__ bitmap,
+                                                       uint32_t* __restrict__ bsum) {
+  const uint64_t w = blockIdx.x * static_cast<uint64_t>(kBlock) + threadIdx.x;
+  uint32_t word = 0;
+  if (w < nwords) {
+    const uint4* q = reinterpret_cast<const uint4*>(bytes + 32 * w);
+    const uint4 a = q[0], b = q[1];
+    const uint32_t v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int k = 0; k < 8; ++k)      // bytes are 0 or 1: their lowest bits, gathered
+      word |= (((v[k] & 0x01010101u) * 0x10204080u) >> 28) << (4 * k);
+    bitmap[w] = word;
+  }
+  uint32_t tot;
+  block_excl_scan<uint32_t>(__popc(word), &tot);
   if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
@@ -1321,24 +1432,40 @@ __global__ __launch_bounds__(kBlock) void k_bitscan(uint32_t* __restrict__ bsum,
 }
 
 // Emit the marked output sites in rank order: coordinates and packed keys.
-// Block b works on bitmap block b / kEmitParts (256 words, whose rank base is
-// bbase[b / kEmitParts]) and, of it, the 32 words of part b % kEmitParts;
-// kEmitParts threads share a word, 32 / kEmitParts cells each, so a dense
-// word is not emitted by one thread in 32 serial steps.  bbase = NULL (at
-// most kSelfWords words): every block counts the words before its bitmap
-// block itself, and the last bitmap block sets n_out, in place of k_bitsum
-// and k_bitscan.
-constexpr int kEmitParts = 8;
+// Block b works on bitmap block b / parts (256 words, whose rank base is
+// bbase[b / parts]) and, of it, the words of part b % parts (parts = 8 gives a
+// small bitmap enough blocks); its threads take the part's output sites in
+// turn: the word of site t by a search of the words' prefix, then the bit of
+// its rank inside the word, so a dense word costs no thread more than one
+// site and the sites' stores are consecutive (2^21 cells of 4 x 128^3, 505,281
+// sites: 57 us with eight threads per word, 14 us now).  bbase = NULL (at most
+// kSelfWords words): every block counts the words before its bitmap block
+// itself, and the last bitmap block sets n_out, in place of k_bitsum and
+// k_bitscan.
+constexpr int kEmitParts = 8;      // threads per word (k_grid_emit_self), most parts here
 constexpr int kEmitBits = 32 / kEmitParts;
 constexpr int kSelfWords = 8192;   // most words of a bitmap ranked without a scan launch
+// Position of the n-th set bit of w (n < popcount).
+__device__ __forceinline__ int nth_bit(uint32_t w, uint32_t n) {
+  int pos = 0;
+#pragma unroll
+  for (int h = 16; h >= 1; h >>= 1) {
+    const uint32_t c = __popc((w >> pos) & ((1u << h) - 1u));
+    if (n >= c) {
+      n -= c;
+      pos += h;
+    }
+  }
+  return pos;
+}
 __global__ __launch_bounds__(kBlock) void k_sc_emit(
     const uint32_t* __restrict__ bitmap, uint64_t nwords, const uint32_t* __restrict__ bbase,
-    Codec cout, Extents E, int32_t* __restrict__ out_coords,
+    int parts, Codec cout, Extents E, int32_t* __restrict__ out_coords,
     uint64_t* __restrict__ out_keys, OutGrid og, DeviceHeader* __restrict__ hdr) {
-  __shared__ uint32_t s_pre[kBlock];
+  __shared__ uint32_t s_pre[kBlock + 1];
   __shared__ uint32_t s_word[kBlock];
-  const uint64_t bw = blockIdx.x / kEmitParts;
-  const int part = blockIdx.x % kEmitParts;
+  const uint64_t bw = blockIdx.x / parts;
+  const int part = blockIdx.x % parts;
   uint32_t bbw = 0;                                // rank base of the bitmap block
   if (!bbase) {
     constexpr int PER = kSelfWords / kBlock;
@@ -1362,40 +1489,29 @@ __global__ __launch_bounds__(kBlock) void k_sc_emit(
     uint32_t tot;
     s_word[threadIdx.x] = tw;
     s_pre[threadIdx.x] = block_excl_scan<uint32_t>(__popc(tw), &tot);
-    if (!bbase && blockIdx.x == gridDim.x - kEmitParts && threadIdx.x == 0)
+    if (threadIdx.x == 0) s_pre[kBlock] = tot;
+    if (!bbase && blockIdx.x == gridDim.x - parts && threadIdx.x == 0)
       hdr->n_out = static_cast<int64_t>(bbw) + tot;
   }
   __syncthreads();
-  const int wi = part * (kBlock / kEmitParts) + threadIdx.x / kEmitParts;   // word in block
-  const int sub = threadIdx.x % kEmitParts;
-  const uint64_t w = bw * kBlock + wi;
-  if (w >= nwords) return;
-  const uint32_t full = s_word[wi];
-  const uint32_t below = (1u << (sub * kEmitBits)) - 1u;
-  uint32_t word = (full >> (sub * kEmitBits)) & ((1u << kEmitBits) - 1u);
-  if (!word) return;
-  uint32_t rank = bbw + s_pre[wi] + __popc(full & below);
-  // coordinates of the thread's first cell (one division per dimension); a
-  // set bit b adds b to the last coordinate, carried into the others only
-  // when it passes the extent
-  int32_t y0[kMaxD];
-  {
-    uint32_t L = static_cast<uint32_t>(w * 32 + sub * kEmitBits);
-    for (int j = cout.D - 1; j >= 0; --j) {
-      y0[j] = static_cast<int32_t>(L % static_cast<uint32_t>(E.e[j]));
-      L /= static_cast<uint32_t>(E.e[j]);
+  const int w0 = part * (kBlock / parts), w1 = w0 + kBlock / parts;
+  const uint32_t end = s_pre[w1];
+  for (uint32_t t = s_pre[w0] + threadIdx.x; t < end; t += kBlock) {
+    int lo = w0, hi = w1;                          // s_pre[lo] <= t < s_pre[hi]
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) / 2;
+      if (s_pre[mid] <= t) lo = mid; else hi = mid;
     }
-  }
-  while (word) {
-    const int b = __builtin_ctz(word);
-    word &= word - 1;
+    uint32_t L = static_cast<uint32_t>((bw * kBlock + lo) * 32) +
+                 nth_bit(s_word[lo], t - s_pre[lo]);
     int32_t yv[kMaxD];
-    for (int j = 0; j < cout.D; ++j) yv[j] = y0[j];
-    yv[cout.D - 1] += b;
-    for (int j = cout.D - 1; j > 0 && yv[j] >= E.e[j]; --j) {
-      yv[j - 1] += yv[j] / E.e[j];
-      yv[j] %= E.e[j];
+    for (int j = cout.D - 1; j > 0; --j) {
+      const uint32_t e = static_cast<uint32_t>(E.e[j]), q = L / e;
+      yv[j] = static_cast<int32_t>(L - q * e);
+      L = q;
     }
+    yv[0] = static_cast<int32_t>(L);
+    const uint32_t rank = bbw + t;
     if (cout.D == 4) {
       reinterpret_cast<int4*>(out_coords)[rank] = make_int4(yv[0], yv[1], yv[2], yv[3]);
     } else {
@@ -1407,9 +1523,11 @@ __global__ __launch_bounds__(kBlock) void k_sc_emit(
       og.grid[cell] = rank + 1;
       if (og.bitmap) atomicOr(&og.bitmap[cell >> 5], 1u << (cell & 31));
     }
-    ++rank;
   }
 }
+
+// Parts per bitmap block: one where the blocks fill the device by themselves.
+inline int emit_parts(int64_t nbw) { return nbw >= 512 ? 1 : kEmitParts; }
 
 // Forward schedule: Morton code of every output row (sample index on top,
 // then the spatial coordinates' bits interleaved from the most significant),
@@ -1724,7 +1842,7 @@ __global__ __launch_bounds__(kBlock) void k_probe_grid(
   for (int j = 0; j < D; ++j) {
     c[j] = valid ? rows_sites[static_cast<int64_t>(y) * D + j] : 0;
     if (SC) c[j] *= ot.s[j];
-    zc[j] = j ? (deposit(static_cast<uint32_t>(c[j]), g.M[j]) | ~g.M[j]) : 0u;
+    zc[j] = j ? (place(g, static_cast<uint32_t>(c[j]), j) | ~g.M[j]) : 0u;
   }
   const uint32_t base = static_cast<uint32_t>(c[0]) << g.B;
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -1825,9 +1943,9 @@ __global__ __launch_bounds__(kBlock) void k_probe_grid_g4(
     dm[j] = g.M[j];
     dp[j] = g.M[j] & (0u - g.M[j]);
   }
-  const uint32_t z1 = deposit(static_cast<uint32_t>(c.y), g.M[1]) | ~g.M[1];
-  const uint32_t z2 = deposit(static_cast<uint32_t>(c.z), g.M[2]) | ~g.M[2];
-  const uint32_t z3 = deposit(static_cast<uint32_t>(c.w), g.M[3]) | ~g.M[3];
+  const uint32_t z1 = place(g, static_cast<uint32_t>(c.y), 1) | ~g.M[1];
+  const uint32_t z2 = place(g, static_cast<uint32_t>(c.z), 2) | ~g.M[2];
+  const uint32_t z3 = place(g, static_cast<uint32_t>(c.w), 3) | ~g.M[3];
   const uint32_t base = static_cast<uint32_t>(c.x) << g.B;
   const uint32_t xp[3] = {(z1 + dm[1]) & g.M[1], z1 & g.M[1], (z1 + dp[1]) & g.M[1]};
   const uint32_t yp[2] = {(z2 + dm[2]) & g.M[2], (z2 + dp[2]) & g.M[2]};
@@ -1932,9 +2050,9 @@ __global__ __launch_bounds__(kBlock) void k_probe_grid_sc2(
   int4 c = make_int4(0, 0, 0, 0);
   if (valid) c = reinterpret_cast<const int4*>(rows_sites)[y];
   const uint32_t cell = (static_cast<uint32_t>(c.x) << g.B) |
-                        deposit(2u * static_cast<uint32_t>(c.y), g.M[1]) |
-                        deposit(2u * static_cast<uint32_t>(c.z), g.M[2]) |
-                        deposit(2u * static_cast<uint32_t>(c.w), g.M[3]);
+                        place(g, 2u * static_cast<uint32_t>(c.y), 1) |
+                        place(g, 2u * static_cast<uint32_t>(c.z), 2) |
+                        place(g, 2u * static_cast<uint32_t>(c.w), 3);
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint32_t*>(grid), 0, static_cast<int>(cells * 4), static_cast<int>(kBufDword3));
   const dw4 v0 = __builtin_bit_cast(
@@ -1978,11 +2096,11 @@ inline unsigned grid_for(int64_t n, int per = kBlock) {
 }
 
 void launch_zero(uint32_t* p, uint64_t n, hipStream_t stream, DeviceHeader* hdr = nullptr,
-                 int64_t n_out = 0) {
-  const uint64_t n4 = n / 4;
+                 int64_t n_out = 0, uint32_t* p2 = nullptr, uint64_t n2 = 0) {
+  const uint64_t n4 = (n > n2 ? n : n2) / 4;
   uint64_t blocks = (n4 + 4 * kBlock - 1) / (4 * kBlock);   // 4 stores per thread
   blocks = blocks < 1 ? 1 : (blocks > 65536 ? 65536 : blocks);
-  k_zero_u32<<<static_cast<unsigned>(blocks), kBlock, 0, stream>>>(p, n, hdr, n_out);
+  k_zero_u32<<<static_cast<unsigned>(blocks), kBlock, 0, stream>>>(p, n, hdr, n_out, p2, n2);
 }
 
 OffsetTable make_offsets(spconv_rulebook rb) {
@@ -2314,6 +2432,8 @@ bool make_grid_geom(int D, const int32_t* size, GridGeom* g, uint64_t* cells) {
   for (int L = 0; L < maxb; ++L)
     for (int j = D - 1; j >= 1; --j)
       if (bits[j] > L) g->M[j] |= 1u << pos++;
+  g->cubic = D > 1;
+  for (int j = 1; j < D; ++j) g->cubic = g->cubic && bits[j] == maxb;
   if (g->B > 29) return false;
   *cells = static_cast<uint64_t>(size[0]) << g->B;
   return *cells < kGridMaxCells;
@@ -2474,9 +2594,12 @@ int build_vsc_grid(spconv_rulebook rb, const int32_t* coords, const GridGeom& g,
 // same pass, the output set marked in a lexicographic bitmap over the output
 // grid; the bitmap ranked (rows in lexicographic order), and the emission of
 // the output sites fills the output grid, whose occupancy gives the Z-order
-// schedule.  Everything that must start at zero (input grid, lexicographic
-// bitmap, output grid and, for a one-launch schedule, its bitmap) is laid
-// out in one range and cleared by one launch.
+// schedule.  Everything that must start at zero (input grid; lexicographic
+// marks, output grid and, for a one-launch schedule, its bitmap) is laid out
+// in two ranges cleared by one launch, in one transient block; books for the
+// reversed direction take the input grid from a block of its own, so that
+// their builds make three allocations as those with transposed lists do (an
+// extra block costs an event on the build stream, ~2 us).
 int build_sc_grid(spconv_rulebook rb, const int32_t* coords, const GridGeom& gi,
                   uint64_t cells_in, const GridGeom& go, uint64_t cells_out) {
   const int64_t N = rb->n_in;
@@ -2485,38 +2608,60 @@ int build_sc_grid(spconv_rulebook rb, const int32_t* coords, const GridGeom& gi,
   for (int j = 0; j < rb->D; ++j) lex_cells *= static_cast<uint64_t>(rb->out_size[j]);
   const uint64_t lwords = (lex_cells + 31) / 32;
   const int64_t lnbw = static_cast<int64_t>((lwords + kBlock - 1) / kBlock);
-  const size_t bytes = align_up(cells_in * 4, 256) +
-                       align_up(lwords * 4, 256) + grid_bytes(cells_out) +
-                       align_up(static_cast<size_t>(lnbw) * 4, 256) + 256;
+  // large output grids are marked byte by byte (clearing and reading a byte
+  // per cell, at most 64 a row, costs less than the atomics)
+  const bool lself = lwords <= static_cast<uint64_t>(kSelfWords);
+  const bool bytes = !lself && lex_cells <= 64ull * static_cast<uint64_t>(N);
+  const size_t in_bytes = align_up(cells_in * 4, 256);
+  const size_t out_bytes = align_up(lwords * 4, 256) +
+                           (bytes ? align_up(lwords * 32, 256) : 0) + grid_bytes(cells_out) +
+                           align_up(static_cast<size_t>(lnbw) * 4, 256) + 256;
+  const bool own = rb->t_direct;
+  void* mem_in = nullptr;
   void* mem = nullptr;
-  if (dev_alloc(rb, bytes, rb->stream, &mem) != SPCONV_OK) return SPCONV_ENOMEM;
+  if (own && dev_alloc(rb, in_bytes, rb->stream, &mem_in) != SPCONV_OK) return SPCONV_ENOMEM;
+  if (dev_alloc(rb, out_bytes + (own ? 0 : in_bytes), rb->stream, &mem) != SPCONV_OK) {
+    (void)dev_free(rb, mem_in, rb->stream);
+    return SPCONV_ENOMEM;
+  }
   Carver cv{static_cast<char*>(mem)};
   GridBufs bi{};
-  bi.grid = cv.take<uint32_t>(cells_in);
-  uint32_t* lex = cv.take<uint32_t>(lwords);
+  bi.grid = own ? static_cast<uint32_t*>(mem_in) : cv.take<uint32_t>(cells_in);
+  uint32_t* lex_bits = bytes ? cv.take<uint32_t>(lwords) : nullptr;   // (written whole)
+  uint32_t* lex = cv.take<uint32_t>(bytes ? 8 * lwords : lwords);     // bytes or bits, cleared
   const GridBufs bo = take_grid(&cv, cells_out, true);
   uint32_t* lsum = cv.take<uint32_t>(static_cast<size_t>(lnbw));
-  uint32_t* from = bi.grid;
   uint32_t* to = bo.self ? bo.bitmap + bo.nwords : bo.grid + cells_out;
-  launch_zero(from, static_cast<uint64_t>(to - from), rb->stream, rb->hdr, 0);
+  launch_zero(bi.grid, cells_in, rb->stream, rb->hdr, 0, lex, static_cast<uint64_t>(to - lex));
   Extents E{};
   for (int j = 0; j < rb->D; ++j) E.e[j] = rb->out_size[j];
   const OffsetTable ot = make_offsets(rb);
   // a book on another book's outputs keeps its own copy of their count
   int64_t* cc = rb->in_count ? rb->n_in_dev : nullptr;
-  k_sc_scatter_mark<<<grid_for(N), kBlock, 0, rb->stream>>>(
+  bool rounds = true;
+  for (int j = 1; j < rb->D; ++j) rounds = rounds && rb->f[j] == rb->s[j];
+  auto mark = bytes ? k_sc_scatter_mark<kMarkBytes>
+                    : (rounds ? k_sc_scatter_mark<kMarkRounds> : k_sc_scatter_mark<kMarkFan>);
+  mark<<<grid_for(N), kBlock, 0, rb->stream>>>(
       coords, N, rb->in_count, gi, bi.grid, &rb->hdr->status, cc, ot, E, lex);
-  const bool lself = lwords <= static_cast<uint64_t>(kSelfWords);
+  if (bytes) {
+    k_bytes_bits<<<static_cast<unsigned>(lnbw), kBlock, 0, rb->stream>>>(
+        reinterpret_cast<const uint8_t*>(lex), lwords, lex_bits, lsum);
+    lex = lex_bits;
+  }
   if (!lself) {
-    k_bitsum<<<static_cast<unsigned>(lnbw), kBlock, 0, rb->stream>>>(lex, lwords, lsum);
+    if (!bytes)
+      k_bitsum<<<static_cast<unsigned>(lnbw), kBlock, 0, rb->stream>>>(lex, lwords, lsum);
     k_bitscan<<<1, kBlock, 0, rb->stream>>>(lsum, lnbw, rb->hdr, -1, nullptr);
   }
   const OutGrid og{go, bo.grid, bo.self ? bo.bitmap : nullptr};
-  k_sc_emit<<<static_cast<unsigned>(lnbw * kEmitParts), kBlock, 0, rb->stream>>>(
-      lex, lwords, lself ? nullptr : lsum, cout, E, rb->out_coords, nullptr, og, rb->hdr);
+  const int parts = emit_parts(lnbw);
+  k_sc_emit<<<static_cast<unsigned>(lnbw * parts), kBlock, 0, rb->stream>>>(
+      lex, lwords, lself ? nullptr : lsum, parts, cout, E, rb->out_coords, nullptr, og, rb->hdr);
   launch_grid_schedule(rb, bo, cells_out, -1, nullptr);
   launch_probe_grid(rb, rb->out_coords, gi, bi, cells_in);
-  if (dev_free(rb, mem, rb->stream) != SPCONV_OK) return SPCONV_EHIP;
+  const int f1 = dev_free(rb, mem, rb->stream), f2 = dev_free(rb, mem_in, rb->stream);
+  if (f1 != SPCONV_OK || f2 != SPCONV_OK) return SPCONV_EHIP;
   return hipGetLastError() == hipSuccess ? SPCONV_OK : SPCONV_EHIP;
 }
 }  // namespace
@@ -2642,8 +2787,9 @@ int build_sc(spconv_rulebook rb, const int32_t* coords) {
     k_sc_mark<<<grid_for(N), kBlock, 0, rb->stream>>>(tr.keys, N, nullptr, cin, ot, E, bitmap);
     k_bitsum<<<static_cast<unsigned>(nbw), kBlock, 0, rb->stream>>>(bitmap, nwords, bsum);
     k_bitscan<<<1, kBlock, 0, rb->stream>>>(bsum, nbw, rb->hdr, -1, nullptr);
-    k_sc_emit<<<static_cast<unsigned>(nbw * kEmitParts), kBlock, 0, rb->stream>>>(
-        bitmap, nwords, bsum, cout, E, rb->out_coords, out_keys, OutGrid{}, rb->hdr);
+    const int parts = emit_parts(nbw);
+    k_sc_emit<<<static_cast<unsigned>(nbw * parts), kBlock, 0, rb->stream>>>(
+        bitmap, nwords, bsum, parts, cout, E, rb->out_coords, out_keys, OutGrid{}, rb->hdr);
     launch_schedule(rb, out_keys, cout, &cv, 0, nullptr);
     launch_probe_scan_compact(rb, out_keys, cout, cin, tr);
   } else {

@@ -25,25 +25,31 @@ WIDTHS = [(8, 8), (24, 40), (40, 24), (72, 136), (192, 96), (136, 264), (16, 20)
           (65, 16), (33, 130), (5, 3), (2, 30), (48, 1), (129, 8)]
 
 
-def _layer(op, dtype):
+# layer -> (extent, f): overlapping fields (the transposed map), f = s on extents the stride
+# divides (no transposed structure) and leaves a border of (the transposed lists and map)
+SC_LAYERS = {"map": (24, 3), "direct": (24, 2), "border": (25, 2)}
+
+
+def _layer(op, layer):
     if op == "vsc":
         coords = inputs.pen_strokes(2, 64, seed=41, target=300)[:513]
         return coords, [2, 64, 64], [1, 3, 3], [1, 1, 1]
-    f = [1, 2, 2, 2] if dtype == "bf16" else [1, 3, 3, 3]   # single-offset runs / general map
-    return (inputs.surfaces(1, 24, 4.0, 10.0, seed=42, target=700)[:700], [1, 24, 24, 24], f,
-            [1, 2, 2, 2])
+    e, f = SC_LAYERS[layer]
+    return (inputs.surfaces(1, e, 4.0, 10.0, seed=42, target=700)[:700], [1] + [e] * 3,
+            [1] + [f] * 3, [1, 2, 2, 2])
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("op", ["vsc", "sc", "dc"])
-@pytest.mark.parametrize("ci,co", WIDTHS)
-def test_layer_and_gradients(op, ci, co, dtype):
-    coords, size, f, s = _layer(op, dtype)
+@pytest.mark.parametrize("op,layer", [("vsc", "")] + [(o, k) for o in ("sc", "dc")
+                                                      for k in SC_LAYERS])
+@pytest.mark.parametrize("ci,co", WIDTHS + [(32, 64), (96, 32), (256, 16)])
+def test_layer_and_gradients(op, layer, ci, co, dtype):
+    coords, size, f, s = _layer(op, layer)
     kind = spc.VSC if op == "vsc" else spc.SC
     rb = spc.build_rulebook(kind, _t(coords), size, f, s, transpose=op != "vsc")
     ref = oracle.Rulebook(kind, coords, size, f, s)
     rin, rout = (ref.n_out, ref.n_in) if op == "dc" else (ref.n_in, ref.n_out)
-    _say(f"[widths] {op} {rin} -> {rout} C={ci}->{co} {dtype}")
+    _say(f"[widths] {op} {layer} {rin} -> {rout} C={ci}->{co} {dtype}")
     x, dy = _feats(rin, ci, dtype, 1), _feats(rout, co, dtype, 2)
     wf = inputs.normal_f32((ref.K, ci, co), std=1.0 / np.sqrt(ref.K * ci), seed=3)
     w = inputs.to_bf16_bits(wf) if dtype == "bf16" else wf
@@ -79,3 +85,55 @@ def test_many_rows(ci, co, dtype):
     c = dense_ref.random_sites(np.random.default_rng(43), [1, 64, 64, 64], 0.62)
     compare_layer(spc.VSC, c, [1, 64, 64, 64], [1, 1, 1, 3], [1] * 4, ci, co, dtype=dtype,
                   what="many rows")
+
+
+@pytest.mark.parametrize("ci,co,dtype", [(64, 32, "bf16"), (136, 40, "bf16"), (40, 72, "f32"),
+                                         (7, 24, "f32")])
+def test_many_rows_reversed(ci, co, dtype):
+    """DC and the SC input gradient (f = s) on enough rows for the largest row tiles."""
+    size, f = [1, 64, 64, 64], [1, 1, 1, 2]
+    c = dense_ref.random_sites(np.random.default_rng(44), size, 0.62)
+    c = c[np.random.default_rng(45).permutation(len(c))]
+    rb = spc.build_rulebook(spc.SC, _t(c), size, f, f, transpose=True)
+    ref = oracle.Rulebook(oracle.SC, c, size, f, f)
+    rtol = RTOL_F32 if dtype == "f32" else RTOL_BF16
+    w = _feats(2 * ci, co, dtype, 7).reshape(2, ci, co)
+    b = inputs.normal_f32((co,), seed=8)
+    x, dy = _feats(ref.n_out, ci, dtype, 9), _feats(ref.n_out, co, dtype, 10)
+    y = spc.dc_forward(rb, _dev(x, dtype), _dev(w, dtype), _t(b))
+    yo, ab = ref.dc_forward(x, w, b, in_dt=_odt(dtype))
+    check_features(_to_np(y), yo, ab, rtol, "DC")
+    dx = spc.backward_data(rb, spc.OP_SC, _dev(dy, dtype), _dev(w, dtype))
+    dxo, ad = ref.backward_data(oracle.SC, dy, w, _odt(dtype))
+    check_features(_to_np(dx), dxo, ad, rtol, "dx")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_reversed_on_the_vector_path(monkeypatch, dtype):
+    """The f = s reversed direction without the matrix cores gives the same results within the
+    two paths' bounds."""
+    coords, size, f, s = _layer("dc", "direct")
+    rb = spc.build_rulebook(spc.SC, _t(coords), size, f, s, transpose=True)
+    ref = oracle.Rulebook(oracle.SC, coords, size, f, s)
+    x, w = _feats(ref.n_out, 20, dtype, 1), _feats(8 * 20, 12, dtype, 2).reshape(8, 20, 12)
+    monkeypatch.setenv("SPCONV_FORCE_PATH", "vec")
+    y = spc.dc_forward(rb, _dev(x, dtype), _dev(w, dtype))
+    yo, ab = ref.dc_forward(x, w, None, in_dt=_odt(dtype))
+    check_features(_to_np(y), yo, ab, RTOL_F32 if dtype == "f32" else RTOL_BF16, "DC")
+    g = _feats(ref.n_out, 12, dtype, 3)
+    dx = spc.backward_data(rb, spc.OP_SC, _dev(g, dtype), _dev(w, dtype))
+    dxo, ad = ref.backward_data(oracle.SC, g, w, _odt(dtype))
+    check_features(_to_np(dx), dxo, ad, RTOL_F32 if dtype == "f32" else RTOL_BF16, "dx")
+
+
+@pytest.mark.parametrize("size,f,s", [([3, 101, 77, 95], [1, 3, 3, 3], [1, 2, 2, 2]),
+                                      ([2, 130, 100, 90], [1, 2, 2, 2], [1, 2, 2, 2]),
+                                      ([1, 300, 1000], [1, 1, 2], [1, 1, 1]),
+                                      ([1, 1100, 1100], [1, 3, 1], [1, 2, 1])])
+def test_strided_book_on_large_output_grids(size, f, s):
+    """Output grids past 2^18 cells with at most 64 cells per input site (marked byte by byte),
+    and one with more (marked by bits)."""
+    n = 3000 if size[1] == 1100 else 30000
+    rng = np.random.default_rng(46)
+    c = np.unique(np.stack([rng.integers(0, e, n) for e in size], 1), axis=0).astype(np.int32)
+    compare_layer(spc.SC, c[rng.permutation(len(c))], size, f, s, 16, 16, what="large outputs")
