@@ -12,6 +12,7 @@ the paper).  Everything runs on torch's current stream.
 from __future__ import annotations
 
 import ctypes
+import functools
 
 import numpy as np
 
@@ -29,13 +30,27 @@ __all__ = ["VSC", "SC", "F32", "BF16", "BUILD_ASYNC", "BUILD_TRANSPOSE", "OP_VSC
            "SpconvError", "OK", "EINVAL", "EDUP", "ERANGE", "ENOMEM", "ECAP", "EHIP"]
 
 
+_TORCH = None
+_RAW_STREAM = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _TORCH, _RAW_STREAM
+    if _TORCH is None:
+        import torch
+        # the current stream's handle without a Stream object around it
+        _RAW_STREAM = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _TORCH = torch
+    return _TORCH
 
 
 def _stream_ptr(stream=None):
+    """The stream's handle (the current one of the current device): the
+    wrapper object torch.cuda.current_stream() makes costs 4 us a call, a
+    third of a small layer's whole host time with its book."""
     torch = _torch()
+    if stream is None and _RAW_STREAM is not None and torch.cuda.is_initialized():
+        return ctypes.c_void_p(_RAW_STREAM(torch._C._cuda_getDevice()))
     s = stream if stream is not None else torch.cuda.current_stream()
     return ctypes.c_void_p(s.cuda_stream)
 
@@ -49,11 +64,21 @@ def _dtype_code(t):
     raise TypeError(f"unsupported dtype {t}: use float32 or bfloat16")
 
 
+@functools.lru_cache(maxsize=256)
+def _i32_tuple(v):
+    """The tuple's ints as a C int32 array, which the library only reads (every
+    call with the same extents, filter or strides marshals the same few
+    numbers)."""
+    return np.ctypeslib.as_ctypes(np.array(v, dtype=np.int32))
+
+
 def _i32_array(v, D, name):
+    if type(v) in (list, tuple) and len(v) == D and all(type(e) is int for e in v):
+        return _i32_tuple(tuple(v))
     a = np.ascontiguousarray(np.asarray(v, dtype=np.int32).reshape(-1))
     if a.size != D:
         raise ValueError(f"{name} needs {D} entries, got {a.size}")
-    return a
+    return np.ctypeslib.as_ctypes(a)
 
 
 class Rulebook:
@@ -222,12 +247,11 @@ def build_rulebook(kind, coords, spatial_size, f, s=None, *, sync=True, transpos
     D = coords.shape[1]
     size = _i32_array(spatial_size, D, "spatial_size")
     fa = _i32_array(f, D, "f")
-    sa = _i32_array(np.ones(D) if s is None else s, D, "s")
+    sa = _i32_array((1,) * D if s is None else s, D, "s")
     h = ctypes.c_void_p()
     st_ptr = _stream_ptr(stream)
     st = lib.spconv_build_rulebook(kind, D, coords.data_ptr() if coords.shape[0] else None,
-                                   coords.shape[0], size.ctypes.data, fa.ctypes.data,
-                                   sa.ctypes.data,
+                                   coords.shape[0], size, fa, sa,
                                    (0 if sync else BUILD_ASYNC) | (BUILD_TRANSPOSE if transpose else 0),
                                    st_ptr,
                                    ctypes.byref(h))
@@ -244,10 +268,10 @@ def build_rulebook_on(parent, kind, f, s=None, *, sync=True, stream=None):
         raise ValueError("the parent must be an SC rule book")
     D = parent.D
     fa = _i32_array(f, D, "f")
-    sa = _i32_array(np.ones(D) if s is None else s, D, "s")
+    sa = _i32_array((1,) * D if s is None else s, D, "s")
     h = ctypes.c_void_p()
     st_ptr = _stream_ptr(stream)
-    _lib.check(lib.spconv_build_rulebook_on(parent.handle, kind, fa.ctypes.data, sa.ctypes.data,
+    _lib.check(lib.spconv_build_rulebook_on(parent.handle, kind, fa, sa,
                                             0 if sync else BUILD_ASYNC, st_ptr, ctypes.byref(h)),
                "spconv_build_rulebook_on")
     rb = Rulebook(h, kind, D, st_ptr)
