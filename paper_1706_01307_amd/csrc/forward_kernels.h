@@ -454,14 +454,120 @@ __device__ __forceinline__ uint32_t map_blocks(int32_t v) {
   return pres;
 }
 
+// 16 bytes of adjacent output elements, rounded once; and read back as fp32.
+__device__ __forceinline__ void store16(float* p, const float* v) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void store16(uint16_t* p, const float* v) {
+  uint4 u;
+  u.x = f32_to_bf16(v[0]) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16);
+  u.y = f32_to_bf16(v[2]) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
+  u.z = f32_to_bf16(v[4]) | (static_cast<uint32_t>(f32_to_bf16(v[5])) << 16);
+  u.w = f32_to_bf16(v[6]) | (static_cast<uint32_t>(f32_to_bf16(v[7])) << 16);
+  *reinterpret_cast<uint4*>(p) = u;
+}
+template <typename TOut>
+__device__ __forceinline__ float piece_elem(const u32x4& u, int e) {
+  if constexpr (sizeof(TOut) == 4) return __uint_as_float(u[e]);
+  return __uint_as_float(e & 1 ? u[e / 2] & 0xffff0000u : u[e / 2] << 16);
+}
+
+// Epilogue of the matrix-core kernels: bias (scale, residual, ReLU), one
+// rounding, the store.  W^T was the first operand of the products, so a lane
+// holds LC = 4 NCB adjacent columns, from col0 + LC (lane / 16), of row lane
+// mod 16 of each block, and moves them in 16-byte pieces (x as the first
+// operand leaves NCB columns of four rows per lane: 4- to 8-byte pieces and
+// four times the row numbers; the 2^3 stride-2 layer 32 -> 64 of 1,703,204
+// rows with its affine and ReLU fused took 102 us so, 78 us now; 902,504 rows
+// 64 -> 64 3^3, with 207 registers instead of 225, 302 and 293 us).
+// rowv: the output row of the wave's row map_lane (-1: none).  FULL: every
+// column of the tile exists; otherwise columns past C_out are dropped, and rows
+// that are no whole pieces go element by element.
+template <typename TOut, int RB, int NCB, bool FULL>
+__device__ __forceinline__ void store_tile(const f32x4 (&acc)[RB][NCB], int32_t rowv,
+                                           const float* bias, TOut* y, int C_out, int col0,
+                                           int lg, const Epilogue& epi) {
+  constexpr int LC = 4 * NCB;
+  constexpr int P16 = 16 / static_cast<int>(sizeof(TOut));
+  constexpr int PC = LC < P16 ? LC : P16;         // (one block of bf16 columns: 8 bytes)
+  constexpr int NP = LC / PC;
+  const int n0 = col0 + lg * LC;
+  const bool whole = FULL || C_out % PC == 0;
+  int32_t row[RB];
+  spread_map<RB>(rowv, row);
+  const TOut* res = static_cast<const TOut*>(epi.res);
+  u32x4 rv[RB][NP];
+  if (res && whole) {
+    // all blocks' residual pieces first, so that their latencies overlap (a
+    // row of -1 reads row 0, which exists whenever this tile runs)
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        const int n = n0 + q * PC;
+        const TOut* p = res + static_cast<int64_t>(row[b] >= 0 ? row[b] : 0) * C_out +
+                        (FULL || n < C_out ? n : 0);
+        if constexpr (PC == P16) {
+          rv[b][q] = *reinterpret_cast<const u32x4*>(p);
+        } else {
+          const uint2 u = *reinterpret_cast<const uint2*>(p);
+          rv[b][q] = u32x4{u.x, u.y, 0u, 0u};
+        }
+      }
+  }
+  float bv[LC], sv[LC];
+#pragma unroll
+  for (int e = 0; e < LC; ++e) {
+    const int n = FULL || n0 + e < C_out ? n0 + e : C_out - 1;
+    bv[e] = bias ? bias[n] : 0.0f;
+    sv[e] = epi.scale ? epi.scale[n] : 1.0f;
+  }
+#pragma unroll
+  for (int b = 0; b < RB; ++b) {
+    if (row[b] < 0) continue;
+    TOut* out = y + static_cast<int64_t>(row[b]) * C_out + n0;
+    float z[LC];
+#pragma unroll
+    for (int e = 0; e < LC; ++e) {
+      const float a = acc[b][e / 4][e % 4];
+      z[e] = epi.scale ? fmaf(a, sv[e], bv[e]) : a + bv[e];
+    }
+    if (res) {
+#pragma unroll
+      for (int e = 0; e < LC; ++e) {
+        if (whole)
+          z[e] += piece_elem<TOut>(rv[b][e / PC], e % PC);
+        else if (n0 + e < C_out)
+          z[e] += ElemIO<TOut>::load(res, static_cast<int64_t>(row[b]) * C_out + n0 + e);
+      }
+    }
+    if (epi.relu) {
+#pragma unroll
+      for (int e = 0; e < LC; ++e) z[e] = z[e] < 0.0f ? 0.0f : z[e];
+    }
+    if (whole) {
+#pragma unroll
+      for (int q = 0; q < NP; ++q)
+        if (FULL || n0 + q * PC < C_out) {
+          if constexpr (PC == P16) store16(out + q * PC, z + q * PC);
+          else OutStore<TOut, PC>::store(out + q * PC, z + q * PC);
+        }
+    } else {
+#pragma unroll
+      for (int e = 0; e < LC; ++e)
+        if (n0 + e < C_out) ElemIO<TOut>::store(out, e, z[e]);
+    }
+  }
+}
+
 // Tile of the output handled by one workgroup: 4 waves x RB blocks of 16 rows,
 // NCB blocks of 16 columns (the whole workgroup shares one column chunk).
 //
-// Lane layout (16x16 MFMA): lane l = 16 g + r.  A operand: row r of the
-// 16-row block, k-chunk bytes [16 g, 16 g + 16).  B operand: output column
-// r * NCB + cb of the chunk (so a lane ends up owning NCB adjacent columns),
-// same k bytes.  Result: lane l holds rows 4 g + v (v = 0..3), columns
-// r * NCB + cb.
+// Lane layout (16x16 MFMA): lane l = 16 g + r.  Gathered rows (second operand):
+// row r of the 16-row block, k-chunk bytes [16 g, 16 g + 16).  W^T (first
+// operand): LDS row 16 cb + r of the chunk, same k bytes.  Result: lane l holds
+// row r's products with LDS rows 16 cb + 4 g + v (v = 0..3), which are the
+// columns 4 NCB g + 4 cb + v, so 4 NCB adjacent ones in all.
 //
 // Pipeline over the offsets (iteration i): G(i+3) and W^(i+2) are fetched,
 // gathered rows A(i+2) are issued (their gather-map entries G(i+2) arrived
@@ -469,7 +575,7 @@ __device__ __forceinline__ uint32_t map_blocks(int32_t v) {
 // of W^i, and W^(i+1) (fetched one iteration earlier) is written transposed
 // into the other LDS buffer.  One barrier per offset publishes W^(i+1).
 template <typename TIn, int NCH, int NCB, int RB, typename TOut, int KT, bool SKIP = false,
-          int WT = 0, bool LSKIP = false, bool EPI = false>
+          int WT = 0, bool LSKIP = false>
 __global__ __launch_bounds__(256, 2) void k_fwd_mfma(
     const int32_t* __restrict__ gmap, const int32_t* __restrict__ perm, int64_t gstride,
     const DeviceHeader* __restrict__ hdr, int K_arg,
@@ -564,10 +670,10 @@ __global__ __launch_bounds__(256, 2) void k_fwd_mfma(
     }
   };
   // ---- registers -> LDS, transposed: one LDS row per column n holding
-  // W^i[k][n] for all k.  Column n = NCB r + cb (lane r's cb-th column) sits
-  // in LDS row 16 cb + r, so the lanes that read one fragment chunk together
+  // W^i[k][n] for all k.  Column n = 4 NCB g + 4 cb + v (lane group g's) sits
+  // in LDS row 16 cb + 4 g + v; the lanes that read one fragment chunk together
   // read 16 consecutive rows (spread over the banks by WImage).
-  auto w_row = [](int n) { return (n % NCB) * 16 + n / NCB; };
+  auto w_row = [](int n) { return n % (4 * NCB) / 4 * 16 + n / (4 * NCB) * 4 + n % 4; };
   auto w_store = [&](int i, const WRegs& wr) {
     if (i >= K) return;
     unsigned char* dst = s_w[i & 1];
@@ -665,7 +771,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_mfma(
         if (SKIP && !(pres & (1u << b))) continue;   // all 16 rows lack offset i
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
-          acc[b][cb] = MT<TIn>::mma(a[b][ch], bw[cb], acc[b][cb]);
+          acc[b][cb] = MT<TIn>::mma(bw[cb], a[b][ch], acc[b][cb]);
       }
     }
   };
@@ -716,75 +822,9 @@ __global__ __launch_bounds__(256, 2) void k_fwd_mfma(
     }
   }
 
-  // ---- epilogue: bias (EPI: scale, residual, ReLU), round once, store NCB
-  // adjacent columns per lane-row
-  float bv[NCB];
-#pragma unroll
-  for (int cb = 0; cb < NCB; ++cb) bv[cb] = bias ? bias[col0 + lr * NCB + cb] : 0.0f;
-  if constexpr (!EPI) {
-#pragma unroll
-    for (int b = 0; b < RB; ++b) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t pos = row0 + b * 16 + lg * 4 + v;   // schedule position
-        const int64_t row = pos < n_rows ? perm[pos] : -1;
-        if (row >= 0) {                                   // -1: padding of a segmented view
-          float o[NCB];
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) o[cb] = acc[b][cb][v] + bv[cb];
-          OutStore<TOut, NCB>::store(y + row * C_out + col0 + lr * NCB, o);
-        }
-      }
-    }
-  } else {
-    // the block epilogue: all output rows first, then all residual loads (a
-    // row of -1, padding, reads row 0, which exists whenever this tile runs),
-    // so that their latencies overlap instead of one per store
-    float sv[NCB];
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) sv[cb] = epi.scale ? epi.scale[col0 + lr * NCB + cb] : 1.0f;
-    int64_t rows[RB][4];
-#pragma unroll
-    for (int b = 0; b < RB; ++b)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t pos = row0 + b * 16 + lg * 4 + v;
-        rows[b][v] = pos < n_rows ? perm[pos] : -1;
-      }
-    const TOut* res = static_cast<const TOut*>(epi.res);
-    float r[RB][4][NCB];
-    if (res) {
-#pragma unroll
-      for (int b = 0; b < RB; ++b)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int64_t row = rows[b][v] >= 0 ? rows[b][v] : 0;
-          OutLoad<TOut, NCB>::load(res + row * C_out + col0 + lr * NCB, r[b][v]);
-        }
-    }
-#pragma unroll
-    for (int b = 0; b < RB; ++b) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t row = rows[b][v];
-        if (row >= 0) {
-          float o[NCB];
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb)
-            o[cb] = epi.scale ? fmaf(acc[b][cb][v], sv[cb], bv[cb]) : acc[b][cb][v] + bv[cb];
-          if (res) {
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) o[cb] += r[b][v][cb];
-          }
-          if (epi.relu) {
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) o[cb] = o[cb] < 0.0f ? 0.0f : o[cb];
-          }
-          OutStore<TOut, NCB>::store(y + row * C_out + col0 + lr * NCB, o);
-        }
-      }
-    }
-  }
+  // ---- epilogue (a perm entry of -1: padding of a segmented view)
+  store_tile<TOut, RB, NCB, true>(acc, map_row < n_rows ? perm[map_row] : -1, bias, y, C_out,
+                                  col0, lg, epi);
 }
 
 // ---------------------------------------------------------------------------
@@ -821,15 +861,6 @@ void launch_mfma_rb(const Call& c) {
            : c.v.K == 1 ? k_fwd_mfma<TIn, NCH, NCB, RB, TOut, 1, true, WT>
            : c.v.K == 8 ? k_fwd_mfma<TIn, NCH, NCB, RB, TOut, 8, true, WT, true>
                         : kern;
-  }
-  // The block epilogue (scale / residual / ReLU) is compiled into its own
-  // kernels, so that the plain forward keeps its register count.
-  if constexpr (WT == 0) {
-    if (c.epi.scale || c.epi.res || c.epi.relu) {
-      kern = k_fwd_mfma<TIn, NCH, NCB, RB, TOut, 0, true, WT, true, true>;
-      if constexpr (!SMALL)
-        if (c.v.K == 27) kern = k_fwd_mfma<TIn, NCH, NCB, RB, TOut, 27, true, WT, false, true>;
-    }
   }
   kern<<<grid, 256, 0, c.stream>>>(
       c.v.gmap, c.v.perm, c.v.gstride, c.v.hdr, static_cast<int>(c.v.K),

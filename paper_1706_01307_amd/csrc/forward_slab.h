@@ -61,11 +61,7 @@ __device__ __forceinline__ u32x4 buf_piece(__amdgpu_buffer_rsrc_t r, uint32_t of
 // LDS image, transposed as WImage describes.  WT 0: a task is KPT k-rows x one
 // 16-byte piece of columns (bf16 packs pairs of k-rows); WT 1 / 2 (w holds
 // W^T): one 16-byte piece of k of one column.
-// LDS row of column n of the tile: with x as the first operand (result rows =
-// positions) lane r of a 16-lane group ends up with columns r NCB ..;
-// ROWS: with W^T as the first operand (result rows = columns) the lanes of
-// group g end up with columns 4 NCB g .. of one position each.
-template <typename TIn, int NCH, int NCB, int WT, bool AX, bool AW, bool ROWS = false>
+template <typename TIn, int NCH, int NCB, int WT, bool AX, bool AW>
 struct WStage {
   static constexpr int ESZ = static_cast<int>(sizeof(TIn));
   static constexpr int EPP = 16 / ESZ;
@@ -103,9 +99,9 @@ struct WStage {
       }
     }
   }
+  // column n of the tile sits where k_fwd_mfma puts it
   __device__ static int row_of(int n) {
-    if constexpr (ROWS) return n % (4 * NCB) / 4 * 16 + n / (4 * NCB) * 4 + n % 4;
-    return (n % NCB) * 16 + n / NCB;
+    return n % (4 * NCB) / 4 * 16 + n / (4 * NCB) * 4 + n % 4;
   }
   __device__ static void store(unsigned char* dst, const Regs& r) {
 #pragma unroll
@@ -240,7 +236,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
       for (int b = 0; b < RB; ++b) {
         if (!(pres & (1u << b))) continue;               // all 16 rows lack this offset
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) acc[b][cb] = MT<TIn>::mma(a[b][ch], bw[cb], acc[b][cb]);
+        for (int cb = 0; cb < NCB; ++cb) acc[b][cb] = MT<TIn>::mma(bw[cb], a[b][ch], acc[b][cb]);
       }
     }
   };
@@ -291,67 +287,8 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
     step(e + 2, a2, p2, a1, p1, g2, g1, w0, w1);
   }
 
-  // epilogue: affine, residual, ReLU, one rounding; pieces of adjacent columns
-  constexpr int PC = NCB % 4 == 0 ? 4 : (NCB % 2 == 0 ? 2 : 1);
-  const bool whole = C_out % PC == 0;             // a piece is then in or out as a whole
-  const TOut* res = static_cast<const TOut*>(epi.res);
-#pragma unroll
-  for (int b = 0; b < RB; ++b) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t pos = row0 + b * 16 + lg * 4 + v;
-      const int64_t row = pos < n_rows ? perm[pos] : -1;
-      if (row < 0) continue;                      // past the end, padding of a segmented view
-#pragma unroll
-      for (int pc = 0; pc < NCB / PC; ++pc) {
-        const int n = col0 + lr * NCB + pc * PC;
-        if (n >= C_out) continue;
-        const int64_t o = row * C_out + n;
-        float z[PC];
-#pragma unroll
-        for (int e = 0; e < PC; ++e) {
-          const int ne = n + e < C_out ? n + e : C_out - 1;
-          const float bv = bias ? bias[ne] : 0.0f;
-          const float a = acc[b][pc * PC + e][v];
-          z[e] = epi.scale ? fmaf(a, epi.scale[ne], bv) : a + bv;
-        }
-        if (res) {
-          float rv[PC];
-          if (whole) {
-            OutLoad<TOut, PC>::load(res + o, rv);
-          } else {
-#pragma unroll
-            for (int e = 0; e < PC; ++e)
-              rv[e] = ElemIO<TOut>::load(res, n + e < C_out ? o + e : o);
-          }
-#pragma unroll
-          for (int e = 0; e < PC; ++e) z[e] += rv[e];
-        }
-        if (epi.relu) {
-#pragma unroll
-          for (int e = 0; e < PC; ++e) z[e] = z[e] < 0.0f ? 0.0f : z[e];
-        }
-        if (whole) {
-          OutStore<TOut, PC>::store(y + o, z);
-        } else {
-#pragma unroll
-          for (int e = 0; e < PC; ++e)
-            if (n + e < C_out) ElemIO<TOut>::store(y, o + e, z[e]);
-        }
-      }
-    }
-  }
-}
-
-// 16 bytes of adjacent output elements, rounded once.
-__device__ __forceinline__ void store16(float* p, const float* v) { OutStore<float, 4>::store(p, v); }
-__device__ __forceinline__ void store16(uint16_t* p, const float* v) {
-  uint4 u;
-  u.x = f32_to_bf16(v[0]) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16);
-  u.y = f32_to_bf16(v[2]) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
-  u.z = f32_to_bf16(v[4]) | (static_cast<uint32_t>(f32_to_bf16(v[5])) << 16);
-  u.w = f32_to_bf16(v[6]) | (static_cast<uint32_t>(f32_to_bf16(v[7])) << 16);
-  *reinterpret_cast<uint4*>(p) = u;
+  store_tile<TOut, RB, NCB, false>(acc, map_row < n_rows ? perm[map_row] : -1, bias, y, C_out,
+                                   col0, lg, epi);
 }
 
 // ---------------------------------------------------------------------------
@@ -379,7 +316,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_up(
     const DeviceHeader* __restrict__ hdr, int K, const TIn* __restrict__ x, uint32_t x_bytes,
     const TIn* __restrict__ w, uint32_t w_bytes, const float* __restrict__ bias,
     TOut* __restrict__ y, int C_in, int C_out, int64_t ntiles) {
-  using WS = WStage<TIn, NCH, NCB, WT, AX, AW, true>;
+  using WS = WStage<TIn, NCH, NCB, WT, AX, AW>;
   constexpr int KC = MT<TIn>::KC;
   constexpr int SLAB = WS::SLAB;
   constexpr int EPP = WS::EPP, ESZ = WS::ESZ, ROWB = WS::ROWB;
