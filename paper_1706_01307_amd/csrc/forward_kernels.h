@@ -574,9 +574,19 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[RB][NCB], int32_t 
 // one iteration earlier), the MFMAs of offset i run on A(i) and the LDS copy
 // of W^i, and W^(i+1) (fetched one iteration earlier) is written transposed
 // into the other LDS buffer.  One barrier per offset publishes W^(i+1).
+//
+// kNear (64 bf16 planes to 64 columns per tile, 27 offsets): rows and W^i are
+// requested one offset ahead instead of two, into two row sets instead of
+// three; 167 registers instead of 207 let three workgroups share a compute
+// unit instead of two, which hides more than the longer distance does
+// (902,504 surface rows 64 -> 64 3^3: 298 -> 284 us).  Other shapes gain no
+// workgroup by it, or lose (128 planes: 53 -> 68 us, RB = 2; 32 planes, which
+// go from four to five, are the same).
+template <typename TIn, int NCH, int NCB, int RB, int KT>
+constexpr bool kNear = sizeof(TIn) == 2 && NCH == 2 && NCB == 4 && RB == 4 && KT == 27;
 template <typename TIn, int NCH, int NCB, int RB, typename TOut, int KT, bool SKIP = false,
           int WT = 0, bool LSKIP = false>
-__global__ __launch_bounds__(256, 2) void k_fwd_mfma(
+__global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k_fwd_mfma(
     const int32_t* __restrict__ gmap, const int32_t* __restrict__ perm, int64_t gstride,
     const DeviceHeader* __restrict__ hdr, int K_arg,
     const TIn* __restrict__ x, uint32_t x_bytes, const TIn* __restrict__ w,
@@ -776,49 +786,79 @@ __global__ __launch_bounds__(256, 2) void k_fwd_mfma(
     }
   };
 
-  // Three rotating register sets (offsets i, i+1, i+2 modulo 3).
-  GRegs g0, g1, g2;
-  ARegs a0, a1, a2;
-  WRegs w0, w1, w2;
-  uint32_t p0 = 0, p1 = 0, p2 = 0;
-
-  // prologue: W^0 into LDS, W^1 in registers, A(0), A(1), G(2) in flight
-  g_load(0, g0);
-  g_load(1, g1);
-  g_load(2, g2);
-  w_load(0, w0);
-  w_load(1, w1);
-  p0 = a_load(g0, a0);
-  p1 = a_load(g1, a1);
-  w_store(0, w0);
-  __syncthreads();
-
-  // iteration i uses set (i mod 3): A(i) in aU, G(i+2) in gF -> A(i+2) into aF,
-  // G(i+3) into gU; W^(i+1) stored from wN, W^(i+2) loaded into wF.
-  auto step = [&](int i, ARegs& aU, uint32_t& pU, ARegs& aF, uint32_t& pF, GRegs& gU,
-                  GRegs& gF, WRegs& wN, WRegs& wF) {
-    if (i >= K) return;
-    // issue order matters: the in-order load counter lets a later wait for
-    // G(i+3) or W^(i+2) leave the gathered rows issued after them in flight
-    g_load(i + 3, gU);
-    w_load(i + 2, wF);
-    pF = a_load(gF, aF);
-    mma(i, aU, pU);
-    w_store(i + 1, wN);
+  if constexpr (kNear<TIn, NCH, NCB, RB, KT>) {
+    // two row sets: iteration i multiplies A(i) while A(i+1) and W^(i+1) come;
+    // G(i+2) is requested before them, for the in-order load counter
+    GRegs g0, g1;
+    ARegs a0, a1;
+    WRegs w0;
+    uint32_t p0 = 0, p1 = 0;
+    g_load(0, g0);
+    g_load(1, g1);
+    w_load(0, w0);
+    p0 = a_load(g0, a0);
+    w_store(0, w0);
     __syncthreads();
-  };
-  if constexpr (KT > 0) {
+    auto step = [&](int i, ARegs& aU, uint32_t& pU, ARegs& aF, uint32_t& pF, GRegs& gU,
+                    GRegs& gF) {
+      if (i >= K) return;
+      g_load(i + 2, gU);
+      w_load(i + 1, w0);
+      pF = a_load(gF, aF);
+      mma(i, aU, pU);
+      w_store(i + 1, w0);
+      __syncthreads();
+    };
 #pragma unroll
-    for (int i = 0; i < KT; i += 3) {
-      step(i, a0, p0, a2, p2, g0, g2, w1, w2);
-      step(i + 1, a1, p1, a0, p0, g1, g0, w2, w0);
-      step(i + 2, a2, p2, a1, p1, g2, g1, w0, w1);
+    for (int i = 0; i < KT; i += 2) {
+      step(i, a0, p0, a1, p1, g0, g1);
+      step(i + 1, a1, p1, a0, p0, g1, g0);
     }
   } else {
-    for (int i = 0; i < K; i += 3) {
-      step(i, a0, p0, a2, p2, g0, g2, w1, w2);
-      step(i + 1, a1, p1, a0, p0, g1, g0, w2, w0);
-      step(i + 2, a2, p2, a1, p1, g2, g1, w0, w1);
+    // Three rotating register sets (offsets i, i+1, i+2 modulo 3).
+    GRegs g0, g1, g2;
+    ARegs a0, a1, a2;
+    WRegs w0, w1, w2;
+    uint32_t p0 = 0, p1 = 0, p2 = 0;
+
+    // prologue: W^0 into LDS, W^1 in registers, A(0), A(1), G(2) in flight
+    g_load(0, g0);
+    g_load(1, g1);
+    g_load(2, g2);
+    w_load(0, w0);
+    w_load(1, w1);
+    p0 = a_load(g0, a0);
+    p1 = a_load(g1, a1);
+    w_store(0, w0);
+    __syncthreads();
+
+    // iteration i uses set (i mod 3): A(i) in aU, G(i+2) in gF -> A(i+2) into aF,
+    // G(i+3) into gU; W^(i+1) stored from wN, W^(i+2) loaded into wF.
+    auto step = [&](int i, ARegs& aU, uint32_t& pU, ARegs& aF, uint32_t& pF, GRegs& gU,
+                    GRegs& gF, WRegs& wN, WRegs& wF) {
+      if (i >= K) return;
+      // issue order matters: the in-order load counter lets a later wait for
+      // G(i+3) or W^(i+2) leave the gathered rows issued after them in flight
+      g_load(i + 3, gU);
+      w_load(i + 2, wF);
+      pF = a_load(gF, aF);
+      mma(i, aU, pU);
+      w_store(i + 1, wN);
+      __syncthreads();
+    };
+    if constexpr (KT > 0) {
+#pragma unroll
+      for (int i = 0; i < KT; i += 3) {
+        step(i, a0, p0, a2, p2, g0, g2, w1, w2);
+        step(i + 1, a1, p1, a0, p0, g1, g0, w2, w0);
+        step(i + 2, a2, p2, a1, p1, g2, g1, w0, w1);
+      }
+    } else {
+      for (int i = 0; i < K; i += 3) {
+        step(i, a0, p0, a2, p2, g0, g2, w1, w2);
+        step(i + 1, a1, p1, a0, p0, g1, g0, w2, w0);
+        step(i + 2, a2, p2, a1, p1, g2, g1, w0, w1);
+      }
     }
   }
 
