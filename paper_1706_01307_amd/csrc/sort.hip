@@ -14,8 +14,12 @@ namespace spc {
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kItems = 8;                       // elements per thread per block
-constexpr int kSortTile = kBlock * kItems;      // 2048 elements per block
+// Elements per thread of a block: 8, or 4 where blocks of 8 would be fewer
+// than two per compute unit (every pass is then bound by latency).
+constexpr int kItemsMax = 8, kItemsMin = 4;
+inline int sort_items(int64_t n_cap) {
+  return (n_cap + kBlock * kItemsMax - 1) / (kBlock * kItemsMax) < 512 ? kItemsMin : kItemsMax;
+}
 constexpr int kMaxDigits = 512;
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(uint32_t* __restrict__ a,
 // ---------------------------------------------------------------------------
 // Radix sort passes
 // ---------------------------------------------------------------------------
-template <int DB>
+template <int DB, int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint64_t* __restrict__ keys,
                                                     const DeviceHeader* __restrict__ hdr,
                                                     int shift, int64_t nblocks,
@@ -144,9 +148,9 @@ __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint64_t* __restrict__
   for (int d = threadIdx.x; d < kDig; d += kBlock) s_h[d] = 0;
   __syncthreads();
   const int64_t n = hdr->n_out;
-  const int64_t base = blockIdx.x * static_cast<int64_t>(kSortTile);
+  const int64_t base = blockIdx.x * static_cast<int64_t>(kBlock * ITEMS);
 #pragma unroll
-  for (int r = 0; r < kItems; ++r) {
+  for (int r = 0; r < ITEMS; ++r) {
     const int64_t e = base + r * kBlock + threadIdx.x;
     if (e < n) atomicAdd(&s_h[(keys[e] >> shift) & (kDig - 1)], 1u);
   }
@@ -159,8 +163,9 @@ __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint64_t* __restrict__
 // ranked with DB ballots, across waves and rounds with LDS counters.  A block
 // per compute unit or less (202 blocks for 412,345 sites), bound by latency:
 // loading each round's elements in the round took 11.4 us there, all at the
-// start 8.9 us (RSI us with half the elements per block).
-template <int DB>
+// start 8.9 us, half the elements per block as well
+// 7.7 us.
+template <int DB, int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_rs_scatter(
     const uint64_t* __restrict__ keys, const int32_t* __restrict__ vals,
     uint64_t* __restrict__ keys_out, int32_t* __restrict__ vals_out,
@@ -172,20 +177,20 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(
   __shared__ uint32_t s_wcnt[kBlock / kWave][kDig];
   const int wave = threadIdx.x / kWave;
   const int64_t n = hdr->n_out;
-  const int64_t base = blockIdx.x * static_cast<int64_t>(kSortTile);
+  const int64_t base = blockIdx.x * static_cast<int64_t>(kBlock * ITEMS);
 #pragma unroll
   for (int j = 0; j < kPer; ++j)
     s_base[threadIdx.x + j * kBlock] = hist[(threadIdx.x + j * kBlock) * nblocks + blockIdx.x];
-  uint64_t kr[kItems];
-  int32_t vr[kItems];
+  uint64_t kr[ITEMS];
+  int32_t vr[ITEMS];
 #pragma unroll
-  for (int r = 0; r < kItems; ++r) {                 // every round's element in flight
+  for (int r = 0; r < ITEMS; ++r) {                 // every round's element in flight
     const int64_t e = base + r * kBlock + threadIdx.x;
     kr[r] = keys[e < n ? e : 0];
     vr[r] = vals[e < n ? e : 0];
   }
 #pragma unroll
-  for (int r = 0; r < kItems; ++r) {
+  for (int r = 0; r < ITEMS; ++r) {
 #pragma unroll
     for (int w = 0; w < kBlock / kWave; ++w)
 #pragma unroll
@@ -226,7 +231,8 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(
 }  // namespace
 
 size_t radix_sort_scratch_bytes(int64_t n_cap) {
-  const int64_t nblocks = (n_cap + kSortTile - 1) / kSortTile;
+  const int64_t tile = kBlock * sort_items(n_cap);
+  const int64_t nblocks = (n_cap + tile - 1) / tile;
   const int64_t nh = nblocks * kMaxDigits;
   const int64_t np = (nh + kScanChunk - 1) / kScanChunk;
   return static_cast<size_t>(nh + np + 64) * sizeof(uint32_t);
@@ -254,7 +260,8 @@ bool radix_sort_pairs(uint64_t* keys, int32_t* vals, uint64_t* keys_tmp, int32_t
                       hipStream_t stream, int lo_bit) {
   if (n_cap <= 0 || key_bits <= lo_bit) return false;
   const int db = radix_digit_bits(key_bits, lo_bit);
-  const int64_t nblocks = (n_cap + kSortTile - 1) / kSortTile;
+  const int items = sort_items(n_cap);
+  const int64_t nblocks = (n_cap + kBlock * items - 1) / (kBlock * items);
   const int64_t nh = nblocks * (int64_t{1} << db);
   const int64_t np = (nh + kScanChunk - 1) / kScanChunk;
   uint32_t* hist = static_cast<uint32_t*>(scratch);
@@ -266,10 +273,12 @@ bool radix_sort_pairs(uint64_t* keys, int32_t* vals, uint64_t* keys_tmp, int32_t
     const int32_t* vi = flipped ? vals_tmp : vals;
     uint64_t* ko = flipped ? keys : keys_tmp;
     int32_t* vo = flipped ? vals : vals_tmp;
-    if (db == 9)
-      k_rs_hist<9><<<gb, kBlock, 0, stream>>>(ki, hdr, shift, nblocks, hist);
-    else
-      k_rs_hist<8><<<gb, kBlock, 0, stream>>>(ki, hdr, shift, nblocks, hist);
+    auto hk = db == 9 ? (items == kItemsMin ? k_rs_hist<9, kItemsMin> : k_rs_hist<9, kItemsMax>)
+                      : (items == kItemsMin ? k_rs_hist<8, kItemsMin> : k_rs_hist<8, kItemsMax>);
+    auto sk = db == 9
+                  ? (items == kItemsMin ? k_rs_scatter<9, kItemsMin> : k_rs_scatter<9, kItemsMax>)
+                  : (items == kItemsMin ? k_rs_scatter<8, kItemsMin> : k_rs_scatter<8, kItemsMax>);
+    hk<<<gb, kBlock, 0, stream>>>(ki, hdr, shift, nblocks, hist);
     k_scan_reduce<<<static_cast<unsigned>(np), kBlock, 0, stream>>>(hist, nh, part);
     if (np <= kSelfParts) {
       k_scan_apply<true><<<static_cast<unsigned>(np), kBlock, 0, stream>>>(hist, nh, part);
@@ -277,10 +286,7 @@ bool radix_sort_pairs(uint64_t* keys, int32_t* vals, uint64_t* keys_tmp, int32_t
       k_scan_top<<<1, kBlock, 0, stream>>>(part, np);
       k_scan_apply<false><<<static_cast<unsigned>(np), kBlock, 0, stream>>>(hist, nh, part);
     }
-    if (db == 9)
-      k_rs_scatter<9><<<gb, kBlock, 0, stream>>>(ki, vi, ko, vo, hdr, shift, nblocks, hist);
-    else
-      k_rs_scatter<8><<<gb, kBlock, 0, stream>>>(ki, vi, ko, vo, hdr, shift, nblocks, hist);
+    sk<<<gb, kBlock, 0, stream>>>(ki, vi, ko, vo, hdr, shift, nblocks, hist);
     flipped = !flipped;
   }
   return flipped;
