@@ -191,63 +191,26 @@ __global__ __launch_bounds__(256) void k_fwd_vec(
   }
 }
 
-template <typename TOut, int NCB> struct OutStore;
-template <int NCB> struct OutStore<float, NCB> {
-  __device__ static void store(float* p, const float* v) {
-    if constexpr (NCB == 4) {
-      *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-    } else if constexpr (NCB == 2) {
-      *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
-    } else {
-      p[0] = v[0];
-    }
-  }
-};
-template <int NCB> struct OutStore<uint16_t, NCB> {
-  __device__ static void store(uint16_t* p, const float* v) {
-    if constexpr (NCB == 4) {
-      uint2 u;
-      u.x = f32_to_bf16(v[0]) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16);
-      u.y = f32_to_bf16(v[2]) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
-      *reinterpret_cast<uint2*>(p) = u;
-    } else if constexpr (NCB == 2) {
-      *reinterpret_cast<uint32_t*>(p) =
-          f32_to_bf16(v[0]) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16);
-    } else {
-      p[0] = f32_to_bf16(v[0]);
-    }
-  }
-};
-
-// NCB adjacent output elements as fp32 (the residual of the epilogue).
-template <typename TOut, int NCB> struct OutLoad;
-template <int NCB> struct OutLoad<float, NCB> {
-  __device__ static void load(const float* p, float* v) {
-    if constexpr (NCB == 4) {
-      const float4 u = *reinterpret_cast<const float4*>(p);
-      v[0] = u.x; v[1] = u.y; v[2] = u.z; v[3] = u.w;
-    } else if constexpr (NCB == 2) {
-      const float2 u = *reinterpret_cast<const float2*>(p);
-      v[0] = u.x; v[1] = u.y;
-    } else {
-      v[0] = p[0];
-    }
-  }
-};
-template <int NCB> struct OutLoad<uint16_t, NCB> {
-  __device__ static void load(const uint16_t* p, float* v) {
-    if constexpr (NCB == 4) {
-      const uint2 u = *reinterpret_cast<const uint2*>(p);
-      v[0] = __uint_as_float(u.x << 16); v[1] = __uint_as_float(u.x & 0xffff0000u);
-      v[2] = __uint_as_float(u.y << 16); v[3] = __uint_as_float(u.y & 0xffff0000u);
-    } else if constexpr (NCB == 2) {
-      const uint32_t u = *reinterpret_cast<const uint32_t*>(p);
-      v[0] = __uint_as_float(u << 16); v[1] = __uint_as_float(u & 0xffff0000u);
-    } else {
-      v[0] = bf16_to_f32(p[0]);
-    }
-  }
-};
+// Four adjacent output elements: rounded once and stored, or read as fp32 (the
+// residual of the epilogue).
+__device__ __forceinline__ void store4(float* p, const float* v) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void store4(uint16_t* p, const float* v) {
+  uint2 u;
+  u.x = f32_to_bf16(v[0]) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16);
+  u.y = f32_to_bf16(v[2]) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
+  *reinterpret_cast<uint2*>(p) = u;
+}
+__device__ __forceinline__ void load4(const float* p, float* v) {
+  const float4 u = *reinterpret_cast<const float4*>(p);
+  v[0] = u.x; v[1] = u.y; v[2] = u.z; v[3] = u.w;
+}
+__device__ __forceinline__ void load4(const uint16_t* p, float* v) {
+  const uint2 u = *reinterpret_cast<const uint2*>(p);
+  v[0] = __uint_as_float(u.x << 16); v[1] = __uint_as_float(u.x & 0xffff0000u);
+  v[2] = __uint_as_float(u.y << 16); v[3] = __uint_as_float(u.y & 0xffff0000u);
+}
 
 // Few input planes (C_in <= kLowCin, C_out a multiple of kLowCols): one
 // thread per output position and kLowCols output columns, a block of threads
@@ -351,7 +314,7 @@ __global__ __launch_bounds__(256) void k_fwd_lowc(
     }
     if (epi.res) {
       float rv[4];
-      OutLoad<TOut, 4>::load(static_cast<const TOut*>(epi.res) + o + col, rv);
+      load4(static_cast<const TOut*>(epi.res) + o + col, rv);
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] += rv[e];
     }
@@ -359,7 +322,7 @@ __global__ __launch_bounds__(256) void k_fwd_lowc(
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = v[e] < 0.0f ? 0.0f : v[e];
     }
-    OutStore<TOut, 4>::store(y + o + col, v);
+    store4(y + o + col, v);
   }
 }
 
@@ -455,9 +418,7 @@ __device__ __forceinline__ uint32_t map_blocks(int32_t v) {
 }
 
 // 16 bytes of adjacent output elements, rounded once; and read back as fp32.
-__device__ __forceinline__ void store16(float* p, const float* v) {
-  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-}
+__device__ __forceinline__ void store16(float* p, const float* v) { store4(p, v); }
 __device__ __forceinline__ void store16(uint16_t* p, const float* v) {
   uint4 u;
   u.x = f32_to_bf16(v[0]) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16);
@@ -550,7 +511,7 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[RB][NCB], int32_t 
       for (int q = 0; q < NP; ++q)
         if (FULL || n0 + q * PC < C_out) {
           if constexpr (PC == P16) store16(out + q * PC, z + q * PC);
-          else OutStore<TOut, PC>::store(out + q * PC, z + q * PC);
+          else store4(out + q * PC, z + q * PC);
         }
     } else {
 #pragma unroll
