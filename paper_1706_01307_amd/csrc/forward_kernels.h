@@ -963,6 +963,13 @@ bool launch_generic(const Call& c, int C_in) {
   // one-lane-per-column kernel finishes first (measured: 460 rows of 16
   // columns 6.1 us against 7.7 us; 29759 rows of 32 columns 16.4 us against
   // 12.7 us).
+  // So it does before the slab kernel wherever few columns leave the slabs
+  // and column tiles mostly padding: its time goes with rows x K x C_out x
+  // (C_in + 2), the slab kernel's with rows x K (400,000 surface rows 3^3:
+  // 1 -> 8 fp32 68 against 200 us, 1 -> 24 192 / 202, 1 -> 33 266 / 224, 4 -> 5
+  // 161 / 202; bf16 1 -> 8 102 / 117, 1 -> 24 277 / 120), and on layers small
+  // enough to be bound by latency (3,200 rows 3x3, 4 -> 100: 8 against 16 us;
+  // 29,760 rows 1 -> 33: 14 / 16, 1 -> 100: 35 / 20).
   constexpr int64_t kLowMinRows = 2048;
   const uint64_t xb = static_cast<uint64_t>(c.v.n_src) * C_in * sizeof(TIn);
   const uint64_t wb = static_cast<uint64_t>(c.v.K) * C_in * c.C_out * sizeof(TIn);
@@ -974,7 +981,11 @@ bool launch_generic(const Call& c, int C_in) {
     return true;
   }
   const bool wfits = (c.v.seg ? 1024 * wb : wb) < kBufOOB;
-  if ((c.v.seg || !few || c.v.n_cap >= kLowMinRows) && fits && wfits && !force_vector_path()) {
+  const int64_t cols = static_cast<int64_t>(c.C_out) * (C_in + 2);
+  const bool narrow = (C_in <= 16 && cols < (sizeof(TIn) == 4 ? 80 : 48)) ||
+                      (few && c.v.n_cap * c.v.K * cols < 27000000);
+  if ((c.v.seg || !(narrow || (few && c.v.n_cap < kLowMinRows))) && fits && wfits &&
+      !force_vector_path()) {
     Call cc = c;
     cc.x_bytes = static_cast<uint32_t>(xb);
     slab_entry<TIn, TOut>()(cc, WT, C_in, static_cast<uint32_t>(c.v.seg ? 0x7fffffffu : wb));
