@@ -176,8 +176,12 @@ int spconv_rulebook_out_coords(spconv_rulebook rb, const int32_t** coords);
  *   y       device [n_out][C_out], fully overwritten
  * Accumulation is fp32, in ascending offset order, without atomics, so
  * repeated calls give bit-identical results; the result is rounded once to
- * out_dt (round to nearest even).  Nothing is allocated; the call is
- * asynchronous on `stream`.  Errors: EINVAL (kind, dtype, C < 1, NULL). */
+ * out_dt (round to nearest even).  Infinities and NaN in x or w reach the
+ * rows they have a pair with; for C_in of 32, 64, 96, 128 (bf16) or 16, 32,
+ * 64, 96, 128 (fp32) with C_out a multiple of 16, a non-finite W^i can also
+ * put NaN into rows that have no pair at offset i.  Nothing is allocated; the
+ * call is asynchronous on `stream`.  Errors: EINVAL (kind, dtype, C < 1,
+ * NULL). */
 int spconv_vsc_forward(spconv_rulebook rb, int in_dt, const void* x,
                        const void* w, const float* bias, int out_dt, void* y,
                        int C_in, int C_out, void* stream);

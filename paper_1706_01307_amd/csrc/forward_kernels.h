@@ -127,6 +127,19 @@ __device__ __forceinline__ int64_t w_index(int i, int K, int c, int n, int C_in,
   return (static_cast<int64_t>(iw) * C_out + n) * C_in + c;
 }
 
+// Epilogue and store of one output element (column col, element o of y).
+template <typename TOut>
+__device__ __forceinline__ void store_elem(float acc, int64_t o, int col, const float* bias,
+                                           const Epilogue& epi, TOut* y) {
+  if (epi.scale)
+    acc = fmaf(acc, epi.scale[col], bias ? bias[col] : 0.0f);
+  else if (bias)
+    acc += bias[col];
+  if (epi.res) acc += ElemIO<TOut>::load(static_cast<const TOut*>(epi.res), o);
+  if (epi.relu) acc = acc < 0.0f ? 0.0f : acc;
+  ElemIO<TOut>::store(y, o, acc);
+}
+
 // Positions run over the capacity n_cap (known on the host) so that the
 // loads of the gather map do not wait for the device-side row count; a
 // position at or past the count contributes nothing and stores nothing.
@@ -179,15 +192,7 @@ __global__ __launch_bounds__(256) void k_fwd_vec(
         }
       }
     }
-    if (!live) continue;
-    const int64_t o = static_cast<int64_t>(perm[p]) * C_out + col;
-    if (epi.scale)
-      acc = fmaf(acc, epi.scale[col], bias ? bias[col] : 0.0f);
-    else if (bias)
-      acc += bias[col];
-    if (epi.res) acc += ElemIO<TOut>::load(static_cast<const TOut*>(epi.res), o);
-    if (epi.relu) acc = acc < 0.0f ? 0.0f : acc;
-    ElemIO<TOut>::store(y, o, acc);
+    if (live) store_elem(acc, static_cast<int64_t>(perm[p]) * C_out + col, col, bias, epi, y);
   }
 }
 

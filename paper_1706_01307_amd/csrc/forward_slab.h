@@ -129,6 +129,45 @@ struct WStage {
   }
 };
 
+// Whether any of the lane's sums is an infinity or NaN.
+template <int RB, int NCB>
+__device__ __forceinline__ bool nonfinite(const f32x4 (&acc)[RB][NCB]) {
+  float z = 0.0f;
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) z = fmaf(acc[b][cb][v], 0.0f, z);
+  return z != z;
+}
+
+// A row that lacks offset i enters the products of its 16-row block as zeros,
+// and 0 times a non-finite W^i is NaN, where the row has no term at all.  So a
+// wave that ends with a non-finite sum adds its tile up again over the rows'
+// own pairs, one element per lane at a time as k_fwd_vec does.
+template <typename TIn, typename TOut, int WT>
+__device__ __forceinline__ void sum_over_pairs(
+    const int32_t* gmap, const int32_t* perm, int64_t gstride, int64_t n_rows, int K, int wseg,
+    const TIn* x, const TIn* w, const float* bias, TOut* y, int C_in, int C_out, int64_t row0,
+    int rows, int col0, int cols, const Epilogue& epi) {
+  for (int e = __lane_id(); e < rows * cols; e += kWave) {
+    const int64_t p = row0 + e / cols;
+    const int col = col0 + e % cols;
+    if (p >= n_rows || col >= C_out || perm[p] < 0) continue;
+    float acc = 0.0f;
+    for (int i = 0; i < K; ++i) {
+      const int64_t g = static_cast<int64_t>(gmap[i * gstride + p]) - 1;
+      if (g < 0) continue;
+      for (int c = 0; c < C_in; ++c)
+        acc = fmaf(ElemIO<TIn>::load(x, g * C_in + c),
+                   ElemIO<TIn>::load(w, w_index<WT>(wseg >= 0 ? wseg : i, K, c, col, C_in, C_out)),
+                   acc);
+    }
+    store_elem(acc, static_cast<int64_t>(perm[p]) * C_out + col, col, bias, epi, y);
+  }
+}
+
 template <typename TIn, typename TOut, int NCH, int NCB, int RB, int WT, bool AX, bool AW>
 __global__ __launch_bounds__(256, 2) void k_fwd_slab(
     const int32_t* __restrict__ gmap, const int32_t* __restrict__ perm, int64_t gstride,
@@ -162,6 +201,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
 
   const int col0 = blockIdx.y * COLS;
   const int wave = threadIdx.x / kWave;
+  const int uwave = __builtin_amdgcn_readfirstlane(wave);   // (a scalar: no register kept)
   const int lane = threadIdx.x % kWave;
   const int lr = lane % 16, lg = lane / 16;
   const int64_t row0 = tile * TILE_ROWS + wave * WAVE_ROWS;
@@ -287,6 +327,12 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
     step(e + 2, a2, p2, a1, p1, g2, g1, w0, w1);
   }
 
+  if (__any(nonfinite(acc))) {
+    sum_over_pairs<TIn, TOut, WT>(gmap, perm, gstride, n_rows, K, wseg, x, w, bias, y, C_in, C_out,
+                                  tile * TILE_ROWS + uwave * WAVE_ROWS, WAVE_ROWS, col0, COLS,
+                                  epi);
+    return;
+  }
   store_tile<TOut, RB, NCB, false>(acc, map_row < n_rows ? perm[map_row] : -1, bias, y, C_out,
                                    col0, lg, epi);
 }

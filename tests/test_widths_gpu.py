@@ -126,6 +126,48 @@ def test_reversed_on_the_vector_path(monkeypatch, dtype):
     check_features(_to_np(dx), dxo, ad, RTOL_F32 if dtype == "f32" else RTOL_BF16, "dx")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("op,layer,ci,co", [("vsc", "", 24, 40), ("vsc", "", 33, 130),
+                                            ("vsc", "", 200, 72), ("sc", "map", 136, 24),
+                                            ("dc", "map", 40, 24), ("dc", "direct", 40, 24)])
+def test_nonfinite_weights_stay_with_their_pairs(op, layer, ci, co, dtype):
+    """An infinity and a NaN in W^i reach the rows that have a neighbour at offset i and no other,
+    as the sum over the pairs says: forward, input gradient and the in-place fused forward."""
+    coords, size, f, s = _layer(op, layer)
+    kind = spc.VSC if op == "vsc" else spc.SC
+    rb = spc.build_rulebook(kind, _t(coords), size, f, s, transpose=op != "vsc")
+    ref = oracle.Rulebook(kind, coords, size, f, s)
+    rin, rout = (ref.n_out, ref.n_in) if op == "dc" else (ref.n_in, ref.n_out)
+    x, dy = _feats(rin, ci, dtype, 1), _feats(rout, co, dtype, 2)
+    w = _feats(ref.K * ci, co, dtype, 3, std=1.0 / np.sqrt(ref.K * ci)).reshape(ref.K, ci, co)
+    inf, nan = (0x7f80, 0x7fc0) if dtype == "bf16" else (np.inf, np.nan)
+    w[1, 3, 2], w[ref.K - 2, ci - 1, co - 1] = inf, nan
+    b = inputs.normal_f32((co,), std=0.1, seed=4)
+    rtol = RTOL_F32 if dtype == "f32" else RTOL_BF16
+
+    def check(got, want, bound, what):
+        got = _to_np(got).astype(np.float64)
+        ok = np.isfinite(want)
+        assert not ok.all() and ok.any(), what
+        np.testing.assert_array_equal(got[~ok], want[~ok], err_msg=what)     # NaN where NaN
+        assert (np.abs(got - want)[ok] <= rtol * bound[ok]).all(), what
+
+    with np.errstate(invalid="ignore"):
+        fwd = {"vsc": spc.vsc_forward, "sc": spc.sc_forward, "dc": spc.dc_forward}[op]
+        yo, ab = (ref.dc_forward if op == "dc" else ref.forward)(x, w, b, in_dt=_odt(dtype))
+        check(fwd(rb, _dev(x, dtype), _dev(w, dtype), _t(b)), yo, ab, "y")
+        dxo, ad = ref.backward_data(OP[op][1], dy, w, _odt(dtype))
+        check(spc.backward_data(rb, OP[op][0], _dev(dy, dtype), _dev(w, dtype)), dxo, ad, "dx")
+        if op != "dc":
+            scale, res = inputs.normal_f32((co,), seed=5), _feats(rout, co, dtype, 6)
+            y64, a64 = ref.forward(x, w, None, in_dt=_odt(dtype))
+            zo, bound = oracle.fused_epilogue(y64, a64, scale, b, res, True, _odt(dtype))
+            z = _dev(res, dtype)
+            spc.forward_fused(rb, _dev(x, dtype), _dev(w, dtype), scale=_t(scale), shift=_t(b),
+                              residual=z, relu=True, out=z)
+            check(z, zo, bound, "fused")
+
+
 @pytest.mark.parametrize("size,f,s", [([3, 101, 77, 95], [1, 3, 3, 3], [1, 2, 2, 2]),
                                       ([2, 130, 100, 90], [1, 2, 2, 2], [1, 2, 2, 2]),
                                       ([1, 300, 1000], [1, 1, 2], [1, 1, 1]),
