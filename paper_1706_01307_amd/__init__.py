@@ -75,7 +75,7 @@ def _i32_tuple(v):
 def _i32_array(v, D, name):
     if type(v) in (list, tuple) and len(v) == D and all(type(e) is int for e in v):
         return _i32_tuple(tuple(v))
-    a = np.ascontiguousarray(np.asarray(v, dtype=np.int32).reshape(-1))
+    a = np.asarray(v, dtype=np.int32).reshape(-1).copy()     # (v may be read-only)
     if a.size != D:
         raise ValueError(f"{name} needs {D} entries, got {a.size}")
     return np.ctypeslib.as_ctypes(a)

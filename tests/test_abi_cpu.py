@@ -37,6 +37,22 @@ def test_status_strings():
     assert lib.spconv_status_string(-99).decode() == "unknown status"
 
 
+def test_extents_from_any_sequence():
+    """Extents, filters and strides as lists, tuples or arrays: read-only, strided, of another
+    type, empty."""
+    import paper_1706_01307_amd as spc
+    frozen = np.array([2, 5, 7], np.int32)
+    frozen.setflags(write=False)
+    want = [2, 5, 7]
+    for v in (want, tuple(want), frozen, np.frombuffer(frozen.tobytes(), np.int32),
+              np.array([2, 0, 5, 0, 7], np.int32)[::2], np.array(want, np.float64), [2, True + 4, 7.0],
+              np.broadcast_to(frozen[:, None], (3, 2))[:, 0]):
+        assert list(spc._i32_array(v, 3, "f")) == want
+    assert list(frozen) == want and list(spc._i32_array((), 0, "f")) == []
+    with pytest.raises(ValueError):
+        spc._i32_array(frozen, 4, "f")
+
+
 def _build_status(kind, D, N, size, f, s):
     lib = _lib.load()
     size = np.asarray(size, np.int32)
