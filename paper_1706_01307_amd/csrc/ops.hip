@@ -1014,8 +1014,9 @@ size_t backward_weight_workspace(spconv_rulebook rb, int C_in, int C_out, int op
   const int64_t rows = op == SPCONV_OP_DC ? rb->n_in : rb->n_cap;
   const int64_t nrc = (rows + kRowChunk - 1) / kRowChunk;
   const int64_t nchunk = dw_plan(rb, C_in, C_out).nchunk;
+  const int64_t nb = nrc > nchunk ? nrc : nchunk;      // rows of the bias partials
   return static_cast<size_t>(rb->K * nchunk) * C_in * C_out * 4 +
-         static_cast<size_t>(nrc > nchunk ? nrc : nchunk + 1) * C_out * 4 + 256;
+         static_cast<size_t>(nb > 0 ? nb : 1) * C_out * 4 + 256;
 }
 
 int backward_weight(spconv_rulebook rb, int op, int dt, const void* x, const void* dy, float* dw,

@@ -119,3 +119,20 @@ def test_noalloc_rejects_requests_beyond_the_scratch_array():
                                             None)
     assert st == _lib.ESCRATCH
     assert "scratch" in lib.spconv_status_string(st).decode()
+
+
+def test_noalloc_takes_requests_up_to_the_scratch_array():
+    """One chunk of partials, one row of bias partials and 256 bytes: 32,512 bytes less than the
+    array holds, and less than another row of bias partials."""
+    C_in, C_out, N = 4094, 8192, 300
+    c = inputs.surfaces(1, 32, 4, 14, seed=45, target=N)[:N]
+    rb = spc.build_rulebook(spc.VSC, _t(c), [1, 32, 32, 32], [1, 1, 1, 1])
+    x = torch.randn(N, C_in, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    g = torch.randn(N, C_out, device="cuda", generator=torch.Generator("cuda").manual_seed(2))
+    (w1, b1), (w2, b2) = _grads_both_ways(rb, spc.OP_VSC, x, g, C_in, C_out, _lib.F32)
+    np.testing.assert_array_equal(w1, w2)
+    np.testing.assert_array_equal(b1, b2)
+    check_features(w2[0], (x.double().T @ g.double()).cpu().numpy(),
+                   (x.double().abs().T @ g.double().abs()).cpu().numpy(), RTOL_GRAD, "dw")
+    check_features(b2, g.double().sum(0).cpu().numpy(), g.double().abs().sum(0).cpu().numpy(),
+                   RTOL_GRAD, "db")
