@@ -952,6 +952,10 @@ void launch_lowc(const Call& c, int C_in, uint32_t x_bytes) {
       C_in, c.C_out, x_bytes, c.epi);
 }
 
+// Columns of a launch whose column tiles (64 at least where there are this
+// many) are the grid's second dimension.
+constexpr int kMaxTileCols = 65535 * 64;
+
 template <typename TIn, typename TOut>
 constexpr auto slab_entry() {
   if constexpr (sizeof(TIn) == 4) return sizeof(TOut) == 4 ? forward_slab_ff : forward_slab_fb;
@@ -985,7 +989,7 @@ bool launch_generic(const Call& c, int C_in) {
     launch_lowc<TIn, TOut, WT>(c, C_in, static_cast<uint32_t>(xb));
     return true;
   }
-  const bool wfits = (c.v.seg ? 1024 * wb : wb) < kBufOOB;
+  const bool wfits = (c.v.seg ? 1024 * wb : wb) < kBufOOB && c.C_out <= kMaxTileCols;
   const int64_t cols = static_cast<int64_t>(c.C_out) * (C_in + 2);
   const bool narrow = (C_in <= 16 && cols < (sizeof(TIn) == 4 ? 80 : 48)) ||
                       (few && c.v.n_cap * c.v.K * cols < 27000000);

@@ -518,7 +518,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_up(
 }
 
 // The same on the vector ALU, one lane per (position, offset, column): for
-// operands past the buffer range.
+// operands past the buffer range and columns past the grid's.
 template <typename TIn, typename TOut, int WT>
 __global__ __launch_bounds__(256) void k_fwd_up_vec(
     const int32_t* __restrict__ gmap, const int32_t* __restrict__ perm, int64_t gstride,
@@ -651,7 +651,7 @@ void launch_up(const Call& c, int C_in) {
   const uint64_t xb = static_cast<uint64_t>(c.v.n_src) * C_in * sizeof(TIn);
   const uint64_t wb = static_cast<uint64_t>(c.v.K) * C_in * c.C_out * sizeof(TIn);
   if (force_vector_path() || xb >= kBufOOB || wb >= kBufOOB ||
-      static_cast<uint64_t>(c.v.gstride) * 4 >= kBufOOB) {
+      static_cast<uint64_t>(c.v.gstride) * 4 >= kBufOOB || c.C_out > kMaxTileCols) {
     int64_t blocks = (c.v.n_cap * c.v.K * c.C_out + 255) / 256;
     if (blocks > 65536) blocks = 65536;
     k_fwd_up_vec<TIn, TOut, WT><<<static_cast<unsigned>(blocks), 256, 0, c.stream>>>(

@@ -168,6 +168,21 @@ def test_nonfinite_weights_stay_with_their_pairs(op, layer, ci, co, dtype):
             check(z, zo, bound, "fused")
 
 
+@pytest.mark.parametrize("op", ["vsc", "dc"])
+def test_more_columns_than_a_grid_has_tiles(op):
+    """4,194,308 output planes: one past 65535 tiles of 64 columns."""
+    co = 65535 * 64 + 68
+    c = np.array([[0, 1, 2], [0, 1, 3], [0, 5, 5]], np.int32)
+    rb = spc.build_rulebook(spc.VSC if op == "vsc" else spc.SC, _t(c), [1, 8, 8], [1, 1, 1],
+                            transpose=op == "dc")
+    g = torch.Generator("cuda").manual_seed(1)
+    x = torch.randn(3, 5, device="cuda", generator=g)
+    w = torch.randn(1, 5, co, device="cuda", generator=g)
+    y = (spc.vsc_forward if op == "vsc" else spc.dc_forward)(rb, x, w)
+    want, bound = x.double() @ w[0].double(), x.double().abs() @ w[0].double().abs()
+    assert ((y.double() - want).abs() <= RTOL_F32 * bound).all()
+
+
 @pytest.mark.parametrize("size,f,s", [([3, 101, 77, 95], [1, 3, 3, 3], [1, 2, 2, 2]),
                                       ([2, 130, 100, 90], [1, 2, 2, 2], [1, 2, 2, 2]),
                                       ([1, 300, 1000], [1, 1, 2], [1, 1, 1]),
