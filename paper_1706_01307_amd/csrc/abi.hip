@@ -505,14 +505,10 @@ int spconv_dc_forward(spconv_rulebook rb, int in_dt, const void* x, const void* 
       (reinterpret_cast<uintptr_t>(bias) & 3))
     return SPCONV_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (rb->t_direct)
-    return used_on(rb, stream, forward_up(rb, 0, in_dt, x, w, bias, out_dt, y, C_in, C_out, st));
-  if (rb->t_single && rb->n_in > 0) {
-    const int r = transpose_single(rb, 0, in_dt, x, w, bias, out_dt, y, C_in, C_out, st);
-    if (r != kNotSingle) return used_on(rb, stream, r);
-  }
-  return used_on(rb, stream, forward_view(transpose_view(rb), 0, in_dt, x, w, bias, out_dt, y,
-                                          C_in, C_out, st));
+  FwdView v;
+  const int vs = reversed_view(rb, &v);
+  if (vs != SPCONV_OK) return vs;
+  return used_on(rb, stream, forward_view(v, 0, in_dt, x, w, bias, out_dt, y, C_in, C_out, st));
 }
 
 // The book, view and weight mode an input gradient runs on.
@@ -526,8 +522,7 @@ static int data_grad_view(spconv_rulebook rb, int op, FwdView* v, int* wmode) {
       return SPCONV_OK;
     case SPCONV_OP_SC:
       if (rb->kind != SPCONV_SC || !(rb->t_gmap || rb->t_direct)) return SPCONV_EINVAL;
-      if (!rb->t_direct) *v = transpose_view(rb);       // SC pairs reversed
-      *wmode = 2;
+      *wmode = 2;                    // SC pairs reversed (reversed_view, after the checks)
       return SPCONV_OK;
     case SPCONV_OP_DC:
       if (rb->kind != SPCONV_SC) return SPCONV_EINVAL;
@@ -553,12 +548,9 @@ int spconv_backward_data(spconv_rulebook rb, int op, int dt, const void* dy, con
   if (misaligned(dy) || misaligned(w) || misaligned(dx)) return SPCONV_EINVAL;
   // the kernels' input channels are the layer's output channels
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (op == SPCONV_OP_SC && rb->t_direct)
-    return used_on(rb, stream, forward_up(rb, wmode, dt, dy, w, nullptr, out_dt, dx, C_out, C_in,
-                                          st));
-  if (op == SPCONV_OP_SC && rb->t_single && rb->n_in > 0) {
-    const int r = transpose_single(rb, wmode, dt, dy, w, nullptr, out_dt, dx, C_out, C_in, st);
-    if (r != kNotSingle) return used_on(rb, stream, r);
+  if (op == SPCONV_OP_SC) {
+    const int rs = reversed_view(rb, &v);
+    if (rs != SPCONV_OK) return rs;
   }
   return used_on(rb, stream, forward_view(v, wmode, dt, dy, w, nullptr, out_dt, dx, C_out, C_in,
                                           st));

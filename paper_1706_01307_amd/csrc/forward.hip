@@ -16,7 +16,6 @@ FwdView view_of(spconv_rulebook rb) {
   v.n_cap = rb->n_cap;
   v.K = rb->K;
   v.n_src = rb->n_in;
-  v.seg = nullptr;
   return v;
 }
 
@@ -26,26 +25,12 @@ int forward_view(const FwdView& v, int wmode, int in_dt, const void* x, const vo
   if (v.n_cap == 0) return SPCONV_OK;
   FwdCall c{v, x, 0u, w, bias, y, C_out, stream, epi};
   if (!x) c.v.n_src = 0;   // no source rows (the map then names none): every gather reads 0
-  bool done = false;
   switch (wmode) {
-    case 0: done = forward_run_w0(c, in_dt, out_dt, C_in); break;
-    case 1: done = forward_run_w1(c, in_dt, out_dt, C_in); break;
-    case 2: done = forward_run_w2(c, in_dt, out_dt, C_in); break;
+    case 0: forward_run_w0(c, in_dt, out_dt, C_in); break;
+    case 1: forward_run_w1(c, in_dt, out_dt, C_in); break;
+    case 2: forward_run_w2(c, in_dt, out_dt, C_in); break;
     default: return SPCONV_EINVAL;
   }
-  if (!done) return kNotSingle;           // a segmented view with no matrix-core kernel
-  return hipGetLastError() == hipSuccess ? SPCONV_OK : SPCONV_EHIP;
-}
-
-int forward_up(spconv_rulebook rb, int wmode, int in_dt, const void* x, const void* w,
-               const float* bias, int out_dt, void* y, int C_in, int C_out, hipStream_t stream) {
-  FwdCall c{view_of(rb), x, 0u, w, bias, y, C_out, stream, Epilogue{}};
-  if (c.v.n_cap == 0) return SPCONV_OK;
-  c.v.n_src = x ? rb->n_cap : 0;          // the source rows are the book's output rows
-  if (in_dt == SPCONV_F32)
-    (out_dt == SPCONV_F32 ? forward_up_ff : forward_up_fb)(c, wmode, C_in);
-  else
-    (out_dt == SPCONV_F32 ? forward_up_bf : forward_up_bb)(c, wmode, C_in);
   return hipGetLastError() == hipSuccess ? SPCONV_OK : SPCONV_EHIP;
 }
 

@@ -196,6 +196,32 @@ __global__ __launch_bounds__(256) void k_fwd_vec(
   }
 }
 
+// A pair view on the vector ALU, one lane per (pair, column).
+template <typename TIn, typename TOut, int WT>
+__global__ __launch_bounds__(256) void k_pairs_vec(
+    const int32_t* __restrict__ pairs, const int64_t* __restrict__ pair_off, int K,
+    const TIn* __restrict__ x, const TIn* __restrict__ w, const float* __restrict__ bias,
+    TOut* __restrict__ y, int C_in, int C_out) {
+  const int64_t total = pair_off[K] * C_out;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  for (int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; t < total;
+       t += stride) {
+    const int64_t e = t / C_out;
+    const int n = static_cast<int>(t % C_out);
+    int i = 0, hi = K;                             // pair_off[i] <= e < pair_off[hi]
+    while (hi - i > 1) {
+      const int mid = (i + hi) / 2;
+      if (pair_off[mid] <= e) i = mid; else hi = mid;
+    }
+    const int64_t xb = static_cast<int64_t>(pairs[2 * e + 1]) * C_in;
+    float acc = 0.0f;
+    for (int c = 0; c < C_in; ++c)
+      acc = fmaf(ElemIO<TIn>::load(x, xb + c),
+                 ElemIO<TIn>::load(w, w_index<WT>(i, K, c, n, C_in, C_out)), acc);
+    store_elem(acc, static_cast<int64_t>(pairs[2 * e]) * C_out + n, n, bias, Epilogue{}, y);
+  }
+}
+
 // Four adjacent output elements: rounded once and stored, or read as fp32 (the
 // residual of the epilogue).
 __device__ __forceinline__ void store4(float* p, const float* v) {
@@ -526,6 +552,76 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[RB][NCB], int32_t 
   }
 }
 
+// Pair views: the tiles of offset i are runs of ROWS of its pairs.  They sit in
+// the slots from pair_off[i] / ROWS + i on (both rounded down), which are at
+// least as many as the offset's tiles, so no list or sum of tile counts is
+// needed to find a slot's offset: the last one whose first slot is not past
+// it.  At most one slot per offset holds no pairs; the XCDs get contiguous
+// ranges of slots.
+struct PairTile {
+  int i, count;                // offset; pairs (fewer than ROWS at the end of R_i)
+  int64_t first;               // first pair
+};
+template <int ROWS>
+__device__ __forceinline__ bool pair_tile(const int64_t* __restrict__ pair_off, int K,
+                                          int64_t nslots, PairTile* t) {
+  const int64_t per = (nslots + 7) / 8, q8 = blockIdx.x / 8;
+  const int64_t slot = static_cast<int64_t>(blockIdx.x % 8) * per + q8;
+  if (q8 >= per || slot >= nslots) return false;
+  // the wave looks at every J-th offset, then (J > 1) at those in between
+  static_assert(kMaxK <= kWave * kWave, "two looks");
+  const int lane = __lane_id(), J = (K + kWave - 1) / kWave;
+  auto last = [&](int i, bool in) -> int {         // the last lane whose offset starts in time
+    const int64_t off = pair_off[in ? i : K];
+    return 63 - __builtin_clzll(__ballot(in && off / ROWS + i <= slot) | 1ull);
+  };
+  int i = J * last(J * lane, J * lane < K);
+  if (J > 1) i += last(i + lane, lane < J && i + lane < K);
+  const int64_t lo = pair_off[i], k = pair_off[i + 1] - lo;
+  const int64_t e = (slot - lo / ROWS - i) * ROWS;
+  if (e >= k) return false;
+  t->i = i;
+  t->first = lo + e;
+  t->count = static_cast<int>(k - e < ROWS ? k - e : ROWS);
+  return true;
+}
+// The input row (which 0) or output row (1) of pair e of the tile, -1 past its
+// end; a buffer load without a branch, as the map's.
+__device__ __forceinline__ int32_t pair_row(const int32_t* pairs, const PairTile& t, int e,
+                                            int which) {
+  const __amdgpu_buffer_rsrc_t r =
+      buf_rsrc(pairs + 2 * t.first, static_cast<uint32_t>(t.count) * 8u);
+  const int32_t v = static_cast<int32_t>(
+      __builtin_amdgcn_raw_buffer_load_b32(r, static_cast<uint32_t>(8 * e + 4 * which), 0, 0));
+  return e < t.count ? v : -1;
+}
+// The arguments of a kernel on a view: a pair view's pairs, offsets and pair_K
+// stand in for the map, the schedule and K.
+struct ViewArgs {
+  const int32_t* gmap;
+  const int32_t* perm;
+  int K;
+};
+inline ViewArgs view_args(const FwdView& v) {
+  if (v.pair_off) return {v.pairs, reinterpret_cast<const int32_t*>(v.pair_off), v.pair_K};
+  return {v.gmap, v.perm, static_cast<int>(v.K)};
+}
+// Tiles (slots, for pair views) of a launch on a view.
+inline int64_t view_tiles(const FwdView& v, int rows) {
+  return v.pair_off ? v.n_cap / rows + v.pair_K : (v.n_cap + rows - 1) / rows;
+}
+
+// -1 as a value the compiler does not know.  The offset whose W is staged is
+// chosen against it at every step: left to itself the compiler carries a 64-bit
+// address per staged piece through the offset loop (128 -> 128 bf16 with RB = 1:
+// 173 registers instead of 153, two workgroups per compute unit instead of
+// three).
+__device__ __forceinline__ int unknown_minus_one() {
+  int v;
+  asm("s_mov_b32 %0, -1" : "=s"(v));
+  return v;
+}
+
 // Tile of the output handled by one workgroup: 4 waves x RB blocks of 16 rows,
 // NCB blocks of 16 columns (the whole workgroup shares one column chunk).
 //
@@ -551,17 +647,19 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[RB][NCB], int32_t 
 template <typename TIn, int NCH, int NCB, int RB, int KT>
 constexpr bool kNear = sizeof(TIn) == 2 && NCH == 2 && NCB == 4 && RB == 4 && KT == 27;
 template <typename TIn, int NCH, int NCB, int RB, typename TOut, int KT, bool SKIP = false,
-          int WT = 0, bool LSKIP = false>
+          int WT = 0, bool LSKIP = false, bool PAIRS = false>
 __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k_fwd_mfma(
     const int32_t* __restrict__ gmap, const int32_t* __restrict__ perm, int64_t gstride,
     const DeviceHeader* __restrict__ hdr, int K_arg,
     const TIn* __restrict__ x, uint32_t x_bytes, const TIn* __restrict__ w,
     const float* __restrict__ bias, TOut* __restrict__ y, int C_out, int64_t ntiles,
-    const int32_t* __restrict__ seg, Epilogue epi) {
+    Epilogue epi) {
   // KT > 0: the offset count is a compile-time constant and the offset loop
   // is unrolled completely (no loop-carried register hazards).
-  // seg != NULL: a segmented single-offset view; this tile's weights are
-  // W^seg[chunk] (tiles never straddle a chunk of kSegRows positions).
+  // PAIRS (KT = 1): a pair view, from which the tile's rows and its W^i come;
+  // its pairs, their offsets and its K are in the map's, the schedule's and K's
+  // arguments (longer argument lists cost every launch: 16 bytes 0.2 us).
+  static_assert(!PAIRS || KT == 1, "a pair view has one offset per tile");
   const int K = KT > 0 ? KT : K_arg;
   constexpr int KC = MT<TIn>::KC;
   constexpr int CIN = NCH * KC;
@@ -585,16 +683,22 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
   // grid is sized for a bound on the rows (an SC output count is known only
   // on the device), so the ranges split the device-side tile count, not the
   // grid: otherwise a loose bound would leave whole XCDs without work.
-  const int64_t n_rows = hdr->n_out;
-  const int64_t nt_real = (n_rows + TILE_ROWS - 1) / TILE_ROWS;
-  const int64_t nt = nt_real < ntiles ? nt_real : ntiles;
-  const int64_t per = (nt + 7) / 8;
-  const int64_t q = blockIdx.x / 8;
-  if (q >= per) return;
-  const int64_t tile = static_cast<int64_t>(blockIdx.x % 8) * per + q;
-  if (tile >= nt) return;
-  static_assert(kSegRows % TILE_ROWS == 0, "tiles inside one segment chunk");
-  const int wseg = seg ? seg[tile * TILE_ROWS / kSegRows] : -1;
+  PairTile pt{0, 0, 0};
+  int64_t n_rows = TILE_ROWS, tile = 0;
+  if constexpr (PAIRS) {
+    if (!pair_tile<TILE_ROWS>(reinterpret_cast<const int64_t*>(perm), K_arg, ntiles, &pt)) return;
+  } else {
+    n_rows = hdr->n_out;
+    const int64_t nt_real = (n_rows + TILE_ROWS - 1) / TILE_ROWS;
+    const int64_t nt = nt_real < ntiles ? nt_real : ntiles;
+    const int64_t per = (nt + 7) / 8;
+    const int64_t q = blockIdx.x / 8;
+    if (q >= per) return;
+    tile = static_cast<int64_t>(blockIdx.x % 8) * per + q;
+    if (tile >= nt) return;
+  }
+
+  const int fixed = PAIRS ? pt.i : unknown_minus_one();   // the tile's only W^i, or -1
 
   const int col0 = blockIdx.y * COLS;
   const int wave = threadIdx.x / kWave;
@@ -627,14 +731,14 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
         const int t0 = threadIdx.x + q * 256;
         const int t = (NTASK % 256 == 0 || t0 < NTASK) ? t0 : 0;
         const int kt = t / NGRP, nt = t % NGRP;
-        const int iv = wseg >= 0 ? wseg : i;
+        const int iv = fixed >= 0 ? fixed : i;
         const TIn* src = w + (static_cast<int64_t>(iv) * CIN + kt * KPT) * C_out + col0 + nt * NPT;
 #pragma unroll
         for (int r = 0; r < KPT; ++r)
           wr[q * KPT + r] = *reinterpret_cast<const u32x4*>(src + static_cast<int64_t>(r) * C_out);
       }
     } else {
-      const int iw = wseg >= 0 ? wseg : (WT == 1 ? K - 1 - i : i);
+      const int iw = fixed >= 0 ? fixed : (WT == 1 ? K - 1 - i : i);
 #pragma unroll
       for (int q = 0; q < TPT_T; ++q) {
         const int t0 = threadIdx.x + q * 256;
@@ -697,6 +801,10 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
   const int64_t map_row = row0 + map_lane<RB>(lane);
   const uint32_t map_off = map_row < n_rows ? static_cast<uint32_t>(map_row) * 4u : kOOB;
   auto g_load = [&](int i, GRegs& g) {
+    if constexpr (PAIRS) {
+      g = i < K ? pair_row(gmap, pt, static_cast<int>(map_row), 1) : -1;
+      return;
+    }
     const int ic = i < K ? i : 0;
     const __amdgpu_buffer_rsrc_t gr = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int32_t*>(gmap + static_cast<int64_t>(ic) * gstride), 0,
@@ -828,9 +936,10 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
     }
   }
 
-  // ---- epilogue (a perm entry of -1: padding of a segmented view)
-  store_tile<TOut, RB, NCB, true>(acc, map_row < n_rows ? perm[map_row] : -1, bias, y, C_out,
-                                  col0, lg, epi);
+  int32_t row = -1;
+  if constexpr (PAIRS) row = pair_row(gmap, pt, static_cast<int>(map_row), 0);
+  else if (map_row < n_rows) row = perm[map_row];
+  store_tile<TOut, RB, NCB, true>(acc, row, bias, y, C_out, col0, lg, epi);
 }
 
 // ---------------------------------------------------------------------------
@@ -852,14 +961,14 @@ constexpr int64_t kSmallLayerTiles = 512;
 template <typename TIn, int NCH, int NCB, typename TOut, int WT, int RB, bool SMALL = false>
 void launch_mfma_rb(const Call& c) {
   constexpr int kTileRows = 4 * RB * 16;
-  const int64_t ntiles = (c.v.n_cap + kTileRows - 1) / kTileRows;
+  const int64_t ntiles = view_tiles(c.v, kTileRows);
   const int64_t per = (ntiles + 7) / 8;
   dim3 grid(static_cast<unsigned>(8 * per), static_cast<unsigned>(c.C_out / (NCB * 16)));
   // Whole 16-row blocks that lack an offset skip their products.  3^3
   // filters run the unrolled kernel; other filters (strided SC, DC and the
   // SC input gradient, whose rows come ordered by offset class so that most
   // blocks take one offset only) also skip the blocks' gathers.
-  // Single-offset views (f = s transposed runs, 1^d filters) unroll to one
+  // Single-offset views (the pairs of f = s books, 1^d filters) unroll to one
   // step with a third of the registers, so more workgroups share a CU.
   auto kern = k_fwd_mfma<TIn, NCH, NCB, RB, TOut, 0, true, WT, true>;
   if constexpr (!SMALL) {
@@ -867,11 +976,13 @@ void launch_mfma_rb(const Call& c) {
            : c.v.K == 1 ? k_fwd_mfma<TIn, NCH, NCB, RB, TOut, 1, true, WT>
            : c.v.K == 8 ? k_fwd_mfma<TIn, NCH, NCB, RB, TOut, 8, true, WT, true>
                         : kern;
+    if constexpr (WT != 1)
+      if (c.v.pair_off) kern = k_fwd_mfma<TIn, NCH, NCB, RB, TOut, 1, true, WT, false, true>;
   }
+  const ViewArgs a = view_args(c.v);
   kern<<<grid, 256, 0, c.stream>>>(
-      c.v.gmap, c.v.perm, c.v.gstride, c.v.hdr, static_cast<int>(c.v.K),
-      static_cast<const TIn*>(c.x), c.x_bytes, static_cast<const TIn*>(c.w), c.bias,
-      static_cast<TOut*>(c.y), c.C_out, ntiles, c.v.seg, c.epi);
+      a.gmap, a.perm, c.v.gstride, c.v.hdr, a.K, static_cast<const TIn*>(c.x), c.x_bytes,
+      static_cast<const TIn*>(c.w), c.bias, static_cast<TOut*>(c.y), c.C_out, ntiles, c.epi);
 }
 
 template <typename TIn, int NCH, int NCB, typename TOut, int WT>
@@ -880,7 +991,7 @@ void launch_mfma(const Call& c) {
   const bool generic_k = c.v.K != 27 && c.v.K != 1 && c.v.K != 8;
   const int64_t tiles = (c.v.n_cap + 4 * RB * 16 - 1) / (4 * RB * 16);
   if constexpr (RB > 1) {
-    if (generic_k && !c.v.seg && tiles < kSmallLayerTiles) {
+    if (generic_k && tiles < kSmallLayerTiles) {
       launch_mfma_rb<TIn, NCH, NCB, TOut, WT, 1, true>(c);
       return;
     }
@@ -933,6 +1044,12 @@ void launch_vec(const Call& c, int C_in) {
   int64_t blocks = (total + 255) / 256;
   if (blocks > 65536) blocks = 65536;
   if (blocks < 1) blocks = 1;
+  if (c.v.pair_off) {
+    k_pairs_vec<TIn, TOut, WT><<<static_cast<unsigned>(blocks), 256, 0, c.stream>>>(
+        c.v.pairs, c.v.pair_off, c.v.pair_K, static_cast<const TIn*>(c.x),
+        static_cast<const TIn*>(c.w), c.bias, static_cast<TOut*>(c.y), C_in, c.C_out);
+    return;
+  }
   k_fwd_vec<TIn, TOut, WT><<<static_cast<unsigned>(blocks), 256, 0, c.stream>>>(
       c.v.gmap, c.v.perm, c.v.gstride, c.v.n_cap, c.v.hdr, static_cast<int>(c.v.K),
       static_cast<const TIn*>(c.x), static_cast<const TIn*>(c.w), c.bias, static_cast<TOut*>(c.y),
@@ -962,10 +1079,9 @@ constexpr auto slab_entry() {
   else return sizeof(TOut) == 4 ? forward_slab_bf : forward_slab_bb;
 }
 
-// Channel counts k_fwd_mfma is not compiled for.  Returns false for a
-// segmented view that no kernel here takes.
+// Channel counts k_fwd_mfma is not compiled for.
 template <typename TIn, typename TOut, int WT>
-bool launch_generic(const Call& c, int C_in) {
+void launch_generic(const Call& c, int C_in) {
   // buffer ranges (inputs, weights, one offset's map row) are kept below 2^31
   // bytes; lowc also needs one grid row of blocks per kLowCols columns (at
   // most 65535).  Below kLowMinRows positions of few planes the
@@ -981,42 +1097,46 @@ bool launch_generic(const Call& c, int C_in) {
   // 29,760 rows 1 -> 33: 14 / 16, 1 -> 100: 35 / 20).
   constexpr int64_t kLowMinRows = 2048;
   const uint64_t xb = static_cast<uint64_t>(c.v.n_src) * C_in * sizeof(TIn);
-  const uint64_t wb = static_cast<uint64_t>(c.v.K) * C_in * c.C_out * sizeof(TIn);
+  const bool by_pairs = c.v.pair_off != nullptr;
+  const uint64_t wb =
+      static_cast<uint64_t>(by_pairs ? c.v.pair_K : c.v.K) * C_in * c.C_out * sizeof(TIn);
   const bool fits = xb < kBufOOB && static_cast<uint64_t>(c.v.gstride) * 4 < kBufOOB;
   const bool few = C_in <= kLowCin;
-  if (!c.v.seg && few && fits && c.v.n_cap >= kLowMinRows && c.C_out % kLowCols == 0 &&
+  if (!by_pairs && few && fits && c.v.n_cap >= kLowMinRows && c.C_out % kLowCols == 0 &&
       c.C_out / kLowCols <= 65535) {
     launch_lowc<TIn, TOut, WT>(c, C_in, static_cast<uint32_t>(xb));
-    return true;
+    return;
   }
-  const bool wfits = (c.v.seg ? 1024 * wb : wb) < kBufOOB && c.C_out <= kMaxTileCols;
+  const bool wfits = wb < kBufOOB && c.C_out <= kMaxTileCols;
   const int64_t cols = static_cast<int64_t>(c.C_out) * (C_in + 2);
   const bool narrow = (C_in <= 16 && cols < (sizeof(TIn) == 4 ? 80 : 48)) ||
                       (few && c.v.n_cap * c.v.K * cols < 27000000);
-  if ((c.v.seg || !(narrow || (few && c.v.n_cap < kLowMinRows))) && fits && wfits &&
+  if ((by_pairs || !(narrow || (few && c.v.n_cap < kLowMinRows))) && fits && wfits &&
       !force_vector_path()) {
     Call cc = c;
     cc.x_bytes = static_cast<uint32_t>(xb);
-    slab_entry<TIn, TOut>()(cc, WT, C_in, static_cast<uint32_t>(c.v.seg ? 0x7fffffffu : wb));
-    return true;
+    slab_entry<TIn, TOut>()(cc, WT, C_in, static_cast<uint32_t>(wb));
+    return;
   }
-  if (c.v.seg) return false;
   launch_vec<TIn, TOut, WT>(c, C_in);
-  return true;
 }
 
 template <int WT>
-bool run(const Call& c, int in_dt, int out_dt, int C_in) {
+void run(const Call& c, int in_dt, int out_dt, int C_in) {
   bool done = false;
   if (!force_vector_path()) {
     done = out_dt == SPCONV_F32 ? try_mfma<float, WT>(c, in_dt, C_in)
                                 : try_mfma<uint16_t, WT>(c, in_dt, C_in);
   }
-  if (done) return true;
-  if (in_dt == SPCONV_F32 && out_dt == SPCONV_F32) return launch_generic<float, float, WT>(c, C_in);
-  if (in_dt == SPCONV_F32) return launch_generic<float, uint16_t, WT>(c, C_in);
-  if (out_dt == SPCONV_F32) return launch_generic<uint16_t, float, WT>(c, C_in);
-  return launch_generic<uint16_t, uint16_t, WT>(c, C_in);
+  if (done) return;
+  if (in_dt == SPCONV_F32 && out_dt == SPCONV_F32)
+    launch_generic<float, float, WT>(c, C_in);
+  else if (in_dt == SPCONV_F32)
+    launch_generic<float, uint16_t, WT>(c, C_in);
+  else if (out_dt == SPCONV_F32)
+    launch_generic<uint16_t, float, WT>(c, C_in);
+  else
+    launch_generic<uint16_t, uint16_t, WT>(c, C_in);
 }
 
 }  // namespace

@@ -148,33 +148,35 @@ __device__ __forceinline__ bool nonfinite(const f32x4 (&acc)[RB][NCB]) {
 // own pairs, one element per lane at a time as k_fwd_vec does.
 template <typename TIn, typename TOut, int WT>
 __device__ __forceinline__ void sum_over_pairs(
-    const int32_t* gmap, const int32_t* perm, int64_t gstride, int64_t n_rows, int K, int wseg,
+    const int32_t* gmap, const int32_t* perm, int64_t gstride, int64_t n_rows, int K,
     const TIn* x, const TIn* w, const float* bias, TOut* y, int C_in, int C_out, int64_t row0,
     int rows, int col0, int cols, const Epilogue& epi) {
   for (int e = __lane_id(); e < rows * cols; e += kWave) {
     const int64_t p = row0 + e / cols;
     const int col = col0 + e % cols;
-    if (p >= n_rows || col >= C_out || perm[p] < 0) continue;
+    if (p >= n_rows || col >= C_out) continue;
     float acc = 0.0f;
     for (int i = 0; i < K; ++i) {
       const int64_t g = static_cast<int64_t>(gmap[i * gstride + p]) - 1;
       if (g < 0) continue;
       for (int c = 0; c < C_in; ++c)
         acc = fmaf(ElemIO<TIn>::load(x, g * C_in + c),
-                   ElemIO<TIn>::load(w, w_index<WT>(wseg >= 0 ? wseg : i, K, c, col, C_in, C_out)),
-                   acc);
+                   ElemIO<TIn>::load(w, w_index<WT>(i, K, c, col, C_in, C_out)), acc);
     }
     store_elem(acc, static_cast<int64_t>(perm[p]) * C_out + col, col, bias, epi, y);
   }
 }
 
-template <typename TIn, typename TOut, int NCH, int NCB, int RB, int WT, bool AX, bool AW>
+// PAIRS: a pair view (K = 1), from which the tile's rows and its W^i come, in
+// the arguments of the map, the schedule and K.
+template <typename TIn, typename TOut, int NCH, int NCB, int RB, int WT, bool AX, bool AW,
+          bool PAIRS>
 __global__ __launch_bounds__(256, 2) void k_fwd_slab(
     const int32_t* __restrict__ gmap, const int32_t* __restrict__ perm, int64_t gstride,
-    const DeviceHeader* __restrict__ hdr, int K, const TIn* __restrict__ x, uint32_t x_bytes,
+    const DeviceHeader* __restrict__ hdr, int K_arg, const TIn* __restrict__ x, uint32_t x_bytes,
     const TIn* __restrict__ w, uint32_t w_bytes, const float* __restrict__ bias,
-    TOut* __restrict__ y, int C_in, int C_out, int64_t ntiles, const int32_t* __restrict__ seg,
-    Epilogue epi) {
+    TOut* __restrict__ y, int C_in, int C_out, int64_t ntiles, Epilogue epi) {
+  const int K = PAIRS ? 1 : K_arg;
   constexpr int KC = MT<TIn>::KC;
   constexpr int SLAB = NCH * KC;
   constexpr int COLS = NCB * 16;
@@ -184,20 +186,24 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
   constexpr int LDWB = WImage<ROWB>::kRowBytes;
   constexpr int WAVE_ROWS = RB * 16;
   constexpr int TILE_ROWS = 4 * WAVE_ROWS;
-  static_assert(kSegRows % TILE_ROWS == 0, "tiles inside one segment chunk");
 
   __shared__ __attribute__((aligned(16))) unsigned char s_w[2][COLS * LDWB];
 
   // XCD-contiguous tile ranges over the device-side row count, as k_fwd_mfma
-  const int64_t n_rows = hdr->n_out;
-  const int64_t nt_real = (n_rows + TILE_ROWS - 1) / TILE_ROWS;
-  const int64_t nt = nt_real < ntiles ? nt_real : ntiles;
-  const int64_t per = (nt + 7) / 8;
-  const int64_t q8 = blockIdx.x / 8;
-  if (q8 >= per) return;
-  const int64_t tile = static_cast<int64_t>(blockIdx.x % 8) * per + q8;
-  if (tile >= nt) return;
-  const int wseg = seg ? seg[tile * TILE_ROWS / kSegRows] : -1;
+  PairTile pt{0, 0, 0};
+  int64_t n_rows = TILE_ROWS, tile = 0;
+  if constexpr (PAIRS) {
+    if (!pair_tile<TILE_ROWS>(reinterpret_cast<const int64_t*>(perm), K_arg, ntiles, &pt)) return;
+  } else {
+    n_rows = hdr->n_out;
+    const int64_t nt_real = (n_rows + TILE_ROWS - 1) / TILE_ROWS;
+    const int64_t nt = nt_real < ntiles ? nt_real : ntiles;
+    const int64_t per = (nt + 7) / 8;
+    const int64_t q8 = blockIdx.x / 8;
+    if (q8 >= per) return;
+    tile = static_cast<int64_t>(blockIdx.x % 8) * per + q8;
+    if (tile >= nt) return;
+  }
 
   const int col0 = blockIdx.y * COLS;
   const int wave = threadIdx.x / kWave;
@@ -225,7 +231,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
   using WS = WStage<TIn, NCH, NCB, WT, AX, AW>;
   typedef typename WS::Regs WRegs;
   auto w_load = [&](At a, WRegs& r) {
-    const int iv = wseg >= 0 ? wseg : (WT == 1 ? K - 1 - a.i : a.i);
+    const int iv = PAIRS ? pt.i : (WT == 1 ? K - 1 - a.i : a.i);
     WS::load(wr_, a.i < K, iv, a.c, C_in, C_out, col0, r);
   };
   auto w_store = [&](int buf, const WRegs& r) { WS::store(s_w[buf], r); };
@@ -234,6 +240,10 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
   const int64_t map_row = row0 + map_lane<RB>(lane);
   const uint32_t map_off = map_row < n_rows ? static_cast<uint32_t>(map_row) * 4u : kBufOOB;
   auto g_load = [&](At a, GRegs& g) {
+    if constexpr (PAIRS) {
+      g = pair_row(gmap, pt, static_cast<int>(map_row), 1);
+      return;
+    }
     const int ic = a.i < K ? a.i : 0;
     const __amdgpu_buffer_rsrc_t gr = buf_rsrc(gmap + static_cast<int64_t>(ic) * gstride,
                                                gmap_bytes);
@@ -327,232 +337,35 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
     step(e + 2, a2, p2, a1, p1, g2, g1, w0, w1);
   }
 
-  if (__any(nonfinite(acc))) {
-    sum_over_pairs<TIn, TOut, WT>(gmap, perm, gstride, n_rows, K, wseg, x, w, bias, y, C_in, C_out,
-                                  tile * TILE_ROWS + uwave * WAVE_ROWS, WAVE_ROWS, col0, COLS,
-                                  epi);
-    return;
+  int32_t row;
+  if constexpr (PAIRS) {
+    row = pair_row(gmap, pt, static_cast<int>(map_row), 0);
+  } else {
+    if (__any(nonfinite(acc))) {
+      sum_over_pairs<TIn, TOut, WT>(gmap, perm, gstride, n_rows, K, x, w, bias, y, C_in, C_out,
+                                    tile * TILE_ROWS + uwave * WAVE_ROWS, WAVE_ROWS, col0, COLS,
+                                    epi);
+      return;
+    }
+    row = map_row < n_rows ? perm[map_row] : -1;
   }
-  store_tile<TOut, RB, NCB, false>(acc, map_row < n_rows ? perm[map_row] : -1, bias, y, C_out,
-                                   col0, lg, epi);
-}
-
-// ---------------------------------------------------------------------------
-// The reversed direction of SC with f = s
-// ---------------------------------------------------------------------------
-// k_fwd_up: DC and the SC input gradient on a book whose filter equals its
-// stride.  Every SC input row then hangs on exactly one (offset, SC output
-// row), so the reversed layer is a dense product of the SC output rows with
-// all K matrices whose results are dealt to the SC input rows: a tile of
-// output positions reads its rows once (registers, C_in <= 4 k-chunks: KEEP;
-// wider rows come again per slab), walks the offsets, and stores row p of
-// x W^i to input row G[i][p] - 1 of the forward's own gather map.  No
-// transposed map is built or read.  Every destination row is written exactly
-// once provided every input row has its pair (the book checks the extents).
-//
-// Bound: HBM, the destination rows and their map.  Measured, 505,281 surface
-// rows 64 -> 1,703,204 rows 32 bf16 2^3: DC 72 us, the input gradient 66 us
-// (77-81 us with the rows gathered once per pair from per-offset lists, whose
-// building also took 130 us of every book; 101 us here with x as the first
-// operand, every result row then stored in 4-byte pieces).
-template <typename TIn, typename TOut, int NCH, int NCB, int RB, int WT, bool KEEP, bool AX,
-          bool AW>
-__global__ __launch_bounds__(256, 2) void k_fwd_up(
-    const int32_t* __restrict__ gmap, const int32_t* __restrict__ perm, int64_t gstride,
-    const DeviceHeader* __restrict__ hdr, int K, const TIn* __restrict__ x, uint32_t x_bytes,
-    const TIn* __restrict__ w, uint32_t w_bytes, const float* __restrict__ bias,
-    TOut* __restrict__ y, int C_in, int C_out, int64_t ntiles) {
-  using WS = WStage<TIn, NCH, NCB, WT, AX, AW>;
-  constexpr int KC = MT<TIn>::KC;
-  constexpr int SLAB = WS::SLAB;
-  constexpr int EPP = WS::EPP, ESZ = WS::ESZ, ROWB = WS::ROWB;
-  constexpr int WAVE_ROWS = RB * 16;
-  constexpr int TILE_ROWS = 4 * WAVE_ROWS;
-  __shared__ __attribute__((aligned(16))) unsigned char s_w[2][WS::COLS * WImage<ROWB>::kRowBytes];
-
-  // XCD-contiguous tile ranges over the device-side row count, as k_fwd_mfma
-  const int64_t n_rows = hdr->n_out;
-  const int64_t nt_real = (n_rows + TILE_ROWS - 1) / TILE_ROWS;
-  const int64_t nt = nt_real < ntiles ? nt_real : ntiles;
-  const int64_t per = (nt + 7) / 8;
-  const int64_t q8 = blockIdx.x / 8;
-  if (q8 >= per) return;
-  const int64_t tile = static_cast<int64_t>(blockIdx.x % 8) * per + q8;
-  if (tile >= nt) return;
-
-  const int col0 = blockIdx.y * WS::COLS;
-  const int lane = threadIdx.x % kWave;
-  const int lr = lane % 16, lg = lane / 16;
-  const int64_t row0 = tile * TILE_ROWS + threadIdx.x / kWave * WAVE_ROWS;
-  const uint32_t row_bytes = static_cast<uint32_t>(C_in) * ESZ;
-  const __amdgpu_buffer_rsrc_t xr = buf_rsrc(x, x_bytes);
-  const __amdgpu_buffer_rsrc_t wr = buf_rsrc(w, w_bytes);
-  const uint32_t gmap_bytes = static_cast<uint32_t>(gstride * 4);
-
-  int32_t src[RB];                                 // x row of position 16 b + lr, -1 past the end
-#pragma unroll
-  for (int b = 0; b < RB; ++b) {
-    const int64_t p = row0 + b * 16 + lr;
-    src[b] = p < n_rows ? perm[p] : -1;
-  }
-  typedef u32x4 ARegs[RB][NCH];
-  auto a_load = [&](int c0, ARegs& a) {
-#pragma unroll
-    for (int b = 0; b < RB; ++b)
-#pragma unroll
-      for (int ch = 0; ch < NCH; ++ch) {
-        const int c = c0 + ch * KC + lg * EPP;
-        const uint32_t off =
-            static_cast<uint32_t>(src[b]) * row_bytes + static_cast<uint32_t>(c) * ESZ;
-        a[b][ch] = buf_piece<TIn, AX>(xr, off, src[b] >= 0 ? C_in - c : 0);
-      }
-  };
-  // destinations (row, -1 = none) of the wave's positions at offset i, as
-  // k_fwd_mfma's map entries
-  const int64_t map_row = row0 + map_lane<RB>(lane);
-  const uint32_t map_off = map_row < n_rows ? static_cast<uint32_t>(map_row) * 4u : kBufOOB;
-  auto d_load = [&](int i) -> int32_t {
-    const __amdgpu_buffer_rsrc_t gr =
-        buf_rsrc(gmap + static_cast<int64_t>(i < K ? i : 0) * gstride, gmap_bytes);
-    return static_cast<int32_t>(
-               __builtin_amdgcn_raw_buffer_load_b32(gr, i < K ? map_off : kBufOOB, 0, 0)) - 1;
-  };
-
-  // W^T is the first operand of the products, so a lane holds 4 NCB adjacent
-  // columns (from n0) of position 16 b + lr and stores them in 16-byte pieces
-  constexpr int LC = 4 * NCB;
-  constexpr int PC = 16 / static_cast<int>(sizeof(TOut));
-  const bool whole = C_out % PC == 0;
-  const int n0 = col0 + lg * LC;
-  float bv[LC];
-#pragma unroll
-  for (int e = 0; e < LC; ++e) bv[e] = bias && n0 + e < C_out ? bias[n0 + e] : 0.0f;
-  f32x4 acc[RB][NCB];
-  auto clear = [&]() {
-#pragma unroll
-    for (int b = 0; b < RB; ++b)
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) acc[b][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  };
-  auto mma = [&](int c0, int buf, const ARegs& a, uint32_t pres) {
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      if (ch > 0 && c0 + ch * KC >= C_in) break;
-      u32x4 bw[NCB];
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb)
-        bw[cb] = *reinterpret_cast<const u32x4*>(
-            &s_w[buf][WImage<ROWB>::at(cb * 16 + lr, ch * 64 + lg * 16)]);
-#pragma unroll
-      for (int b = 0; b < RB; ++b) {
-        if (!(pres & (1u << b))) continue;
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) acc[b][cb] = MT<TIn>::mma(bw[cb], a[b][ch], acc[b][cb]);
-      }
-    }
-  };
-  auto put = [&](int32_t dv, uint32_t pres) {
-    int32_t d[RB];
-    spread_map<RB>(dv, d);
-#pragma unroll
-    for (int b = 0; b < RB; ++b) {
-      if (!(pres & (1u << b)) || d[b] < 0) continue;
-      TOut* out = y + static_cast<int64_t>(d[b]) * C_out + n0;
-      float z[LC];
-#pragma unroll
-      for (int e = 0; e < LC; ++e) z[e] = acc[b][e / 4][e % 4] + bv[e];
-      if (whole) {
-#pragma unroll
-        for (int q = 0; q < LC / PC; ++q)
-          if (n0 + q * PC < C_out) store16(out + q * PC, z + q * PC);
-      } else {
-#pragma unroll
-        for (int e = 0; e < LC; ++e)
-          if (n0 + e < C_out) ElemIO<TOut>::store(out, e, z[e]);
-      }
-    }
-  };
-
-  // step e = (offset i, slab from channel c); W of step e + 1 (and, without
-  // KEEP, its rows) and the destinations of offset i + 1 are on their way
-  // while step e multiplies
-  typename WS::Regs wn;
-  ARegs a0, a1;
-  a_load(0, a0);
-  int32_t d0 = d_load(0), d1 = -1;
-  WS::load(wr, true, 0, 0, C_in, C_out, col0, wn);
-  WS::store(s_w[0], wn);
-  __syncthreads();
-  clear();
-  int i = 0, c = 0, buf = 0;
-  uint32_t pres = map_blocks<RB>(d0);
-  for (;;) {
-    int ni = i, nc = c + SLAB;
-    if (KEEP || nc >= C_in) {
-      nc = 0;
-      ++ni;
-    }
-    d1 = d_load(ni);
-    WS::load(wr, ni < K, ni, nc, C_in, C_out, col0, wn);
-    if constexpr (!KEEP) a_load(nc, a1);
-    mma(c, buf, a0, pres);
-    WS::store(s_w[buf ^ 1], wn);
-    if (ni != i) {
-      put(d0, pres);
-      if (ni >= K) break;
-      clear();
-      d0 = d1;
-      pres = map_blocks<RB>(d0);
-    }
-    if constexpr (!KEEP) {
-#pragma unroll
-      for (int b = 0; b < RB; ++b)
-#pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) a0[b][ch] = a1[b][ch];
-    }
-    __syncthreads();
-    i = ni;
-    c = nc;
-    buf ^= 1;
-  }
-}
-
-// The same on the vector ALU, one lane per (position, offset, column): for
-// operands past the buffer range and columns past the grid's.
-template <typename TIn, typename TOut, int WT>
-__global__ __launch_bounds__(256) void k_fwd_up_vec(
-    const int32_t* __restrict__ gmap, const int32_t* __restrict__ perm, int64_t gstride,
-    const DeviceHeader* __restrict__ hdr, int K, const TIn* __restrict__ x,
-    const TIn* __restrict__ w, const float* __restrict__ bias, TOut* __restrict__ y, int C_in,
-    int C_out) {
-  const int64_t n_rows = hdr->n_out, total = n_rows * K * C_out;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; t < total;
-       t += stride) {
-    const int n = static_cast<int>(t % C_out);
-    const int64_t r = t / C_out, p = r % n_rows;
-    const int i = static_cast<int>(r / n_rows);
-    const int64_t dst = static_cast<int64_t>(gmap[i * gstride + p]) - 1;
-    if (dst < 0) continue;
-    const int64_t xb = static_cast<int64_t>(perm[p]) * C_in;
-    float acc = 0.0f;
-    for (int c = 0; c < C_in; ++c)
-      acc = fmaf(ElemIO<TIn>::load(x, xb + c),
-                 ElemIO<TIn>::load(w, w_index<WT>(i, K, c, n, C_in, C_out)), acc);
-    ElemIO<TOut>::store(y, dst * C_out + n, bias ? acc + bias[n] : acc);
-  }
+  store_tile<TOut, RB, NCB, false>(acc, row, bias, y, C_out, col0, lg, epi);
 }
 
 template <typename TIn, typename TOut, int WT, int NCH, int NCB, int RB, bool AX, bool AW>
 void launch_slab_tile(const Call& c, int C_in, uint32_t w_bytes) {
   constexpr int kTileRows = 4 * RB * 16;
-  const int64_t ntiles = (c.v.n_cap + kTileRows - 1) / kTileRows;
+  const int64_t ntiles = view_tiles(c.v, kTileRows);
   const dim3 grid(static_cast<unsigned>(8 * ((ntiles + 7) / 8)),
                   static_cast<unsigned>((c.C_out + NCB * 16 - 1) / (NCB * 16)));
-  k_fwd_slab<TIn, TOut, NCH, NCB, RB, WT, AX, AW><<<grid, 256, 0, c.stream>>>(
-      c.v.gmap, c.v.perm, c.v.gstride, c.v.hdr, static_cast<int>(c.v.K),
-      static_cast<const TIn*>(c.x), c.x_bytes, static_cast<const TIn*>(c.w), w_bytes, c.bias,
-      static_cast<TOut*>(c.y), C_in, c.C_out, ntiles, c.v.seg, c.epi);
+  auto kern = k_fwd_slab<TIn, TOut, NCH, NCB, RB, WT, AX, AW, false>;
+  if constexpr (WT != 1)
+    if (c.v.pair_off) kern = k_fwd_slab<TIn, TOut, NCH, NCB, RB, WT, AX, AW, true>;
+  const ViewArgs a = view_args(c.v);
+  kern<<<grid, 256, 0, c.stream>>>(
+      a.gmap, a.perm, c.v.gstride, c.v.hdr, a.K, static_cast<const TIn*>(c.x), c.x_bytes,
+      static_cast<const TIn*>(c.w), w_bytes, c.bias, static_cast<TOut*>(c.y), C_in, c.C_out,
+      ntiles, c.epi);
 }
 
 // Rows per tile: 64 when the usual 256 (128 with more than 64 columns) would
@@ -611,72 +424,6 @@ void run_slab(const Call& c, int wmode, int C_in, uint32_t w_bytes) {
     case 1: launch_slab<TIn, TOut, 1>(c, C_in, w_bytes); break;
     default: launch_slab<TIn, TOut, 2>(c, C_in, w_bytes); break;
   }
-}
-
-template <typename TIn, typename TOut, int WT, int NCH, int NCB, int RB, bool KEEP, bool AX,
-          bool AW>
-void launch_up_tile(const Call& c, int C_in, uint32_t w_bytes) {
-  constexpr int kTileRows = 4 * RB * 16;
-  const int64_t ntiles = (c.v.n_cap + kTileRows - 1) / kTileRows;
-  const dim3 grid(static_cast<unsigned>(8 * ((ntiles + 7) / 8)),
-                  static_cast<unsigned>((c.C_out + NCB * 16 - 1) / (NCB * 16)));
-  k_fwd_up<TIn, TOut, NCH, NCB, RB, WT, KEEP, AX, AW><<<grid, 256, 0, c.stream>>>(
-      c.v.gmap, c.v.perm, c.v.gstride, c.v.hdr, static_cast<int>(c.v.K),
-      static_cast<const TIn*>(c.x), c.x_bytes, static_cast<const TIn*>(c.w), w_bytes, c.bias,
-      static_cast<TOut*>(c.y), C_in, c.C_out, ntiles);
-}
-
-template <typename TIn, typename TOut, int WT, int NCB>
-void launch_up_cols(const Call& c, int C_in, uint32_t w_bytes) {
-  const int chunks = (C_in + MT<TIn>::KC - 1) / MT<TIn>::KC;
-  // 64-row tiles for small layers, as the forward
-  const bool small = c.v.n_cap / 256 < kSmallLayerTiles;
-  if (chunks == 1)
-    (small ? launch_up_tile<TIn, TOut, WT, 1, NCB, 1, true, true, true>
-           : launch_up_tile<TIn, TOut, WT, 1, NCB, 4, true, true, true>)(c, C_in, w_bytes);
-  else if (chunks == 2)
-    (small ? launch_up_tile<TIn, TOut, WT, 2, NCB, 1, true, true, true>
-           : launch_up_tile<TIn, TOut, WT, 2, NCB, 4, true, true, true>)(c, C_in, w_bytes);
-  else if (chunks <= 4)
-    (small ? launch_up_tile<TIn, TOut, WT, 4, NCB, 1, true, true, true>
-           : launch_up_tile<TIn, TOut, WT, 4, NCB, 2, true, true, true>)(c, C_in, w_bytes);
-  else
-    (small ? launch_up_tile<TIn, TOut, WT, 2, NCB, 1, false, true, true>
-           : launch_up_tile<TIn, TOut, WT, 2, NCB, 2, false, true, true>)(c, C_in, w_bytes);
-}
-
-template <typename TIn, typename TOut, int WT>
-void launch_up(const Call& c, int C_in) {
-  constexpr int EPP = 16 / static_cast<int>(sizeof(TIn));
-  const uint64_t xb = static_cast<uint64_t>(c.v.n_src) * C_in * sizeof(TIn);
-  const uint64_t wb = static_cast<uint64_t>(c.v.K) * C_in * c.C_out * sizeof(TIn);
-  if (force_vector_path() || xb >= kBufOOB || wb >= kBufOOB ||
-      static_cast<uint64_t>(c.v.gstride) * 4 >= kBufOOB || c.C_out > kMaxTileCols) {
-    int64_t blocks = (c.v.n_cap * c.v.K * c.C_out + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    k_fwd_up_vec<TIn, TOut, WT><<<static_cast<unsigned>(blocks), 256, 0, c.stream>>>(
-        c.v.gmap, c.v.perm, c.v.gstride, c.v.hdr, static_cast<int>(c.v.K),
-        static_cast<const TIn*>(c.x), static_cast<const TIn*>(c.w), c.bias,
-        static_cast<TOut*>(c.y), C_in, c.C_out);
-    return;
-  }
-  Call cc = c;
-  cc.x_bytes = static_cast<uint32_t>(xb);
-  const uint32_t w_bytes = static_cast<uint32_t>(wb);
-  const bool ax = C_in % EPP == 0, aw = WT != 0 || c.C_out % EPP == 0;
-  if (ax && aw)
-    (c.C_out <= 32 ? launch_up_cols<TIn, TOut, WT, 2>
-                   : launch_up_cols<TIn, TOut, WT, 4>)(cc, C_in, w_bytes);
-  else if (WT == 0 && ax)
-    launch_up_tile<TIn, TOut, WT, 1, 4, 1, false, true, WT != 0>(cc, C_in, w_bytes);
-  else
-    launch_up_tile<TIn, TOut, WT, 1, 4, 1, false, false, WT != 0>(cc, C_in, w_bytes);
-}
-
-template <typename TIn, typename TOut>
-void run_up(const Call& c, int wmode, int C_in) {
-  if (wmode == 0) launch_up<TIn, TOut, 0>(c, C_in);
-  else launch_up<TIn, TOut, 2>(c, C_in);
 }
 
 }  // namespace

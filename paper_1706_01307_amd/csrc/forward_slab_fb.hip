@@ -1,14 +1,10 @@
-// k_fwd_slab and k_fwd_up for fp32 inputs and bf16 outputs.
+// k_fwd_slab for fp32 inputs and bf16 outputs.
 #include "forward_slab.h"
 
 namespace spc {
 
 void forward_slab_fb(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes) {
   run_slab<float, uint16_t>(c, wmode, C_in, w_bytes);
-}
-
-void forward_up_fb(const FwdCall& c, int wmode, int C_in) {
-  run_up<float, uint16_t>(c, wmode, C_in);
 }
 
 }  // namespace spc

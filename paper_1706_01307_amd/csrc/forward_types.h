@@ -26,12 +26,14 @@ struct FwdView {
   int64_t n_cap;
   int64_t K;
   int64_t n_src;
-  // Segmented single-offset views (K = 1): position chunks of kSegRows rows
-  // belong to one offset each, seg[chunk] naming which W^i they take; a
-  // position whose perm entry is negative is padding.  NULL otherwise.
-  const int32_t* seg = nullptr;
+  // Pair views (K = 1; pair_off not NULL): instead of a map, pair e of offset
+  // i < pair_K, pairs[pair_off[i] + e] = (input row, output row), adds row
+  // `output row` of the source times W^i to row `input row`, each of which is
+  // in one pair; n_cap pairs in all.  gmap, perm and gstride are not read.
+  const int32_t* pairs = nullptr;
+  const int64_t* pair_off = nullptr;
+  int pair_K = 0;
 };
-constexpr int kSegRows = 256;
 // Optional epilogue of a forward.  The networks of Section 5 follow each
 // convolution with batch normalisation (at inference a per-channel affine
 // map), add the block input back in residual blocks, and apply a ReLU, all at
@@ -55,22 +57,14 @@ struct FwdCall {
   hipStream_t stream;
   Epilogue epi;
 };
-// Each returns false when the view is segmented and no matrix-core kernel
-// fits the shape (nothing is launched then).
-bool forward_run_w0(const FwdCall& c, int in_dt, int out_dt, int C_in);
-bool forward_run_w1(const FwdCall& c, int in_dt, int out_dt, int C_in);
-bool forward_run_w2(const FwdCall& c, int in_dt, int out_dt, int C_in);
+void forward_run_w0(const FwdCall& c, int in_dt, int out_dt, int C_in);
+void forward_run_w1(const FwdCall& c, int in_dt, int out_dt, int C_in);
+void forward_run_w2(const FwdCall& c, int in_dt, int out_dt, int C_in);
 // Any channel counts, by the types of inputs and outputs (f: fp32, b: bf16);
 // c.x_bytes set, w_bytes the bytes of w (both below 2^31).
 void forward_slab_ff(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
 void forward_slab_fb(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
 void forward_slab_bf(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
 void forward_slab_bb(const FwdCall& c, int wmode, int C_in, uint32_t w_bytes);
-// The reversed direction (wmode 0: DC, 2: the SC input gradient) on the
-// forward's view of an SC book with f = s whose input rows all have a pair.
-void forward_up_ff(const FwdCall& c, int wmode, int C_in);
-void forward_up_fb(const FwdCall& c, int wmode, int C_in);
-void forward_up_bf(const FwdCall& c, int wmode, int C_in);
-void forward_up_bb(const FwdCall& c, int wmode, int C_in);
 
 }  // namespace spc

@@ -188,23 +188,14 @@ struct spconv_rulebook_s {
   // the SC input rows ordered by offset class, and for every (offset, position
   // in that order) 1 + the SC output row paired with that input row
   // t_direct: f = s and the strides divide the extents, so every input row has
-  // exactly one pair and the reversed direction runs on the forward's own map;
-  // none of the arrays below are built then.
+  // exactly one pair and the reversed direction runs on the pair lists; none of
+  // the arrays below are built then.
   bool t_direct = false;
   spc::DeviceHeader* t_hdr;    // n_out = n_in
   int32_t* t_perm;             // [n_in]
   int32_t* t_gmap;             // [K][t_gstride]
   int64_t t_gstride;
-  // f = s: R_i also split into its two columns, each offset's run padded to
-  // whole chunks of kSegRows positions (padding: source 0, destination -1)
-  bool t_single;
-  int64_t t_npad_cap;          // bound on the padded length (sum k + K kSegRows)
-  int32_t* t_src;              // [t_npad_cap] 1 + SC output row
-  int32_t* t_dst;              // [t_npad_cap] SC input row, -1 = padding
-  int32_t* t_seg;              // [t_npad_cap / kSegRows] offset of every chunk
-  int32_t* t_chunk_off;        // [K + 1] first chunk of every offset
-  spc::DeviceHeader* t_hdrs;   // [K] n_out = k_i; [K] (one more) n_out = padded length
-  std::vector<int64_t> h_pair_off;   // host copy of pair_off, filled on first use
+  int64_t h_total = -1;        // pairs in all, once read on the host (reversed_view)
   // Streams other than the build stream that work reading this book was
   // enqueued on, each with an event recorded after its latest such work:
   // the release makes the build stream wait on all of them before the
@@ -259,9 +250,6 @@ FwdView view_of(spconv_rulebook rb);
 int forward_view(const FwdView& v, int wmode, int in_dt, const void* x, const void* w,
                  const float* bias, int out_dt, void* y, int C_in, int C_out,
                  hipStream_t stream, const Epilogue& epi = Epilogue{});
-// The reversed direction of a book with t_direct (wmode 0 or 2).
-int forward_up(spconv_rulebook rb, int wmode, int in_dt, const void* x, const void* w,
-               const float* bias, int out_dt, void* y, int C_in, int C_out, hipStream_t stream);
 int forward(spconv_rulebook rb, int in_dt, const void* x, const void* w,
             const float* bias, int out_dt, void* y, int C_in, int C_out,
             hipStream_t stream);
@@ -271,11 +259,7 @@ int pool_forward(spconv_rulebook rb, int mode, int dt, const void* x, void* y, i
                  hipStream_t stream);
 size_t transpose_bytes(int64_t n_in, int64_t K);
 int build_transpose(spconv_rulebook rb, const int32_t* coords, char* mem);
-FwdView transpose_view(spconv_rulebook rb);
-constexpr int kNotSingle = 1;
-int transpose_single(spconv_rulebook rb, int wmode, int in_dt, const void* x, const void* w,
-                     const float* bias, int out_dt, void* y, int C_in, int C_out,
-                     hipStream_t st);
+int reversed_view(spconv_rulebook rb, FwdView* out);
 size_t backward_weight_workspace(spconv_rulebook rb, int C_in, int C_out, int op);
 int backward_weight(spconv_rulebook rb, int op, int dt, const void* x, const void* dy, float* dw,
                     float* db, int C_in, int C_out, void* ws, hipStream_t stream);

@@ -10,7 +10,7 @@
 // Transposed rule book (Section 3: DC(.,.,f,s) inverts SC(.,.,f,s), same
 // connections reversed; the SC input gradient runs the same reversed pairs),
 // for books whose filter overlaps or whose extents the stride does not divide
-// (the others run on the forward's own map, k_fwd_up):
+// (the others run on the pair lists, see the end):
 //   k_class_keys + radix sort  SC input rows ordered by their offset class
 //                              x mod s (stable, so by row inside a class):
 //                              with f = s every row of a class takes the same
@@ -21,13 +21,10 @@
 //                              whose input row sits at position q (each
 //                              (offset, input row) has at most one pair)
 // The output-stationary forward kernels then run DC and the input gradients
-// over this map.  When f = s every SC input row has exactly one pair, and
-// the rule book also keeps R_i split into its two columns (source rows + 1,
-// destination rows), each offset's run padded to whole chunks of kSegRows:
-//   k_chunk_layout, k_seg_fill, k_seg_scatter
-// so DC and the SC input gradient run as one gather-multiply-store launch
-// (the forward kernels with one offset, W^i chosen per chunk), with no empty
-// offsets to walk.
+// over this map.  When f = s an SC input row has at most one pair, and where
+// all of them have theirs DC and the SC input gradient run over the rule
+// book's own pair lists instead (the forward kernels with one offset, W^i
+// chosen per tile of pairs): one launch, with no empty offsets to walk.
 //
 // Weight gradient dW^i = sum over the pairs of R_i of (input row)^T x (output
 // gradient row): the output positions of the rule book's schedule are cut
@@ -210,63 +207,6 @@ __global__ __launch_bounds__(256) void k_fill_i32(int32_t* __restrict__ a, int32
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
   for (int64_t r = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; r < n; r += stride)
     a[r] = v;
-}
-
-// f = s layout: chunk_off[i] = first chunk of offset i's run (runs padded to
-// whole chunks of kSegRows), hdrs[i].n_out = k_i, hdrs[K].n_out = padded length
-__global__ void k_chunk_layout(const int64_t* __restrict__ pair_off, int K,
-                               int32_t* __restrict__ chunk_off, DeviceHeader* __restrict__ hdrs) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int64_t c = 0;
-  for (int i = 0; i < K; ++i) {
-    const int64_t k_i = pair_off[i + 1] - pair_off[i];
-    chunk_off[i] = static_cast<int32_t>(c);
-    hdrs[i].status = 0;
-    hdrs[i].n_out = k_i;
-    c += (k_i + kSegRows - 1) / kSegRows;
-  }
-  chunk_off[K] = static_cast<int32_t>(c);
-  hdrs[K].status = 0;
-  hdrs[K].n_out = c * kSegRows;
-}
-
-// seg[c] = the offset whose run holds chunk c (0 past the last run)
-__global__ __launch_bounds__(256) void k_seg_fill(const int32_t* __restrict__ chunk_off, int K,
-                                                  int64_t nchunks, int32_t* __restrict__ seg) {
-  const int64_t c = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (c >= nchunks) return;
-  int lo = 0, hi = K;                 // chunk_off[lo] <= c < chunk_off[hi], else 0
-  if (c >= chunk_off[K]) {
-    seg[c] = 0;
-    return;
-  }
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) / 2;
-    if (chunk_off[mid] <= c) lo = mid; else hi = mid;
-  }
-  seg[c] = lo;
-}
-
-// pair e of R_i -> position chunk_off[i] kSegRows + (e - pair_off[i]):
-// src = 1 + SC output row, dst = SC input row
-__global__ __launch_bounds__(256) void k_seg_scatter(const int32_t* __restrict__ pairs,
-                                                     const int64_t* __restrict__ pair_off, int K,
-                                                     const int32_t* __restrict__ chunk_off,
-                                                     int32_t* __restrict__ src,
-                                                     int32_t* __restrict__ dst) {
-  const int64_t total = pair_off[K];
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; e < total;
-       e += stride) {
-    int lo = 0, hi = K;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) / 2;
-      if (pair_off[mid] <= e) lo = mid; else hi = mid;
-    }
-    const int64_t pos = static_cast<int64_t>(chunk_off[lo]) * kSegRows + (e - pair_off[lo]);
-    src[pos] = pairs[2 * e + 1] + 1;
-    dst[pos] = pairs[2 * e];
-  }
 }
 
 __global__ void k_set_rows(DeviceHeader* h, int64_t n) {
@@ -849,15 +789,10 @@ int pool_forward(spconv_rulebook rb, int mode, int dt, const void* x, void* y, i
   return hipGetLastError() == hipSuccess ? SPCONV_OK : SPCONV_EHIP;
 }
 
-static int64_t seg_cap(int64_t n_in, int64_t K) { return n_in + K * kSegRows; }
-
 size_t transpose_bytes(int64_t n_in, int64_t K) {
   const int64_t tgstride = ((n_in + kBlock - 1) / kBlock) * kBlock;
-  const int64_t npad = seg_cap(n_in, K);
   auto al = [](size_t v) { return (v + 255) / 256 * 256; };
-  return al(256) + al(static_cast<size_t>(n_in) * 4) + al(static_cast<size_t>(K * tgstride) * 4) +
-         2 * al(static_cast<size_t>(npad) * 4) + al(static_cast<size_t>(npad / kSegRows + 1) * 4) +
-         al(static_cast<size_t>(K + 1) * 4) + al(static_cast<size_t>(K + 1) * sizeof(DeviceHeader));
+  return al(256) + al(static_cast<size_t>(n_in) * 4) + al(static_cast<size_t>(K * tgstride) * 4);
 }
 
 int build_transpose(spconv_rulebook rb, const int32_t* coords, char* mem) {
@@ -867,21 +802,6 @@ int build_transpose(spconv_rulebook rb, const int32_t* coords, char* mem) {
   rb->t_perm = reinterpret_cast<int32_t*>(mem + al(256));
   rb->t_gstride = ((n + kBlock - 1) / kBlock) * kBlock;
   rb->t_gmap = reinterpret_cast<int32_t*>(mem + al(256) + al(static_cast<size_t>(n) * 4));
-  {
-    char* q = mem + al(256) + al(static_cast<size_t>(n) * 4) +
-              al(static_cast<size_t>(rb->K * rb->t_gstride) * 4);
-    rb->t_npad_cap = seg_cap(n, rb->K);
-    const size_t pb = al(static_cast<size_t>(rb->t_npad_cap) * 4);
-    rb->t_src = reinterpret_cast<int32_t*>(q);
-    rb->t_dst = reinterpret_cast<int32_t*>(q + pb);
-    rb->t_seg = reinterpret_cast<int32_t*>(q + 2 * pb);
-    const size_t sb = al(static_cast<size_t>(rb->t_npad_cap / kSegRows + 1) * 4);
-    rb->t_chunk_off = reinterpret_cast<int32_t*>(q + 2 * pb + sb);
-    rb->t_hdrs = reinterpret_cast<DeviceHeader*>(q + 2 * pb + sb +
-                                                 al(static_cast<size_t>(rb->K + 1) * 4));
-  }
-  rb->t_single = true;               // f = s: one pair per SC input row
-  for (int j = 1; j < rb->D; ++j) rb->t_single = rb->t_single && rb->f[j] == rb->s[j];
   hipStream_t st = rb->stream;
   k_set_rows<<<1, 64, 0, st>>>(rb->t_hdr, n);
   k_fill_i32<<<grid_of(rb->K * rb->t_gstride), 256, 0, st>>>(rb->t_gmap, 0, rb->K * rb->t_gstride);
@@ -925,89 +845,52 @@ int build_transpose(spconv_rulebook rb, const int32_t* coords, char* mem) {
   k_scatter_transpose<<<grid_of(rb->K * n), 256, 0, st>>>(rb->pairs, rb->pair_off,
                                                           static_cast<int>(rb->K), iperm,
                                                           rb->t_gmap, rb->t_gstride);
-  if (rb->t_single) {
-    const int64_t nchunks = rb->t_npad_cap / kSegRows + 1;
-    k_fill_i32<<<grid_of(rb->t_npad_cap), 256, 0, st>>>(rb->t_src, 0, rb->t_npad_cap);
-    k_fill_i32<<<grid_of(rb->t_npad_cap), 256, 0, st>>>(rb->t_dst, -1, rb->t_npad_cap);
-    k_chunk_layout<<<1, 64, 0, st>>>(rb->pair_off, static_cast<int>(rb->K), rb->t_chunk_off,
-                                     rb->t_hdrs);
-    k_seg_fill<<<grid_of(nchunks, 1ll << 30), 256, 0, st>>>(rb->t_chunk_off,
-                                                            static_cast<int>(rb->K), nchunks,
-                                                            rb->t_seg);
-    k_seg_scatter<<<grid_of(n), 256, 0, st>>>(rb->pairs, rb->pair_off, static_cast<int>(rb->K),
-                                              rb->t_chunk_off, rb->t_src, rb->t_dst);
-  }
   if (dev_free(rb, tmem, st) != SPCONV_OK) return SPCONV_EHIP;
   return hipGetLastError() == hipSuccess ? SPCONV_OK : SPCONV_EHIP;
 }
 
-// The transposed direction with f = s: one single-offset launch per R_i
-// (source rows pairs[.][1], destination rows pairs[.][0]), W^i sliced out of
-// w.  Needs the offsets' lengths on the host (the rule book is synchronised
-// once for that).  Returns kNotSingle, having launched nothing, when some
-// SC input row has no pair.
-int transpose_single(spconv_rulebook rb, int wmode, int in_dt, const void* x, const void* w,
-                     const float* bias, int out_dt, void* y, int C_in, int C_out,
-                     hipStream_t st) {
-  if (rb->h_pair_off.empty()) {
-    rb->h_pair_off.assign(static_cast<size_t>(rb->K + 1), 0);
-    if (hipMemcpyAsync(rb->h_pair_off.data(), rb->pair_off, (rb->K + 1) * sizeof(int64_t),
-                       hipMemcpyDeviceToHost, rb->stream) != hipSuccess ||
-        hipStreamSynchronize(rb->stream) != hipSuccess) {
-      (void)hipGetLastError();
-      rb->h_pair_off.clear();
-      return SPCONV_EHIP;
+// The reversed direction of an SC book (DC, the SC input gradient).  Where f =
+// s and every SC input row has its pair it runs over the pair lists.  The
+// extents may say so (t_direct); otherwise rows near the far border may lack
+// theirs (their output site falls off the SC grid), and the pair total tells
+// (read once, a wait).  All other books walk the transposed map.
+int reversed_view(spconv_rulebook rb, FwdView* out) {
+  bool paired = rb->t_direct;
+  if (!paired && rb->n_in > 0) {
+    paired = true;
+    for (int j = 1; j < rb->D; ++j) paired = paired && rb->f[j] == rb->s[j];
+  }
+  if (paired && !rb->t_direct) {
+    if (rb->h_total < 0) {
+      int64_t total = 0;
+      if (hipMemcpyAsync(&total, rb->pair_off + rb->K, sizeof(int64_t), hipMemcpyDeviceToHost,
+                         rb->stream) != hipSuccess ||
+          hipStreamSynchronize(rb->stream) != hipSuccess) {
+        (void)hipGetLastError();
+        return SPCONV_EHIP;
+      }
+      rb->h_total = total;
     }
+    paired = rb->h_total == rb->n_in;
   }
-  // rows near the far border may lack a pair (their output site falls off
-  // the SC grid); then not every destination row is written here
-  if (rb->h_pair_off[rb->K] != rb->n_in) return kNotSingle;
-  // one launch over all offsets when a matrix-core kernel fits the shape
-  FwdView sv;
-  sv.gmap = rb->t_src;
-  sv.perm = rb->t_dst;
-  sv.gstride = rb->t_npad_cap;
-  sv.hdr = rb->t_hdrs + rb->K;
-  sv.n_cap = rb->t_npad_cap;
-  sv.K = 1;
-  sv.n_src = rb->n_cap;
-  sv.seg = rb->t_seg;
-  const int r0 = forward_view(sv, wmode, in_dt, x, w, bias, out_dt, y, C_in, C_out, st);
-  if (r0 != kNotSingle) return r0;
-  // otherwise one launch per offset
-  const size_t esz = in_dt == SPCONV_BF16 ? 2 : 4;
-  int64_t chunk = 0;
-  for (int64_t i = 0; i < rb->K; ++i) {
-    const int64_t off = chunk * kSegRows, k_i = rb->h_pair_off[i + 1] - rb->h_pair_off[i];
-    chunk += (k_i + kSegRows - 1) / kSegRows;
-    if (k_i == 0) continue;
-    FwdView v;
-    v.gmap = rb->t_src + off;
-    v.perm = rb->t_dst + off;
-    v.gstride = k_i;
-    v.hdr = rb->t_hdrs + i;
-    v.n_cap = k_i;
-    v.K = 1;
-    v.n_src = rb->n_cap;
-    v.seg = nullptr;
-    const void* wi = static_cast<const char*>(w) + static_cast<size_t>(i) * C_in * C_out * esz;
-    const int r = forward_view(v, wmode, in_dt, x, wi, bias, out_dt, y, C_in, C_out, st);
-    if (r != SPCONV_OK) return r;
-  }
-  return SPCONV_OK;
-}
-
-FwdView transpose_view(spconv_rulebook rb) {
-  FwdView v;
-  v.gmap = rb->t_gmap;
-  v.perm = rb->t_perm;
-  v.gstride = rb->t_gstride;
-  v.hdr = rb->t_hdr;
+  FwdView v{};
   v.n_cap = rb->n_in;
-  v.K = rb->K;
   v.n_src = rb->n_cap;
-  v.seg = nullptr;
-  return v;
+  if (paired) {
+    v.hdr = rb->hdr;
+    v.K = 1;
+    v.pairs = rb->pairs;
+    v.pair_off = rb->pair_off;
+    v.pair_K = static_cast<int>(rb->K);
+  } else {
+    v.gmap = rb->t_gmap;
+    v.perm = rb->t_perm;
+    v.gstride = rb->t_gstride;
+    v.hdr = rb->t_hdr;
+    v.K = rb->K;
+  }
+  *out = v;
+  return SPCONV_OK;
 }
 
 size_t backward_weight_workspace(spconv_rulebook rb, int C_in, int C_out, int op) {

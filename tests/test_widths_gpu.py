@@ -26,7 +26,7 @@ WIDTHS = [(8, 8), (24, 40), (40, 24), (72, 136), (192, 96), (136, 264), (16, 20)
 
 
 # layer -> (extent, f): overlapping fields (the transposed map), f = s on extents the stride
-# divides (no transposed structure) and leaves a border of (the transposed lists and map)
+# divides (the pair lists) and leaves a border of, with sites there (the transposed map)
 SC_LAYERS = {"map": (24, 3), "direct": (24, 2), "border": (25, 2)}
 
 
