@@ -392,16 +392,23 @@ __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t o
 
 // LDS image of W^i transposed: one row per output column of the chunk, ROWB
 // bytes of k.  Rows whose length is a multiple of 128 bytes store 16-byte
-// chunk c at c ^ (row & 7) (measured conflict-free for the fragment reads,
-// where 16 lanes read one chunk of 16 consecutive rows; a 16-byte pad per
-// row, used for other lengths, leaves a 2-way conflict).
-template <int ROWB>
+// chunk c at c ^ swz(row), so that the fragment reads, where 8 lanes read one
+// chunk of 8 consecutive rows, fall on different banks.  fp32: also the 4-byte
+// writes of the staging, whose lanes hold every fourth row (TileCols): with row
+// & 7 eight of them met on a bank in tiles of 64 columns, now four (two in
+// smaller ones; 29,760 pen rows 64 -> 64 3^3 32.3 us, 30.0  now).  A 16-byte
+// pad per row, used for other lengths, leaves a 2-way conflict.
+template <typename TIn, int ROWB>
 struct WImage {
   static constexpr bool kSwz = ROWB % 128 == 0;
   static constexpr int kRowBytes = kSwz ? ROWB : ROWB + 16;
+  __device__ static int swz(int row) {
+    if constexpr (sizeof(TIn) == 2) return row & 7;
+    return (row ^ (row >> 3 & 1)) & 7;
+  }
   __device__ static int at(int row, int byte) {
     if constexpr (kSwz)
-      return row * kRowBytes + ((((byte >> 4) ^ (row & 7)) << 4) | (byte & 15));
+      return row * kRowBytes + ((((byte >> 4) ^ swz(row)) << 4) | (byte & 15));
     else
       return row * kRowBytes + byte;
   }
@@ -464,26 +471,47 @@ __device__ __forceinline__ float piece_elem(const u32x4& u, int e) {
   return __uint_as_float(e & 1 ? u[e / 2] & 0xffff0000u : u[e / 2] << 16);
 }
 
+// Which columns a lane of a tile of NCB blocks ends with: W^T is the first
+// operand of the products, so lane group g (lane / 16) holds, of row lane mod
+// 16 of each row block, the results of LDS rows 16 cb + 4 g .. + 3 of every
+// column block cb.  Runs of kRun adjacent columns are dealt to the four groups
+// in turn: all 4 NCB of a lane's columns; 16 bytes of them for fp32, so that one
+// store instruction writes 64 adjacent bytes of each of its 16 rows instead of
+// 16 bytes in every 64 (348,208 rows 64 -> 64 of one offset 49.2 us, 43.1  now;
+// bf16 stores 16 bytes in every 32 at most, and loses more registers than it
+// gains).
+template <typename TIn, typename TOut, int NCB>
+struct TileCols {
+  static constexpr int kRun = sizeof(TIn) == 4 && sizeof(TOut) == 4 ? 4 : 4 * NCB;
+  // LDS row of column n
+  __device__ static int row_of(int n) {
+    if constexpr (kRun == 4 * NCB) return n % kRun / 4 * 16 + n / kRun * 4 + n % 4;
+    const int q = n / (4 * kRun), g = n % (4 * kRun) / kRun, e = n % kRun;
+    return 16 * (q * (kRun / 4) + e / 4) + 4 * g + e % 4;
+  }
+  // of a lane's 4 NCB columns, the e-th: where it lies past the first
+  __device__ static constexpr int col(int e) { return e / kRun * 4 * kRun + e % kRun; }
+};
+
 // Epilogue of the matrix-core kernels: bias (scale, residual, ReLU), one
-// rounding, the store.  W^T was the first operand of the products, so a lane
-// holds LC = 4 NCB adjacent columns, from col0 + LC (lane / 16), of row lane
-// mod 16 of each block, and moves them in 16-byte pieces (x as the first
-// operand leaves NCB columns of four rows per lane: 4- to 8-byte pieces and
+// rounding, the store, in 16-byte pieces (x as the first operand of the
+// products leaves NCB columns of four rows per lane: 4- to 8-byte pieces and
 // four times the row numbers; the 2^3 stride-2 layer 32 -> 64 of 1,703,204
 // rows with its affine and ReLU fused took 102 us so, 78 us now; 902,504 rows
 // 64 -> 64 3^3, with 207 registers instead of 225, 302 and 293 us).
 // rowv: the output row of the wave's row map_lane (-1: none).  FULL: every
 // column of the tile exists; otherwise columns past C_out are dropped, and rows
 // that are no whole pieces go element by element.
-template <typename TOut, int RB, int NCB, bool FULL>
+template <typename TIn, typename TOut, int RB, int NCB, bool FULL>
 __device__ __forceinline__ void store_tile(const f32x4 (&acc)[RB][NCB], int32_t rowv,
                                            const float* bias, TOut* y, int C_out, int col0,
                                            int lg, const Epilogue& epi) {
   constexpr int LC = 4 * NCB;
   constexpr int P16 = 16 / static_cast<int>(sizeof(TOut));
+  using TC = TileCols<TIn, TOut, NCB>;
   constexpr int PC = LC < P16 ? LC : P16;         // (one block of bf16 columns: 8 bytes)
   constexpr int NP = LC / PC;
-  const int n0 = col0 + lg * LC;
+  const int n0 = col0 + lg * TC::kRun;            // the lane's e-th column: n0 + col(e)
   const bool whole = FULL || C_out % PC == 0;
   int32_t row[RB];
   spread_map<RB>(rowv, row);
@@ -496,7 +524,7 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[RB][NCB], int32_t 
     for (int b = 0; b < RB; ++b)
 #pragma unroll
       for (int q = 0; q < NP; ++q) {
-        const int n = n0 + q * PC;
+        const int n = n0 + TC::col(q * PC);
         const TOut* p = res + static_cast<int64_t>(row[b] >= 0 ? row[b] : 0) * C_out +
                         (FULL || n < C_out ? n : 0);
         if constexpr (PC == P16) {
@@ -510,7 +538,8 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[RB][NCB], int32_t 
   float bv[LC], sv[LC];
 #pragma unroll
   for (int e = 0; e < LC; ++e) {
-    const int n = FULL || n0 + e < C_out ? n0 + e : C_out - 1;
+    const int c = n0 + TC::col(e);
+    const int n = FULL || c < C_out ? c : C_out - 1;
     bv[e] = bias ? bias[n] : 0.0f;
     sv[e] = epi.scale ? epi.scale[n] : 1.0f;
   }
@@ -529,8 +558,8 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[RB][NCB], int32_t 
       for (int e = 0; e < LC; ++e) {
         if (whole)
           z[e] += piece_elem<TOut>(rv[b][e / PC], e % PC);
-        else if (n0 + e < C_out)
-          z[e] += ElemIO<TOut>::load(res, static_cast<int64_t>(row[b]) * C_out + n0 + e);
+        else if (n0 + TC::col(e) < C_out)
+          z[e] += ElemIO<TOut>::load(res, static_cast<int64_t>(row[b]) * C_out + n0 + TC::col(e));
       }
     }
     if (epi.relu) {
@@ -540,14 +569,15 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[RB][NCB], int32_t 
     if (whole) {
 #pragma unroll
       for (int q = 0; q < NP; ++q)
-        if (FULL || n0 + q * PC < C_out) {
-          if constexpr (PC == P16) store16(out + q * PC, z + q * PC);
-          else store4(out + q * PC, z + q * PC);
+        if (FULL || n0 + TC::col(q * PC) < C_out) {
+          if constexpr (PC == P16) store16(out + TC::col(q * PC), z + q * PC);
+          else store4(out + TC::col(q * PC), z + q * PC);
         }
     } else {
 #pragma unroll
       for (int e = 0; e < LC; ++e)
-        if (n0 + e < C_out) ElemIO<TOut>::store(out, e, z[e]);
+        if (n0 + TC::col(e) < C_out)
+          ElemIO<TOut>::store(out, TC::col(e), z[e]);
     }
   }
 }
@@ -628,8 +658,8 @@ __device__ __forceinline__ int unknown_minus_one() {
 // Lane layout (16x16 MFMA): lane l = 16 g + r.  Gathered rows (second operand):
 // row r of the 16-row block, k-chunk bytes [16 g, 16 g + 16).  W^T (first
 // operand): LDS row 16 cb + r of the chunk, same k bytes.  Result: lane l holds
-// row r's products with LDS rows 16 cb + 4 g + v (v = 0..3), which are the
-// columns 4 NCB g + 4 cb + v, so 4 NCB adjacent ones in all.
+// row r's products with LDS rows 16 cb + 4 g + v (v = 0..3), whose columns
+// TileCols says.
 //
 // Pipeline over the offsets (iteration i): G(i+3) and W^(i+2) are fetched,
 // gathered rows A(i+2) are issued (their gather-map entries G(i+2) arrived
@@ -666,7 +696,7 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
   constexpr int COLS = NCB * 16;
   constexpr int ESZ = static_cast<int>(sizeof(TIn));
   constexpr int ROWB = CIN * ESZ;                 // bytes of one input row
-  constexpr int LDWB = WImage<ROWB>::kRowBytes;   // LDS row of W^T (bytes)
+  constexpr int LDWB = WImage<TIn, ROWB>::kRowBytes;   // LDS row of W^T (bytes)
   // W^T staging tasks: bf16 takes 2 k-rows x 8 columns (packed in pairs),
   // fp32 1 k-row x 4 columns; each task is one 16-byte load per k-row.
   constexpr int KPT = ESZ == 2 ? 2 : 1;           // k-rows per task
@@ -750,10 +780,9 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
     }
   };
   // ---- registers -> LDS, transposed: one LDS row per column n holding
-  // W^i[k][n] for all k.  Column n = 4 NCB g + 4 cb + v (lane group g's) sits
-  // in LDS row 16 cb + 4 g + v; the lanes that read one fragment chunk together
-  // read 16 consecutive rows (spread over the banks by WImage).
-  auto w_row = [](int n) { return n % (4 * NCB) / 4 * 16 + n / (4 * NCB) * 4 + n % 4; };
+  // W^i[k][n] for all k (TileCols); the lanes that read one fragment chunk
+  // together read 16 consecutive rows (spread over the banks by WImage).
+  auto w_row = [](int n) { return TileCols<TIn, TOut, NCB>::row_of(n); };
   auto w_store = [&](int i, const WRegs& wr) {
     if (i >= K) return;
     unsigned char* dst = s_w[i & 1];
@@ -770,12 +799,12 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
               const uint32_t a = wr[q * KPT][j / 2], b = wr[q * KPT + 1][j / 2];
               const uint32_t v = (j & 1) ? ((a >> 16) | (b & 0xffff0000u))
                                          : ((a & 0xffffu) | (b << 16));
-              *reinterpret_cast<uint32_t*>(&dst[WImage<ROWB>::at(w_row(nt * 8 + j), kt * 4)]) = v;
+              *reinterpret_cast<uint32_t*>(&dst[WImage<TIn, ROWB>::at(w_row(nt * 8 + j), kt * 4)]) = v;
             }
           } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              *reinterpret_cast<uint32_t*>(&dst[WImage<ROWB>::at(w_row(nt * 4 + j), kt * 4)]) =
+              *reinterpret_cast<uint32_t*>(&dst[WImage<TIn, ROWB>::at(w_row(nt * 4 + j), kt * 4)]) =
                   wr[q][j];
           }
         }
@@ -786,7 +815,7 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
         const int t = threadIdx.x + q * 256;
         if (NTASK_T % 256 == 0 || t < NTASK_T) {
           const int n = t / CPR, kc = t % CPR;
-          *reinterpret_cast<u32x4*>(&dst[WImage<ROWB>::at(w_row(n), kc * 16)]) = wr[q];
+          *reinterpret_cast<u32x4*>(&dst[WImage<TIn, ROWB>::at(w_row(n), kc * 16)]) = wr[q];
         }
       }
     }
@@ -849,7 +878,7 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb)
         bw[cb] = *reinterpret_cast<const u32x4*>(
-            &sw[WImage<ROWB>::at(cb * 16 + lr, ch * 64 + lg * 16)]);
+            &sw[WImage<TIn, ROWB>::at(cb * 16 + lr, ch * 64 + lg * 16)]);
 #pragma unroll
       for (int b = 0; b < RB; ++b) {
         if (SKIP && !(pres & (1u << b))) continue;   // all 16 rows lack offset i
@@ -939,7 +968,7 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
   int32_t row = -1;
   if constexpr (PAIRS) row = pair_row(gmap, pt, static_cast<int>(map_row), 0);
   else if (map_row < n_rows) row = perm[map_row];
-  store_tile<TOut, RB, NCB, true>(acc, row, bias, y, C_out, col0, lg, epi);
+  store_tile<TIn, TOut, RB, NCB, true>(acc, row, bias, y, C_out, col0, lg, epi);
 }
 
 // ---------------------------------------------------------------------------

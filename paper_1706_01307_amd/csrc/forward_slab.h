@@ -61,7 +61,7 @@ __device__ __forceinline__ u32x4 buf_piece(__amdgpu_buffer_rsrc_t r, uint32_t of
 // LDS image, transposed as WImage describes.  WT 0: a task is KPT k-rows x one
 // 16-byte piece of columns (bf16 packs pairs of k-rows); WT 1 / 2 (w holds
 // W^T): one 16-byte piece of k of one column.
-template <typename TIn, int NCH, int NCB, int WT, bool AX, bool AW>
+template <typename TIn, typename TOut, int NCH, int NCB, int WT, bool AX, bool AW>
 struct WStage {
   static constexpr int ESZ = static_cast<int>(sizeof(TIn));
   static constexpr int EPP = 16 / ESZ;
@@ -99,10 +99,7 @@ struct WStage {
       }
     }
   }
-  // column n of the tile sits where k_fwd_mfma puts it
-  __device__ static int row_of(int n) {
-    return n % (4 * NCB) / 4 * 16 + n / (4 * NCB) * 4 + n % 4;
-  }
+  __device__ static int row_of(int n) { return TileCols<TIn, TOut, NCB>::row_of(n); }
   __device__ static void store(unsigned char* dst, const Regs& r) {
 #pragma unroll
     for (int q = 0; q < TPT; ++q) {
@@ -119,11 +116,11 @@ struct WStage {
           } else {
             v = r[q][j];
           }
-          *reinterpret_cast<uint32_t*>(&dst[WImage<ROWB>::at(row_of(nt * EPP + j), kt * 4)]) = v;
+          *reinterpret_cast<uint32_t*>(&dst[WImage<TIn, ROWB>::at(row_of(nt * EPP + j), kt * 4)]) = v;
         }
       } else {
         const int n = t / CPR, kc = t % CPR;
-        *reinterpret_cast<u32x4*>(&dst[WImage<ROWB>::at(row_of(n), kc * 16)]) = r[q];
+        *reinterpret_cast<u32x4*>(&dst[WImage<TIn, ROWB>::at(row_of(n), kc * 16)]) = r[q];
       }
     }
   }
@@ -183,7 +180,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
   constexpr int ESZ = static_cast<int>(sizeof(TIn));
   constexpr int EPP = 16 / ESZ;                   // elements per 16-byte piece
   constexpr int ROWB = SLAB * ESZ;                // bytes of one row's slab
-  constexpr int LDWB = WImage<ROWB>::kRowBytes;
+  constexpr int LDWB = WImage<TIn, ROWB>::kRowBytes;
   constexpr int WAVE_ROWS = RB * 16;
   constexpr int TILE_ROWS = 4 * WAVE_ROWS;
 
@@ -228,7 +225,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
     }
   };
 
-  using WS = WStage<TIn, NCH, NCB, WT, AX, AW>;
+  using WS = WStage<TIn, TOut, NCH, NCB, WT, AX, AW>;
   typedef typename WS::Regs WRegs;
   auto w_load = [&](At a, WRegs& r) {
     const int iv = PAIRS ? pt.i : (WT == 1 ? K - 1 - a.i : a.i);
@@ -281,7 +278,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb)
         bw[cb] = *reinterpret_cast<const u32x4*>(
-            &sw[WImage<ROWB>::at(cb * 16 + lr, ch * 64 + lg * 16)]);
+            &sw[WImage<TIn, ROWB>::at(cb * 16 + lr, ch * 64 + lg * 16)]);
 #pragma unroll
       for (int b = 0; b < RB; ++b) {
         if (!(pres & (1u << b))) continue;               // all 16 rows lack this offset
@@ -349,7 +346,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
     }
     row = map_row < n_rows ? perm[map_row] : -1;
   }
-  store_tile<TOut, RB, NCB, false>(acc, row, bias, y, C_out, col0, lg, epi);
+  store_tile<TIn, TOut, RB, NCB, false>(acc, row, bias, y, C_out, col0, lg, epi);
 }
 
 template <typename TIn, typename TOut, int WT, int NCH, int NCB, int RB, bool AX, bool AW>
