@@ -2596,10 +2596,8 @@ int build_vsc_grid(spconv_rulebook rb, const int32_t* coords, const GridGeom& g,
 // the output sites fills the output grid, whose occupancy gives the Z-order
 // schedule.  Everything that must start at zero (input grid; lexicographic
 // marks, output grid and, for a one-launch schedule, its bitmap) is laid out
-// in two ranges cleared by one launch, in one transient block; books for the
-// reversed direction take the input grid from a block of its own, so that
-// their builds make three allocations as those with transposed lists do (an
-// extra block costs an event on the build stream, ~2 us).
+// in two ranges cleared by one launch, in one transient block (a second block
+// costs an event on the build stream, ~2 us).
 int build_sc_grid(spconv_rulebook rb, const int32_t* coords, const GridGeom& gi,
                   uint64_t cells_in, const GridGeom& go, uint64_t cells_out) {
   const int64_t N = rb->n_in;
@@ -2612,21 +2610,14 @@ int build_sc_grid(spconv_rulebook rb, const int32_t* coords, const GridGeom& gi,
   // per cell, at most 64 a row, costs less than the atomics)
   const bool lself = lwords <= static_cast<uint64_t>(kSelfWords);
   const bool bytes = !lself && lex_cells <= 64ull * static_cast<uint64_t>(N);
-  const size_t in_bytes = align_up(cells_in * 4, 256);
-  const size_t out_bytes = align_up(lwords * 4, 256) +
-                           (bytes ? align_up(lwords * 32, 256) : 0) + grid_bytes(cells_out) +
-                           align_up(static_cast<size_t>(lnbw) * 4, 256) + 256;
-  const bool own = rb->t_direct;
-  void* mem_in = nullptr;
+  const size_t total = align_up(cells_in * 4, 256) + align_up(lwords * 4, 256) +
+                       (bytes ? align_up(lwords * 32, 256) : 0) + grid_bytes(cells_out) +
+                       align_up(static_cast<size_t>(lnbw) * 4, 256) + 256;
   void* mem = nullptr;
-  if (own && dev_alloc(rb, in_bytes, rb->stream, &mem_in) != SPCONV_OK) return SPCONV_ENOMEM;
-  if (dev_alloc(rb, out_bytes + (own ? 0 : in_bytes), rb->stream, &mem) != SPCONV_OK) {
-    (void)dev_free(rb, mem_in, rb->stream);
-    return SPCONV_ENOMEM;
-  }
+  if (dev_alloc(rb, total, rb->stream, &mem) != SPCONV_OK) return SPCONV_ENOMEM;
   Carver cv{static_cast<char*>(mem)};
   GridBufs bi{};
-  bi.grid = own ? static_cast<uint32_t*>(mem_in) : cv.take<uint32_t>(cells_in);
+  bi.grid = cv.take<uint32_t>(cells_in);
   uint32_t* lex_bits = bytes ? cv.take<uint32_t>(lwords) : nullptr;   // (written whole)
   uint32_t* lex = cv.take<uint32_t>(bytes ? 8 * lwords : lwords);     // bytes or bits, cleared
   const GridBufs bo = take_grid(&cv, cells_out, true);
@@ -2660,8 +2651,7 @@ int build_sc_grid(spconv_rulebook rb, const int32_t* coords, const GridGeom& gi,
       lex, lwords, lself ? nullptr : lsum, parts, cout, E, rb->out_coords, nullptr, og, rb->hdr);
   launch_grid_schedule(rb, bo, cells_out, -1, nullptr);
   launch_probe_grid(rb, rb->out_coords, gi, bi, cells_in);
-  const int f1 = dev_free(rb, mem, rb->stream), f2 = dev_free(rb, mem_in, rb->stream);
-  if (f1 != SPCONV_OK || f2 != SPCONV_OK) return SPCONV_EHIP;
+  if (dev_free(rb, mem, rb->stream) != SPCONV_OK) return SPCONV_EHIP;
   return hipGetLastError() == hipSuccess ? SPCONV_OK : SPCONV_EHIP;
 }
 }  // namespace

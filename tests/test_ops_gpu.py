@@ -394,10 +394,16 @@ def test_allocator_hook_results_and_balance():
     try:
         rb = spc.build_rulebook(spc.SC, _t(coords), size, [1, 2, 2, 2], [1, 2, 2, 2],
                                 transpose=True)
-        assert al.calls == 3 and len(al.live) == 1     # rule book; grids and sort buffers freed
+        calls = al.calls
+        assert len(al.live) == 1                       # the rule book; the grids' block given back
         y = spc.sc_forward(rb, _dev(x, "bf16"), _dev(w, "bf16"))
         dx = spc.backward_data(rb, spc.OP_SC, y, _dev(w, "bf16"))
         assert torch.equal(y, y_ref) and torch.equal(dx, dx_ref)
+        # f = s on extents the stride divides: nothing is built for the reversed direction, so
+        # nothing more is allocated
+        assert al.calls == calls
+        spc.build_rulebook(spc.SC, _t(coords), size, [1, 2, 2, 2], [1, 2, 2, 2]).close()
+        assert al.calls == 2 * calls
         rb.close()
         torch.cuda.synchronize()
         assert not al.live
@@ -407,12 +413,14 @@ def test_allocator_hook_results_and_balance():
 
 @pytest.mark.parametrize("fail_at", [1, 2, 3])
 def test_allocator_failure_is_enomem_without_leaks(fail_at):
+    # the rule book, the grids' block and, for overlapping fields, the transposed lists' buffers
     coords, size = _sites("pen")
+    f = [1, 3, 3] if fail_at == 3 else [1, 2, 2]
     al = _CountingTorchAllocator(fail_at)
     spc.set_allocator(al.alloc, al.release)
     try:
         with pytest.raises(spc.SpconvError) as e:
-            spc.build_rulebook(spc.SC, _t(coords), size, [1, 2, 2], [1, 2, 2], transpose=True)
+            spc.build_rulebook(spc.SC, _t(coords), size, f, [1, 2, 2], transpose=True)
         assert e.value.status == spc.ENOMEM
         torch.cuda.synchronize()
         assert not al.live
