@@ -53,8 +53,8 @@
 //   k_bitsum / k_bitscan / k_sc_emit
 //                rank the marked sites by a popcount prefix sum, which
 //                numbers the output rows in lexicographic order (small
-//                bitmaps: k_sc_emit alone; large ones on the grid path: marked
-//                as bytes, k_bytes_bits in place of k_bitsum); on the grid path
+//                bitmaps: k_sc_emit alone; on the grid path mostly marked as
+//                bytes, k_bytes_bits in place of k_bitsum); on the grid path
 //                the emission also fills the output grid
 //   then the schedule of the output sites (the output grid, or Morton codes
 //   and the sort), and probe / scan / compact on input site s*y + o.
@@ -1437,7 +1437,7 @@ __global__ __launch_bounds__(kBlock) void k_bitscan(uint32_t* __restrict__ bsum,
 // small bitmap enough blocks); its threads take the part's output sites in
 // turn: the word of site t by a search of the words' prefix, then the bit of
 // its rank inside the word, so a dense word costs no thread more than one
-// site and the sites' stores are consecutive (2^21 cells of 4 x 128^3, 505,281
+// site and the sites' stores are consecutive (2^23 cells of 4 x 128^3, 505,281
 // sites: 57 us with eight threads per word, 14 us now).  bbase = NULL (at most
 // kSelfWords words): every block counts the words before its bitmap block
 // itself, and the last bitmap block sets n_out, in place of k_bitsum and
@@ -2606,10 +2606,16 @@ int build_sc_grid(spconv_rulebook rb, const int32_t* coords, const GridGeom& gi,
   for (int j = 0; j < rb->D; ++j) lex_cells *= static_cast<uint64_t>(rb->out_size[j]);
   const uint64_t lwords = (lex_cells + 31) / 32;
   const int64_t lnbw = static_cast<int64_t>((lwords + kBlock - 1) / kBlock);
-  // large output grids are marked byte by byte (clearing and reading a byte
-  // per cell, at most 64 a row, costs less than the atomics)
+  // output grids of at most 64 cells a row are marked byte by byte: clearing and
+  // reading a byte per cell costs less than the atomics (in k_sc_scatter_mark).
+  // Not small ones with f = s, whose rounds find most bits set where the rows
+  // are ordered (93,423 rows of 4 x 64^3, 2^3 stride 2: 92 us a build in rounds,
+  // 98 by bytes); but where fields overlap (3^3 stride 2 there: 143 us with the
+  // bits, 120 by bytes; 119,255 ordered pen rows 5^2 stride 2: 161 and 124).
   const bool lself = lwords <= static_cast<uint64_t>(kSelfWords);
-  const bool bytes = !lself && lex_cells <= 64ull * static_cast<uint64_t>(N);
+  bool rounds = true;
+  for (int j = 1; j < rb->D; ++j) rounds = rounds && rb->f[j] == rb->s[j];
+  const bool bytes = !(lself && rounds) && lex_cells <= 64ull * static_cast<uint64_t>(N);
   const size_t total = align_up(cells_in * 4, 256) + align_up(lwords * 4, 256) +
                        (bytes ? align_up(lwords * 32, 256) : 0) + grid_bytes(cells_out) +
                        align_up(static_cast<size_t>(lnbw) * 4, 256) + 256;
@@ -2629,8 +2635,6 @@ int build_sc_grid(spconv_rulebook rb, const int32_t* coords, const GridGeom& gi,
   const OffsetTable ot = make_offsets(rb);
   // a book on another book's outputs keeps its own copy of their count
   int64_t* cc = rb->in_count ? rb->n_in_dev : nullptr;
-  bool rounds = true;
-  for (int j = 1; j < rb->D; ++j) rounds = rounds && rb->f[j] == rb->s[j];
   auto mark = bytes ? k_sc_scatter_mark<kMarkBytes>
                     : (rounds ? k_sc_scatter_mark<kMarkRounds> : k_sc_scatter_mark<kMarkFan>);
   mark<<<grid_for(N), kBlock, 0, rb->stream>>>(
