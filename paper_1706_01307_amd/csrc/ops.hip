@@ -35,6 +35,8 @@
 // adds the chunks of every entry in ascending chunk order.  The bias
 // gradient sums the output-gradient rows in fixed row chunks the same way.
 // No atomics anywhere: results are bitwise reproducible.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace spc {
@@ -298,7 +300,7 @@ typedef float dw_f16 __attribute__((ext_vector_type(16)));
 typedef unsigned dw_u4 __attribute__((ext_vector_type(4)));
 
 // Element types: KS pairs per product; frag() reads channels c0 .. c0 + 31 of
-// pairs p0 .. p0 + KS - 1 from a tile of W-channel rows; swz() places 16-byte
+// pairs p0 .. p0 + KS - 1 from a tile of W-channel rows; at() places 16-byte
 // piece k of row r so that the rows of one read fall on different banks
 // (256-byte bank period; narrow tiles are contiguous there already).
 template <typename T> struct Dw;
@@ -716,18 +718,27 @@ __global__ __launch_bounds__(256) void k_db_partial(const T* __restrict__ dy, in
 
 
 // How the output positions are cut into partials: bpc blocks of kBlock
-// positions each.  16 blocks (4096 positions: a row the K offsets share comes
-// back while it is in L2), fewer while that leaves the device short of
-// workgroups (4096: four rounds of four per compute unit; 2048 left the fp32
-// layer above 20 us slower, 16,384 gained nothing) and the partials
-// stay small (29,760 pen-stroke rows 32 x 32 fp32 3x3 have 72 workgroups of
-// 4096 positions, 1,053 of 256).  The row count is the host's best knowledge,
-// so a book's plan may change when it is synchronised; the workspace query
-// and the gradient both synchronise first.
+// positions each, at most 16 (4096 positions: a row the K offsets share comes
+// back while it is in L2).  Fewer shorten the steps of the fullest chunk, which
+// bound layers with few chunks; more keep the partials small, which are written
+// and read once.  The plan takes the bpc whose estimate is least (us; fitted to
+// 712 layers of 490 to 345,353 rows, 1 to 27 offsets, both types, every bpc
+// timed: within 2.3 % of each layer's best on average, where halving bpc until
+// 4096 workgroups were reached was 8 % off; 345,353 rows K = 1 bf16 128 -> 128:
+// 44 / 66 us with 8 / 4 blocks; 48,184 rows of a strided 3^3 24 -> 40: 22 / 37
+// with 8 / 1; 3,305 pen rows 3^2 fp32 24 -> 40: 14 / 87 with 1 / 16), below 16
+// only while the partials stay within 32 MB.
+//   fill     pairs per offset and output position: n_in / (n_out prod s) of an
+//            SC book; half the offsets other than the centre of a VSC book
+//   step     one step of kSub pairs; the narrower tiles' is 0.3 of it
+//   750      workgroups at work at a time
+// The row counts are the host's best knowledge, so a book's plan may change
+// when it is synchronised; the workspace query and the gradient both
+// synchronise first.
 struct DwPlan {
   int nchunk, bpc, tc, tn;
 };
-DwPlan dw_plan(spconv_rulebook rb, int C_in, int C_out) {
+DwPlan dw_plan(spconv_rulebook rb, int dt, int C_in, int C_out) {
   DwPlan p;
   p.tc = C_in <= 32 ? 32 : 64;
   p.tn = C_out <= 32 ? 32 : 64;
@@ -736,10 +747,34 @@ DwPlan dw_plan(spconv_rulebook rb, int C_in, int C_out) {
   const int64_t tiles = static_cast<int64_t>((C_in + p.tc - 1) / p.tc) *
                         ((C_out + p.tn - 1) / p.tn);
   const int64_t per = 4ll * C_in * C_out * rb->K;        // bytes of one chunk's partials
+  double strides = 1.0;
+  for (int j = 1; j < rb->D; ++j) strides *= rb->s[j];
+  const bool vsc = rb->kind == SPCONV_VSC;
+  const double full = vsc || rows == 0 ? 1.0
+                                       : std::min(1.0, static_cast<double>(rb->n_in) /
+                                                           (strides * static_cast<double>(rows)));
+  const double fill = vsc && rb->K > 1 ? 0.5 : full;
+  const double step = (dt == SPCONV_F32 ? 3.0 : 0.57) * (p.tc + p.tn == 128 ? 1.0 : 0.3);
+  // chunks that one thread of the reduction adds in turn (see its launch)
+  const double segs = std::min(8.0, std::max(1.0, 131072.0 * 4.0 / static_cast<double>(per)));
+  constexpr double kSteps = static_cast<double>(kBlock) / kSub;     // of a full block
   p.bpc = 16;
-  while (p.bpc > 1 && rb->K * tiles * ((nblk + p.bpc - 1) / p.bpc) < 4096 &&
-         per * ((nblk + p.bpc / 2 - 1) / (p.bpc / 2)) <= (32ll << 20))
-    p.bpc /= 2;
+  double best = 0.0;
+  for (int b = 16; b >= 1; b /= 2) {
+    const int64_t nchunk = (nblk + b - 1) / b;
+    if (b < 16 && per * nchunk > (32ll << 20)) break;
+    const double blocks = static_cast<double>(std::min<int64_t>(b, nblk));
+    const double nc = static_cast<double>(nchunk);
+    const double chain = kSteps * blocks * full * step;
+    const double work = static_cast<double>(rb->K * tiles) * nc *
+                        std::max(2.35, kSteps * blocks * fill) * step / 750.0;
+    const double t = std::max(chain, work) + 0.33 * std::min(chain, work) +
+                     0.37e-6 * static_cast<double>(per) * nc + 0.068 * nc / segs;
+    if (b == 16 || t < best) {
+      best = t;
+      p.bpc = b;
+    }
+  }
   p.nchunk = static_cast<int>((nblk + p.bpc - 1) / p.bpc);
   return p;
 }
@@ -896,7 +931,9 @@ int reversed_view(spconv_rulebook rb, FwdView* out) {
 size_t backward_weight_workspace(spconv_rulebook rb, int C_in, int C_out, int op) {
   const int64_t rows = op == SPCONV_OP_DC ? rb->n_in : rb->n_cap;
   const int64_t nrc = (rows + kRowChunk - 1) / kRowChunk;
-  const int64_t nchunk = dw_plan(rb, C_in, C_out).nchunk;
+  // the query does not name the type: room for either plan
+  const int64_t nchunk = std::max(dw_plan(rb, SPCONV_F32, C_in, C_out).nchunk,
+                                  dw_plan(rb, SPCONV_BF16, C_in, C_out).nchunk);
   const int64_t nb = nrc > nchunk ? nrc : nchunk;      // rows of the bias partials
   return static_cast<size_t>(rb->K * nchunk) * C_in * C_out * 4 +
          static_cast<size_t>(nb > 0 ? nb : 1) * C_out * 4 + 256;
@@ -904,7 +941,7 @@ size_t backward_weight_workspace(spconv_rulebook rb, int C_in, int C_out, int op
 
 int backward_weight(spconv_rulebook rb, int op, int dt, const void* x, const void* dy, float* dw,
                     float* db, int C_in, int C_out, void* ws, hipStream_t st) {
-  const DwPlan plan = dw_plan(rb, C_in, C_out);
+  const DwPlan plan = dw_plan(rb, dt, C_in, C_out);
   const int nchunk = plan.nchunk;
   const int K = static_cast<int>(rb->K);
   float* part = static_cast<float*>(ws);
