@@ -109,16 +109,16 @@ def forward_kernel(c_in, c_out, bf16, n):
     library's own dispatch rule): the matrix cores for bf16 C_in of 32 / 64 /
     96 / 128 or fp32 C_in of 16 ... 128 with C_out a multiple of 16, else the
     one-plane-group kernel for at most 4 input planes on at least 2048 rows
-    (C_out a multiple of 16), else one lane per output element for few planes on
-    both sides or at most 4 input planes on few rows, else the matrix cores in
-    slabs of channels."""
+    (C_out a multiple of 16), else one lane per output element or the matrix
+    cores in slabs of channels, whichever the library estimates to finish first:
+    the former for at most 4 planes on fewer rows, the only layer of this kind
+    among the workloads."""
     mfma_cin = (32, 64, 96, 128) if bf16 else (16, 32, 64, 96, 128)
     if c_out % 16 == 0 and c_in in mfma_cin:
         return "k_fwd_mfma"
     if c_in <= 4 and n >= 2048 and c_out % 16 == 0:
         return "k_fwd_lowc"
-    narrow = c_in <= 16 and c_out * (c_in + 2) < (48 if bf16 else 80)
-    return "k_fwd_vec" if narrow or (c_in <= 4 and n < 2048) else "k_fwd_slab"
+    return "k_fwd_vec" if c_in <= 4 and n < 2048 else "k_fwd_vec or k_fwd_slab"
 
 
 def cpu_baseline(wl, x_bits, w_bits, bias, n_samples):

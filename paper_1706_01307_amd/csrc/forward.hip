@@ -15,6 +15,7 @@ FwdView view_of(spconv_rulebook rb) {
   v.hdr = rb->hdr;
   v.n_cap = rb->n_cap;
   v.K = rb->K;
+  v.K_row = rb->K;
   v.n_src = rb->n_in;
   return v;
 }

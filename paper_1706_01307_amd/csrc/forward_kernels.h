@@ -25,11 +25,13 @@
 //               FMA chains, weights through the scalar cache.
 //   k_fwd_slab  (forward_slab.h) any other channel count on the matrix cores,
 //               rows walked in slabs of channels.
-//   k_fwd_vec   few input planes on small layers, or operands past the
-//               buffer range: one lane per (output row, output column), fp32
-//               FMA chain.
+//   k_fwd_vec   layers that it finishes before k_fwd_slab (vec_first), or
+//               operands past the buffer range: one lane per (output row,
+//               output column), fp32 FMA chain.
 #pragma once
 
+#include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 
@@ -45,10 +47,11 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kWave = 64;
 
 // Test knob: SPCONV_FORCE_PATH=vec runs the vector path for shapes the
-// matrix-core kernel covers.
-bool force_vector_path() {
+// matrix-core path would take; =slab runs k_fwd_slab for shapes that k_fwd_vec
+// is estimated to finish first.
+bool forced_path(const char* name) {
   const char* e = std::getenv("SPCONV_FORCE_PATH");
-  return e && std::strcmp(e, "vec") == 0;
+  return e && std::strcmp(e, name) == 0;
 }
 
 constexpr uint32_t kBufDword3 = 0x00020000u;   // gfx9 raw buffer descriptor word 3
@@ -1108,6 +1111,56 @@ constexpr auto slab_entry() {
   else return sizeof(TOut) == 4 ? forward_slab_bf : forward_slab_bb;
 }
 
+// Which of k_fwd_vec and k_fwd_slab finishes a layer first, by what each one's
+// time goes with (us; one set of constants for all sizes, fitted to both kernels
+// on 3,996 layers: 400 to 345,353 rows, 9 to 27 offsets, 1 to 96 planes to 1 to
+// 128, both types: the kernel taken is at most 10 % slower than the other in
+// 97 % of them, 1.7 times at worst).
+//   k_fwd_vec   a serial chain of K' C_in multiply-adds per column, or, where
+//               the lanes fill the device, rows x K' x C_out x (C_in + 2), and
+//               twice that for inputs past an XCD's 4 MB of L2; K' the offsets
+//               that one row can have (all K, but every s-th of each
+//               dimension in the reversed direction of a strided layer: 3^3
+//               stride 2 8 of 27, 345,353 rows bf16 12 -> 4: 48 / 174).
+//   k_fwd_slab  K steps per k-chunk of channels: a step's latency where the
+//               tiles fit the device at once, else rows x column tiles; both
+//               nearly double for rows that are no whole 16-byte pieces, and
+//               grow with the columns per tile of those that are.
+// Measured (vec / slab us): few rows make the chain the shorter one (400 rows,
+// 25 offsets, fp32 8 -> 128: 15 / 34; bf16 5 -> 10: 12 / 25; 21,774 surface
+// rows 3^3 bf16 3 -> 10: 14 / 31), as do few columns of few planes (400,000
+// rows fp32 1 -> 8: 68 / 200); whole pieces or more columns the matrix cores
+// (345,353 rows fp32 16 -> 4: 255 / 97, 8 -> 16: 421 / 97; 400 rows, 9 offsets
+// 32 -> 24: 27 / 8).
+template <typename TIn>
+inline bool vec_first(const FwdView& v, int C_in, int C_out, uint64_t x_bytes,
+                      bool w_rows_whole) {
+  constexpr bool f32 = sizeof(TIn) == 4;
+  constexpr int P = 16 / static_cast<int>(sizeof(TIn));
+  // (n_cap is a loose bound on the rows of an SC book whose filter exceeds its
+  // stride, see launch_slab_cols)
+  const double n = static_cast<double>(v.n_src > 0 ? std::min(v.n_src, v.n_cap) : v.n_cap);
+  const double k = static_cast<double>(v.K), kr = static_cast<double>(v.K_row);
+  const double chain = std::max(5.0, 0.085 * kr * C_in);
+  const double lanes = (x_bytes > (4u << 20) ? 5.5e-7 : 2.7e-7) * n * kr * C_out * (C_in + 2.0);
+  const bool ax = C_in % P == 0;
+  double latency, rate;                    // us per step; us per step, row and column tile
+  int col_tiles;
+  if (ax && w_rows_whole) {
+    const int cb = (C_out + 15) / 16, chunks = (cb + 7) / 8, ncb = (cb + chunks - 1) / chunks;
+    const double wide = ncb <= 2 ? 1.0 : ncb <= 4 ? (f32 ? 1.3 : 1.1) : (f32 ? 3.5 : 2.0);
+    latency = (f32 ? 0.56 : 0.35) * wide;
+    rate = (f32 ? 9.6e-6 : 6.3e-6) * wide;
+    col_tiles = chunks;
+  } else {
+    latency = f32 ? 0.77 : ax ? 0.84 : 0.9;
+    rate = f32 ? 2.1e-5 : ax ? 1.35e-5 : 1.45e-5 * (1.0 + 0.025 * C_in);
+    col_tiles = (C_out + 63) / 64;
+  }
+  const double steps = k * ((C_in + MT<TIn>::KC - 1) / MT<TIn>::KC);
+  return 3.0 + std::hypot(chain, lanes) <= 4.2 + steps * std::max(latency, rate * n * col_tiles);
+}
+
 // Channel counts k_fwd_mfma is not compiled for.
 template <typename TIn, typename TOut, int WT>
 void launch_generic(const Call& c, int C_in) {
@@ -1117,31 +1170,21 @@ void launch_generic(const Call& c, int C_in) {
   // one-lane-per-column kernel finishes first (measured: 460 rows of 16
   // columns 6.1 us against 7.7 us; 29759 rows of 32 columns 16.4 us against
   // 12.7 us).
-  // So it does before the slab kernel wherever few columns leave the slabs
-  // and column tiles mostly padding: its time goes with rows x K x C_out x
-  // (C_in + 2), the slab kernel's with rows x K (400,000 surface rows 3^3:
-  // 1 -> 8 fp32 68 against 200 us, 1 -> 24 192 / 202, 1 -> 33 266 / 224, 4 -> 5
-  // 161 / 202; bf16 1 -> 8 102 / 117, 1 -> 24 277 / 120), and on layers small
-  // enough to be bound by latency (3,200 rows 3x3, 4 -> 100: 8 against 16 us;
-  // 29,760 rows 1 -> 33: 14 / 16, 1 -> 100: 35 / 20).
   constexpr int64_t kLowMinRows = 2048;
   const uint64_t xb = static_cast<uint64_t>(c.v.n_src) * C_in * sizeof(TIn);
   const bool by_pairs = c.v.pair_off != nullptr;
   const uint64_t wb =
       static_cast<uint64_t>(by_pairs ? c.v.pair_K : c.v.K) * C_in * c.C_out * sizeof(TIn);
   const bool fits = xb < kBufOOB && static_cast<uint64_t>(c.v.gstride) * 4 < kBufOOB;
-  const bool few = C_in <= kLowCin;
-  if (!by_pairs && few && fits && c.v.n_cap >= kLowMinRows && c.C_out % kLowCols == 0 &&
-      c.C_out / kLowCols <= 65535) {
+  if (!by_pairs && C_in <= kLowCin && fits && c.v.n_cap >= kLowMinRows &&
+      c.C_out % kLowCols == 0 && c.C_out / kLowCols <= 65535) {
     launch_lowc<TIn, TOut, WT>(c, C_in, static_cast<uint32_t>(xb));
     return;
   }
   const bool wfits = wb < kBufOOB && c.C_out <= kMaxTileCols;
-  const int64_t cols = static_cast<int64_t>(c.C_out) * (C_in + 2);
-  const bool narrow = (C_in <= 16 && cols < (sizeof(TIn) == 4 ? 80 : 48)) ||
-                      (few && c.v.n_cap * c.v.K * cols < 27000000);
-  if ((by_pairs || !(narrow || (few && c.v.n_cap < kLowMinRows))) && fits && wfits &&
-      !force_vector_path()) {
+  const bool w_whole = WT != 0 || c.C_out % (16 / static_cast<int>(sizeof(TIn))) == 0;
+  if (fits && wfits && !forced_path("vec") &&
+      (by_pairs || forced_path("slab") || !vec_first<TIn>(c.v, C_in, c.C_out, xb, w_whole))) {
     Call cc = c;
     cc.x_bytes = static_cast<uint32_t>(xb);
     slab_entry<TIn, TOut>()(cc, WT, C_in, static_cast<uint32_t>(wb));
@@ -1153,7 +1196,7 @@ void launch_generic(const Call& c, int C_in) {
 template <int WT>
 void run(const Call& c, int in_dt, int out_dt, int C_in) {
   bool done = false;
-  if (!force_vector_path()) {
+  if (!forced_path("vec")) {
     done = out_dt == SPCONV_F32 ? try_mfma<float, WT>(c, in_dt, C_in)
                                 : try_mfma<uint16_t, WT>(c, in_dt, C_in);
   }

@@ -25,6 +25,7 @@ struct FwdView {
   const DeviceHeader* hdr;
   int64_t n_cap;
   int64_t K;
+  int64_t K_row;               // offsets one row can have at most
   int64_t n_src;
   // Pair views (K = 1; pair_off not NULL): instead of a map, pair e of offset
   // i < pair_K, pairs[pair_off[i] + e] = (input row, output row), adds row

@@ -914,6 +914,7 @@ int reversed_view(spconv_rulebook rb, FwdView* out) {
   if (paired) {
     v.hdr = rb->hdr;
     v.K = 1;
+    v.K_row = 1;
     v.pairs = rb->pairs;
     v.pair_off = rb->pair_off;
     v.pair_K = static_cast<int>(rb->K);
@@ -923,6 +924,8 @@ int reversed_view(spconv_rulebook rb, FwdView* out) {
     v.gstride = rb->t_gstride;
     v.hdr = rb->t_hdr;
     v.K = rb->K;
+    v.K_row = 1;                          // an input row's class takes every s-th offset
+    for (int j = 1; j < rb->D; ++j) v.K_row *= (rb->f[j] + rb->s[j] - 1) / rb->s[j];
   }
   *out = v;
   return SPCONV_OK;

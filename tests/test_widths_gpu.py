@@ -108,6 +108,32 @@ def test_many_rows_reversed(ci, co, dtype):
     check_features(_to_np(dx), dxo, ad, rtol, "dx")
 
 
+@pytest.mark.parametrize("path", ["slab", "vec"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("op,layer", [("vsc", ""), ("sc", "map"), ("dc", "map")])
+@pytest.mark.parametrize("ci,co", [(8, 8), (24, 40), (31, 33), (65, 16), (5, 3), (48, 1),
+                                   (12, 100), (129, 8)])
+def test_either_kernel(monkeypatch, op, layer, ci, co, dtype, path):
+    """The matrix cores' slabs and one lane per column, whichever of them the dispatch takes for
+    these layers: forward and input gradient."""
+    monkeypatch.setenv("SPCONV_FORCE_PATH", path)
+    coords, size, f, s = _layer(op, layer)
+    kind = spc.VSC if op == "vsc" else spc.SC
+    rb = spc.build_rulebook(kind, _t(coords), size, f, s, transpose=op != "vsc")
+    ref = oracle.Rulebook(kind, coords, size, f, s)
+    rin, rout = (ref.n_out, ref.n_in) if op == "dc" else (ref.n_in, ref.n_out)
+    x, dy = _feats(rin, ci, dtype, 1), _feats(rout, co, dtype, 2)
+    w = _feats(ref.K * ci, co, dtype, 3, std=1.0 / np.sqrt(ref.K * ci)).reshape(ref.K, ci, co)
+    b = inputs.normal_f32((co,), std=0.1, seed=4)
+    rtol = RTOL_F32 if dtype == "f32" else RTOL_BF16
+    fwd = {"vsc": spc.vsc_forward, "sc": spc.sc_forward, "dc": spc.dc_forward}[op]
+    yo, ab = (ref.dc_forward if op == "dc" else ref.forward)(x, w, b, in_dt=_odt(dtype))
+    check_features(_to_np(fwd(rb, _dev(x, dtype), _dev(w, dtype), _t(b))), yo, ab, rtol, "y")
+    dxo, ad = ref.backward_data(OP[op][1], dy, w, _odt(dtype))
+    dx = spc.backward_data(rb, OP[op][0], _dev(dy, dtype), _dev(w, dtype))
+    check_features(_to_np(dx), dxo, ad, rtol, "dx")
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_reversed_on_the_vector_path(monkeypatch, dtype):
     """The f = s reversed direction without the matrix cores gives the same results within the
