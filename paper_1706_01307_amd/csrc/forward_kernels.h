@@ -396,17 +396,19 @@ __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t o
 // LDS image of W^i transposed: one row per output column of the chunk, ROWB
 // bytes of k.  Rows whose length is a multiple of 128 bytes store 16-byte
 // chunk c at c ^ swz(row), so that the fragment reads, where 8 lanes read one
-// chunk of 8 consecutive rows, fall on different banks.  fp32: also the 4-byte
-// writes of the staging, whose lanes hold every fourth row (TileCols): with row
-// & 7 eight of them met on a bank in tiles of 64 columns, now four (two in
-// smaller ones; 29,760 pen rows 64 -> 64 3^3 32.3 us, 30.0  now).  A 16-byte
-// pad per row, used for other lengths, leaves a 2-way conflict.
+// chunk of 8 consecutive rows, fall on different banks.  fp32 and 128 bf16
+// planes: also the 4-byte writes of the staging, whose lanes hold every fourth
+// row (TileCols): with row & 7 twice as many met on a bank, in fp32 tiles of 64
+// columns eight, now four (29,760 pen rows 64 -> 64 3^3 32.3 us, 30.0 now;
+// strided 3^3 of 345,353 rows, 128 -> 128 bf16: 163.6 and 150.2).  Not 64 bf16
+// planes, whose kernel needs its registers for a third workgroup (kNear).  A
+// 16-byte pad per row, used for other lengths, leaves a 2-way conflict.
 template <typename TIn, int ROWB>
 struct WImage {
   static constexpr bool kSwz = ROWB % 128 == 0;
   static constexpr int kRowBytes = kSwz ? ROWB : ROWB + 16;
   __device__ static int swz(int row) {
-    if constexpr (sizeof(TIn) == 2) return row & 7;
+    if constexpr (sizeof(TIn) == 2 && ROWB < 256) return row & 7;
     return (row ^ (row >> 3 & 1)) & 7;
   }
   __device__ static int at(int row, int byte) {
