@@ -396,26 +396,35 @@ __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t o
 // LDS image of W^i transposed: one row per output column of the chunk, ROWB
 // bytes of k.  Rows whose length is a multiple of 128 bytes store 16-byte
 // chunk c at c ^ swz(row), so that the fragment reads, where 8 lanes read one
-// chunk of 8 consecutive rows, fall on different banks.  fp32 and 128 bf16
-// planes: also the 4-byte writes of the staging, whose lanes hold every fourth
-// row (TileCols): with row & 7 twice as many met on a bank, in fp32 tiles of 64
-// columns eight, now four (29,760 pen rows 64 -> 64 3^3 32.3 us, 30.0 now;
-// strided 3^3 of 345,353 rows, 128 -> 128 bf16: 163.6 and 150.2).  Not 64 bf16
-// planes, whose kernel needs its registers for a third workgroup (kNear).  A
-// 16-byte pad per row, used for other lengths, leaves a 2-way conflict.
+// chunk of 8 consecutive rows, fall on different banks; a 16-byte pad per row,
+// used for other lengths, leaves them a 2-way conflict.  The 4-byte writes of
+// the staging come from lanes that hold every fourth row of one or of several
+// blocks of 16 (TileCols): with row & 7 alone up to eight of them met on a bank.
+// fp32: swz also takes the row's fourth bit and every block of 16 rows is
+// shifted by half the banks (a quarter for a padded row) and a chunk, which
+// costs the reads nothing: no two meet (16 -> 64 planes 5^2 3,305 pen rows 17.5
+// -> 15.8 us, 29,760 rows 64 -> 64 3^3 32.3 -> 29.0).  128 bf16 planes: the bit
+// alone, two meet (strided 3^3 of 345,353 rows, 128 -> 128: 163.6 -> 150.2 us).
+// Fewer bf16 planes keep row & 7: 64 of them need their registers for a third
+// workgroup (kNear), and 32 -> 64 5^2 lost 6 % by the shifts.
 template <typename TIn, int ROWB>
 struct WImage {
   static constexpr bool kSwz = ROWB % 128 == 0;
   static constexpr int kRowBytes = kSwz ? ROWB : ROWB + 16;
   __device__ static int swz(int row) {
-    if constexpr (sizeof(TIn) == 2 && ROWB < 256) return row & 7;
-    return (row ^ (row >> 3 & 1)) & 7;
+    if constexpr (sizeof(TIn) == 4) return (row ^ (row >> 3 & 1) << 1) & 7;
+    return ROWB < 256 ? row & 7 : (row ^ (row >> 3 & 1)) & 7;
   }
+  __host__ __device__ static constexpr int shift(int block) {
+    return sizeof(TIn) == 4 ? (kSwz ? 128 : 32) * block + 16 * (block >> 1) : 0;
+  }
+  static constexpr int bytes(int rows) { return rows * kRowBytes + shift(rows / 16 - 1); }
   __device__ static int at(int row, int byte) {
+    const int base = row * kRowBytes + shift(row >> 4);
     if constexpr (kSwz)
-      return row * kRowBytes + ((((byte >> 4) ^ swz(row)) << 4) | (byte & 15));
+      return base + ((((byte >> 4) ^ swz(row)) << 4) | (byte & 15));
     else
-      return row * kRowBytes + byte;
+      return base + byte;
   }
 };
 
@@ -701,7 +710,6 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
   constexpr int COLS = NCB * 16;
   constexpr int ESZ = static_cast<int>(sizeof(TIn));
   constexpr int ROWB = CIN * ESZ;                 // bytes of one input row
-  constexpr int LDWB = WImage<TIn, ROWB>::kRowBytes;   // LDS row of W^T (bytes)
   // W^T staging tasks: bf16 takes 2 k-rows x 8 columns (packed in pairs),
   // fp32 1 k-row x 4 columns; each task is one 16-byte load per k-row.
   constexpr int KPT = ESZ == 2 ? 2 : 1;           // k-rows per task
@@ -711,7 +719,7 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
   constexpr int WAVE_ROWS = RB * 16;
   constexpr int TILE_ROWS = 4 * WAVE_ROWS;
 
-  __shared__ __attribute__((aligned(16))) unsigned char s_w[2][COLS * LDWB];
+  __shared__ __attribute__((aligned(16))) unsigned char s_w[2][WImage<TIn, ROWB>::bytes(COLS)];
 
   // XCD-aware tile order: workgroup b runs on XCD b % 8; give each XCD a
   // contiguous range of tiles so neighbouring tiles share that XCD's L2.  The

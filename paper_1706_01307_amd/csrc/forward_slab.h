@@ -180,11 +180,10 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
   constexpr int ESZ = static_cast<int>(sizeof(TIn));
   constexpr int EPP = 16 / ESZ;                   // elements per 16-byte piece
   constexpr int ROWB = SLAB * ESZ;                // bytes of one row's slab
-  constexpr int LDWB = WImage<TIn, ROWB>::kRowBytes;
   constexpr int WAVE_ROWS = RB * 16;
   constexpr int TILE_ROWS = 4 * WAVE_ROWS;
 
-  __shared__ __attribute__((aligned(16))) unsigned char s_w[2][COLS * LDWB];
+  __shared__ __attribute__((aligned(16))) unsigned char s_w[2][WImage<TIn, ROWB>::bytes(COLS)];
 
   // XCD-contiguous tile ranges over the device-side row count, as k_fwd_mfma
   PairTile pt{0, 0, 0};
