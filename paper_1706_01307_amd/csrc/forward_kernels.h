@@ -1125,47 +1125,54 @@ constexpr auto slab_entry() {
 // time goes with (us; one set of constants for all sizes, fitted to both kernels
 // on 3,996 layers: 400 to 345,353 rows, 9 to 27 offsets, 1 to 96 planes to 1 to
 // 128, both types: the kernel taken is at most 10 % slower than the other in
-// 97 % of them, 1.7 times at worst).
+// 98 % of them).
 //   k_fwd_vec   a serial chain of K' C_in multiply-adds per column, or, where
-//               the lanes fill the device, rows x K' x C_out x (C_in + 2), and
-//               twice that for inputs past an XCD's 4 MB of L2; K' the offsets
-//               that one row can have (all K, but every s-th of each
-//               dimension in the reversed direction of a strided layer: 3^3
-//               stride 2 8 of 27, 345,353 rows bf16 12 -> 4: 48 / 174).
+//               the lanes fill the device, rows x C_out x (K' C_in + 2 K), and
+//               twice that for inputs past an XCD's 4 MB of L2; as for up to
+//               four columns where fewer share a row's loads.  K': the offsets
+//               that one row can have, all K but in the reversed direction of a
+//               strided layer (3^3 stride 2: 8 of 27).
 //   k_fwd_slab  K steps per k-chunk of channels: a step's latency where the
-//               tiles fit the device at once, else rows x column tiles; both
-//               nearly double for rows that are no whole 16-byte pieces, and
-//               grow with the columns per tile of those that are.
+//               tiles fit the device at once, else rows x column tiles; up to
+//               double for rows of x or W that are no whole 16-byte pieces, more
+//               with the columns per tile where both are, and less in the
+//               reversed direction, whose rows come ordered by their offsets.
 // Measured (vec / slab us): few rows make the chain the shorter one (400 rows,
 // 25 offsets, fp32 8 -> 128: 15 / 34; bf16 5 -> 10: 12 / 25; 21,774 surface
 // rows 3^3 bf16 3 -> 10: 14 / 31), as do few columns of few planes (400,000
-// rows fp32 1 -> 8: 68 / 200); whole pieces or more columns the matrix cores
-// (345,353 rows fp32 16 -> 4: 255 / 97, 8 -> 16: 421 / 97; 400 rows, 9 offsets
-// 32 -> 24: 27 / 8).
+// rows fp32 1 -> 8: 68 / 200) and few offsets (345,353 rows bf16 12 -> 4
+// reversed: 48 / 174); whole pieces or more columns the matrix cores (345,353
+// rows fp32 16 -> 4: 255 / 97, 8 -> 16: 421 / 97; 400 rows, 9 offsets 32 -> 24:
+// 27 / 8).
 template <typename TIn>
-inline bool vec_first(const FwdView& v, int C_in, int C_out, uint64_t x_bytes,
-                      bool w_rows_whole) {
+inline bool vec_first(const FwdView& v, int C_in, int C_out, bool w_rows_whole) {
   constexpr bool f32 = sizeof(TIn) == 4;
   constexpr int P = 16 / static_cast<int>(sizeof(TIn));
   // (n_cap is a loose bound on the rows of an SC book whose filter exceeds its
-  // stride, see launch_slab_cols)
+  // stride, see launch_slab_cols; the vector kernel's grid covers all of it)
   const double n = static_cast<double>(v.n_src > 0 ? std::min(v.n_src, v.n_cap) : v.n_cap);
   const double k = static_cast<double>(v.K), kr = static_cast<double>(v.K_row);
-  const double chain = std::max(5.0, 0.085 * kr * C_in);
-  const double lanes = (x_bytes > (4u << 20) ? 5.5e-7 : 2.7e-7) * n * kr * C_out * (C_in + 2.0);
-  const bool ax = C_in % P == 0;
+  const bool some = v.K_row < v.K, ax = C_in % P == 0, aw = w_rows_whole;
+  const double chain = std::max(5.0, (some ? 0.1 : 0.085) * kr * C_in);
+  // (of the reversed direction's source rows, far fewer than n, less is read again)
+  const bool past_l2 = n * C_in * sizeof(TIn) > ((some ? 24 : 4) << 20);
+  const double lanes = (past_l2 ? 5.5e-7 : 2.7e-7) * static_cast<double>(v.n_cap) *
+                       std::max<double>(C_out, std::min(4.0, C_in / 6.0)) *
+                       (kr * C_in + 2.0 * k);
   double latency, rate;                    // us per step; us per step, row and column tile
-  int col_tiles;
-  if (ax && w_rows_whole) {
+  int col_tiles = (C_out + 63) / 64;
+  if (ax && aw) {
     const int cb = (C_out + 15) / 16, chunks = (cb + 7) / 8, ncb = (cb + chunks - 1) / chunks;
     const double wide = ncb <= 2 ? 1.0 : ncb <= 4 ? (f32 ? 1.3 : 1.1) : (f32 ? 3.5 : 2.0);
-    latency = (f32 ? 0.56 : 0.35) * wide;
-    rate = (f32 ? 9.6e-6 : 6.3e-6) * wide;
+    latency = (f32 ? 0.56 : 0.35) * wide * (some ? 0.4 : 1.0);
+    rate = (f32 ? 9.6e-6 : 6.3e-6) * wide * (some ? 0.75 : 1.0);
     col_tiles = chunks;
+  } else if (f32) {
+    latency = some ? 0.6 : 0.77;
+    rate = ax ? 1.85e-5 : 2.1e-5;
   } else {
-    latency = f32 ? 0.77 : ax ? 0.84 : 0.9;
-    rate = f32 ? 2.1e-5 : ax ? 1.35e-5 : 1.45e-5 * (1.0 + 0.025 * C_in);
-    col_tiles = (C_out + 63) / 64;
+    latency = aw ? 0.62 : ax ? 0.84 : 0.9;
+    rate = aw ? 1.0e-5 * (1.0 + 0.04 * C_in) : ax ? 1.35e-5 : 1.45e-5 * (1.0 + 0.025 * C_in);
   }
   const double steps = k * ((C_in + MT<TIn>::KC - 1) / MT<TIn>::KC);
   return 3.0 + std::hypot(chain, lanes) <= 4.2 + steps * std::max(latency, rate * n * col_tiles);
@@ -1194,7 +1201,7 @@ void launch_generic(const Call& c, int C_in) {
   const bool wfits = wb < kBufOOB && c.C_out <= kMaxTileCols;
   const bool w_whole = WT != 0 || c.C_out % (16 / static_cast<int>(sizeof(TIn))) == 0;
   if (fits && wfits && !forced_path("vec") &&
-      (by_pairs || forced_path("slab") || !vec_first<TIn>(c.v, C_in, c.C_out, xb, w_whole))) {
+      (by_pairs || forced_path("slab") || !vec_first<TIn>(c.v, C_in, c.C_out, w_whole))) {
     Call cc = c;
     cc.x_bytes = static_cast<uint32_t>(xb);
     slab_entry<TIn, TOut>()(cc, WT, C_in, static_cast<uint32_t>(wb));
