@@ -22,8 +22,8 @@ namespace {
 // Bound: as k_fwd_mfma by the gathers and the per-step latency; these widths
 // ran one lane per output column before, a serial chain of K C_in loads and
 // multiply-adds (87,052 surface rows 192 -> 96 bf16 3^3 with the epilogue:
-// 7,960 us, now 181 us; 64 CAD grids of 32^3, 24 -> 40 fp32 3^3 stride 2, the
-// whole layer with its book: 297 us, now 123 us).  AX / AW: whether the rows of
+// 7,960 us, now 167 us; 64 CAD grids of 32^3, 24 -> 40 fp32 3^3 stride 2, the
+// whole layer with its book: 297 us, now 94 us).  AX / AW: whether the rows of
 // x (and W^T) / of W are whole 16-byte pieces; otherwise single elements are
 // loaded, which needs no alignment beyond the element's.
 template <typename TIn> __device__ __forceinline__ uint32_t buf_elem(__amdgpu_buffer_rsrc_t r,
