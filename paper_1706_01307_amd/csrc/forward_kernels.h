@@ -493,10 +493,11 @@ __device__ __forceinline__ float piece_elem(const u32x4& u, int e) {
 // store instruction writes 64 adjacent bytes of each of its 16 rows instead of
 // 16 bytes in every 64 (348,208 rows 64 -> 64 of one offset 49.2 us, 43.1  now;
 // bf16 stores 16 bytes in every 32 at most, and loses more registers than it
-// gains).
-template <typename TIn, typename TOut, int NCB>
+// gains; so do fp32 tiles of 32 columns on more offsets, whose stores are few:
+// SHORT false, 29,760 pen rows 32 -> 32 3^2 11.2 us with short runs, 10.8 without).
+template <typename TIn, typename TOut, int NCB, bool SHORT>
 struct TileCols {
-  static constexpr int kRun = sizeof(TIn) == 4 && sizeof(TOut) == 4 ? 4 : 4 * NCB;
+  static constexpr int kRun = SHORT && sizeof(TIn) == 4 && sizeof(TOut) == 4 ? 4 : 4 * NCB;
   // LDS row of column n
   __device__ static int row_of(int n) {
     if constexpr (kRun == 4 * NCB) return n % kRun / 4 * 16 + n / kRun * 4 + n % 4;
@@ -516,13 +517,13 @@ struct TileCols {
 // rowv: the output row of the wave's row map_lane (-1: none).  FULL: every
 // column of the tile exists; otherwise columns past C_out are dropped, and rows
 // that are no whole pieces go element by element.
-template <typename TIn, typename TOut, int RB, int NCB, bool FULL>
+template <typename TIn, typename TOut, int RB, int NCB, bool FULL, bool SHORT>
 __device__ __forceinline__ void store_tile(const f32x4 (&acc)[RB][NCB], int32_t rowv,
                                            const float* bias, TOut* y, int C_out, int col0,
                                            int lg, const Epilogue& epi) {
   constexpr int LC = 4 * NCB;
   constexpr int P16 = 16 / static_cast<int>(sizeof(TOut));
-  using TC = TileCols<TIn, TOut, NCB>;
+  using TC = TileCols<TIn, TOut, NCB, SHORT>;
   constexpr int PC = LC < P16 ? LC : P16;         // (one block of bf16 columns: 8 bytes)
   constexpr int NP = LC / PC;
   const int n0 = col0 + lg * TC::kRun;            // the lane's e-th column: n0 + col(e)
@@ -795,7 +796,8 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
   // ---- registers -> LDS, transposed: one LDS row per column n holding
   // W^i[k][n] for all k (TileCols); the lanes that read one fragment chunk
   // together read 16 consecutive rows (spread over the banks by WImage).
-  auto w_row = [](int n) { return TileCols<TIn, TOut, NCB>::row_of(n); };
+  constexpr bool kShort = NCB >= 4 || KT == 1;
+  auto w_row = [](int n) { return TileCols<TIn, TOut, NCB, kShort>::row_of(n); };
   auto w_store = [&](int i, const WRegs& wr) {
     if (i >= K) return;
     unsigned char* dst = s_w[i & 1];
@@ -981,7 +983,7 @@ __global__ __launch_bounds__(256, (kNear<TIn, NCH, NCB, RB, KT> ? 3 : 2)) void k
   int32_t row = -1;
   if constexpr (PAIRS) row = pair_row(gmap, pt, static_cast<int>(map_row), 0);
   else if (map_row < n_rows) row = perm[map_row];
-  store_tile<TIn, TOut, RB, NCB, true>(acc, row, bias, y, C_out, col0, lg, epi);
+  store_tile<TIn, TOut, RB, NCB, true, kShort>(acc, row, bias, y, C_out, col0, lg, epi);
 }
 
 // ---------------------------------------------------------------------------

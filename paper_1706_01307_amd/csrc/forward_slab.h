@@ -99,7 +99,7 @@ struct WStage {
       }
     }
   }
-  __device__ static int row_of(int n) { return TileCols<TIn, TOut, NCB>::row_of(n); }
+  __device__ static int row_of(int n) { return TileCols<TIn, TOut, NCB, true>::row_of(n); }
   __device__ static void store(unsigned char* dst, const Regs& r) {
 #pragma unroll
     for (int q = 0; q < TPT; ++q) {
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_slab(
     }
     row = map_row < n_rows ? perm[map_row] : -1;
   }
-  store_tile<TIn, TOut, RB, NCB, false>(acc, row, bias, y, C_out, col0, lg, epi);
+  store_tile<TIn, TOut, RB, NCB, false, true>(acc, row, bias, y, C_out, col0, lg, epi);
 }
 
 template <typename TIn, typename TOut, int WT, int NCH, int NCB, int RB, bool AX, bool AW>

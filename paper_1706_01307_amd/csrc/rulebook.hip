@@ -1261,7 +1261,8 @@ __global__ __launch_bounds__(kBlock) void k_sc_mark(
 //   kMarkFan: the k of all dimensions are walked directly, 8 sites at a time,
 //   their bitmap words in flight together: 18 us instead of 40 us on 27,072
 //   shuffled rows 3^3 stride 2, whose waves found some row matching in each
-//   of the 27 offsets' rounds and waited out every round's load.
+//   of the 27 offsets' rounds and waited out every round's load (15 us by
+//   bytes; these are grids of more than 64 cells a row).
 //   kMarkBytes: as kMarkFan, a byte per output cell instead of a bit: plain
 //   stores, no atomics on words that many rows share; k_bytes_bits makes the
 //   bitmap.  1,703,204 surface rows 2^3 stride 2: 82 us in rounds, 79 us in
