@@ -49,9 +49,13 @@ constexpr int kWave = 64;
 // Test knob: SPCONV_FORCE_PATH=vec runs the vector path for shapes the
 // matrix-core path would take; =slab runs k_fwd_slab for shapes that k_fwd_vec
 // is estimated to finish first.
-bool forced_path(const char* name) {
+enum class Forced { kNone, kVec, kSlab };
+Forced forced_path() {
   const char* e = std::getenv("SPCONV_FORCE_PATH");
-  return e && std::strcmp(e, name) == 0;
+  if (!e) return Forced::kNone;
+  return std::strcmp(e, "vec") == 0    ? Forced::kVec
+         : std::strcmp(e, "slab") == 0 ? Forced::kSlab
+                                       : Forced::kNone;
 }
 
 constexpr uint32_t kBufDword3 = 0x00020000u;   // gfx9 raw buffer descriptor word 3
@@ -1182,7 +1186,7 @@ inline bool vec_first(const FwdView& v, int C_in, int C_out, bool w_rows_whole) 
 
 // Channel counts k_fwd_mfma is not compiled for.
 template <typename TIn, typename TOut, int WT>
-void launch_generic(const Call& c, int C_in) {
+void launch_generic(const Call& c, int C_in, Forced forced) {
   // buffer ranges (inputs, weights, one offset's map row) are kept below 2^31
   // bytes; lowc also needs one grid row of blocks per kLowCols columns (at
   // most 65535).  Below kLowMinRows positions of few planes the
@@ -1202,8 +1206,8 @@ void launch_generic(const Call& c, int C_in) {
   }
   const bool wfits = wb < kBufOOB && c.C_out <= kMaxTileCols;
   const bool w_whole = WT != 0 || c.C_out % (16 / static_cast<int>(sizeof(TIn))) == 0;
-  if (fits && wfits && !forced_path("vec") &&
-      (by_pairs || forced_path("slab") || !vec_first<TIn>(c.v, C_in, c.C_out, w_whole))) {
+  if (fits && wfits && forced != Forced::kVec &&
+      (by_pairs || forced == Forced::kSlab || !vec_first<TIn>(c.v, C_in, c.C_out, w_whole))) {
     Call cc = c;
     cc.x_bytes = static_cast<uint32_t>(xb);
     slab_entry<TIn, TOut>()(cc, WT, C_in, static_cast<uint32_t>(wb));
@@ -1214,20 +1218,21 @@ void launch_generic(const Call& c, int C_in) {
 
 template <int WT>
 void run(const Call& c, int in_dt, int out_dt, int C_in) {
+  const Forced forced = forced_path();
   bool done = false;
-  if (!forced_path("vec")) {
+  if (forced != Forced::kVec) {
     done = out_dt == SPCONV_F32 ? try_mfma<float, WT>(c, in_dt, C_in)
                                 : try_mfma<uint16_t, WT>(c, in_dt, C_in);
   }
   if (done) return;
   if (in_dt == SPCONV_F32 && out_dt == SPCONV_F32)
-    launch_generic<float, float, WT>(c, C_in);
+    launch_generic<float, float, WT>(c, C_in, forced);
   else if (in_dt == SPCONV_F32)
-    launch_generic<float, uint16_t, WT>(c, C_in);
+    launch_generic<float, uint16_t, WT>(c, C_in, forced);
   else if (out_dt == SPCONV_F32)
-    launch_generic<uint16_t, float, WT>(c, C_in);
+    launch_generic<uint16_t, float, WT>(c, C_in, forced);
   else
-    launch_generic<uint16_t, uint16_t, WT>(c, C_in);
+    launch_generic<uint16_t, uint16_t, WT>(c, C_in, forced);
 }
 
 }  // namespace
